@@ -1488,6 +1488,14 @@ void build_context(infoli_ctx* c, const infoli_network_spec* specs, int32_t nins
             dp.c0 = q.cell_begin;
             dp.c1 = q.cell_end < 0 ? s.n_cells : q.cell_end;
             dp.pad0 = 0;
+            if (p == 0) {
+                InstDesc& dw = c->inst[k];
+                dw.p0_n0 = dp.n0;
+                dw.p0_n1 = dp.n1;
+                dw.p0_amp = dp.amp;
+                dw.p0_c0 = dp.c0;
+                dw.p0_c1 = dp.c1;
+            }
         }
         if (s.i_stream)
             std::memcpy(&h_stream[d.stream_off], s.i_stream, sizeof(float) * s.i_stream_steps * n);

@@ -86,6 +86,10 @@ struct InstDesc {
     int64_t psym_off;      // sym: offset of the network's partial sums in StepArgs::psym
     int32_t sym_ki;        // sym: row blocks per workgroup of k_pairs_sym
     int32_t stream_round;  // stream: chunks per round (0: kStreamRound)
+    int64_t p0_n0, p0_n1;  // the first pulse (StepArgs::pulses[pulse_off]), an empty window without
+    float p0_amp;          // pulses: read with the descriptor, not by a load of its own that the
+    int32_t p0_c0, p0_c1;  // cells' waves would wait for before their gap work
+    int32_t pad0;
     CellParams p;
 };
 
@@ -1336,7 +1340,8 @@ __device__ __forceinline__ void gap_bitmap(const StepArgs& a, const InstDesc& d,
 __device__ __forceinline__ float evoked_input(const StepArgs& a, const InstDesc& d, int64_t step,
                                               int li, int64_t cell) {
     float iapp = a.bias[cell];
-    for (int k = 0; k < d.n_pulses; ++k) {
+    if (step >= d.p0_n0 && step < d.p0_n1 && li >= d.p0_c0 && li < d.p0_c1) iapp += d.p0_amp;
+    for (int k = 1; k < d.n_pulses; ++k) {
         const DevPulse pl = a.pulses[d.pulse_off + k];
         if (step >= pl.n0 && step < pl.n1 && li >= pl.c0 && li < pl.c1) iapp += pl.amp;
     }
