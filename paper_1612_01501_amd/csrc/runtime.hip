@@ -287,7 +287,7 @@ size_t lds_floats_for(const infoli_ctx* c, const InstDesc& d, int block) {
         return (size_t)(block >= 1024 ? stream_lds_floats<1024>(c->blk_cols) : stream_lds_floats<512>(c->blk_cols)) +
                kMaxTileRows;   // the row sums (no static LDS in the stream variant)
     if (d.conn == CONN_CSR && d.blocked)   // the column block, then the tile rows' own voltages
-        return d.cb_off >= 0 ? (size_t)c->blk_cols + kSelfSlots : (size_t)std::min(d.n, c->blk_cols);
+        return (size_t)c->blk_cols + kSelfSlots;
     if (d.conn == CONN_UNIFORM && d.sgj && d.sym) return 4;
     if (d.conn == CONN_UNIFORM) return (size_t)std::min(d.n, kChunk) + 8 * (size_t)(block / 64);
     if (d.conn == CONN_CSR && d.bitmap) return bitmap_lds_floats(d.n);
@@ -393,39 +393,6 @@ void build_bitmaps(infoli_ctx* c, const infoli_network_spec* specs) {
     HIPX(hipMemcpy(c->d_bits, h.data(), sizeof(uint32_t) * words, hipMemcpyHostToDevice));
 }
 
-// Column blocks of CSR networks too large for one LDS copy of Vd: for each
-// row, the offset (from the row start) of its first edge in each block of
-// blk_cols cells (columns are sorted).
-void build_blocks(infoli_ctx* c, const infoli_network_spec* specs) {
-    int64_t total = 0;
-    for (int k = 0; k < c->n_inst; ++k) {
-        InstDesc& d = c->inst[k];
-        d.blk_off = -1;
-        d.nblk = 0;
-        if (d.conn != CONN_CSR || d.n <= kChunk || specs[k].nnz == 0) continue;
-        d.nblk = (d.n + c->blk_cols - 1) / c->blk_cols;
-        d.blk_off = total;
-        total += (int64_t)d.n * d.nblk;
-    }
-    if (total == 0) return;
-    std::vector<int32_t> h((size_t)total);
-    for (int k = 0; k < c->n_inst; ++k) {
-        const InstDesc& d = c->inst[k];
-        if (d.blk_off < 0) continue;
-        const infoli_network_spec& s = specs[k];
-        for (int i = 0; i < d.n; ++i) {
-            const int64_t rs = s.row_ptr[i], re = s.row_ptr[i + 1];
-            int64_t e = rs;
-            for (int b = 0; b < d.nblk; ++b) {
-                while (e < re && s.col[e] < b * c->blk_cols) ++e;
-                h[(size_t)(d.blk_off + (int64_t)i * d.nblk + b)] = (int32_t)(e - rs);
-            }
-        }
-    }
-    c->d_blk = c->alloc<int32_t>((size_t)total);
-    HIPX(hipMemcpy(c->d_blk, h.data(), sizeof(int32_t) * total, hipMemcpyHostToDevice));
-}
-
 // Chunked column lists for 16-byte vector loads (kChunkCols 16-bit columns
 // per chunk). Rows layout, for networks whose columns fit 16 bits: row i's
 // columns padded with i itself to whole chunks; per row its first chunk
@@ -493,8 +460,11 @@ void build_chunks(infoli_ctx* c, const infoli_network_spec* specs) {
     for (int k = 0; k < c->n_inst; ++k) {
         InstDesc& d = c->inst[k];
         d.ca_off = d.cb_off = d.chk_off = d.chkb_off = -1;
+        d.nblk = 0;
         const infoli_network_spec& s = specs[k];
         if (d.conn != CONN_CSR || s.nnz == 0) continue;
+        // networks too large for one LDS copy of Vd have column blocks
+        if (d.n > kChunk) d.nblk = (d.n + C - 1) / C;
         any_w = any_w || d.has_w;
         if (d.n <= 65536) {
             int64_t ch = 0;
@@ -505,7 +475,7 @@ void build_chunks(infoli_ctx* c, const infoli_network_spec* specs) {
             d.chk_off = nchunks;
             nchunks += ch;
         }
-        if (d.blk_off >= 0 && C + kSelfSlots <= 65536) {
+        if (d.nblk > 0 && C + kSelfSlots <= 65536) {
             int64_t ch = 0;
             for (int i = 0; i < d.n; ++i) {
                 int64_t e = s.row_ptr[i];
@@ -653,7 +623,7 @@ void build_chunks(infoli_ctx* c, const infoli_network_spec* specs) {
 // timed on the network's own device data with dry launches (they write only
 // the next-state buffer) replayed from graphs, as steps run, and the fastest
 // is kept, in memory and in an
-// on-disk cache (INFOLI_TUNE_CACHE, else ~/.cache/infoli-tune-v13.txt).
+// on-disk cache (INFOLI_TUNE_CACHE, else ~/.cache/infoli-tune-v15.txt).
 struct TuneChoice {
     int L, R, lds, bm;     // lanes per row, rows per tile, Vd in LDS,
                            // path (0 gathers, 1 bitmap, 2 blocked, 3 chunked gathers,
@@ -666,7 +636,7 @@ std::string tune_cache_path() {
     const char* p = std::getenv("INFOLI_TUNE_CACHE");
     if (p && *p) return p;
     const char* h = std::getenv("HOME");
-    if (h && *h) return std::string(h) + "/.cache/infoli-tune-v14.txt";
+    if (h && *h) return std::string(h) + "/.cache/infoli-tune-v15.txt";
     return "";
 }
 
@@ -675,7 +645,7 @@ std::string tune_key(const infoli_ctx* c, const InstDesc& d, double deg) {
     const int db = (int)std::ceil(std::log2(deg + 1.0) * 4.0);
     char buf[128];
     snprintf(buf, sizeof buf, "gfx950 groups2 c16=%d w=%d bits=%d blk=%d n%d d%d%s", d.col16, d.has_w,
-             d.bits_off >= 0 ? 1 : 0, d.blk_off >= 0 ? c->blk_cols : 0, nb, db, d.sgj ? " sgj" : "");
+             d.bits_off >= 0 ? 1 : 0, d.cb_off >= 0 ? c->blk_cols : 0, nb, db, d.sgj ? " sgj" : "");
     return buf;
 }
 
@@ -860,8 +830,8 @@ TuneChoice pick_shape(const std::vector<std::pair<float, TuneChoice>>& v) {
 
 void apply_choice(infoli_ctx* c, const std::vector<int>& ks, TuneChoice best) {
     for (int k : ks)   // a cached choice this context cannot honour falls back to gathers
-        if ((best.bm == 1 && c->inst[k].bits_off < 0) || (best.bm == 2 && c->inst[k].blk_off < 0) ||
-            (best.bm == 3 && c->inst[k].ca_off < 0) || (best.bm == 4 && c->inst[k].cb_off < 0))
+        if ((best.bm == 1 && c->inst[k].bits_off < 0) || (best.bm == 3 && c->inst[k].ca_off < 0) ||
+            ((best.bm == 2 || best.bm == 4) && c->inst[k].cb_off < 0))
             best = TuneChoice{std::min(best.L, 256), std::max(1, 256 / std::min(best.L, 256)), 0, 0, 256};
     for (int k : ks) {
         c->inst[k].lanes_per_row = best.L;
@@ -918,6 +888,7 @@ void autotune_shapes(infoli_ctx* c) {
         TuneChoice best, best256, best256nc;   // overall; in 256 threads; in 256 threads, not chunked
         TuneChoice best1024;                   // in 1024 threads (block 0: none timed)
         TuneChoice bm256, bm1024;              // the bitmap path in 256 / 1024 threads (block 0: none)
+        bool bits = false;                     // a bitmap shape that the whole step may force (bit 5)
         TuneChoice alt[kAlts];                 // the fastest distinct 256-thread shapes, fastest first
         int nalt = 0;
     };
@@ -1024,8 +995,8 @@ void autotune_shapes(infoli_ctx* c) {
                             consider(TuneChoice{64, kSelfSlots, 0, 4, blk, rnd});
                 }
             // the column-blocked path, when every network of the class has it
-            bool all_blk = c->d_blk != nullptr;
-            for (int k : ks) all_blk = all_blk && c->inst[k].blk_off >= 0;
+            bool all_blk = c->d_cb != nullptr;
+            for (int k : ks) all_blk = all_blk && c->inst[k].cb_off >= 0;
             if (all_blk)
                 for (int L = 8; L <= 64; L *= 2) {
                     if (L > 8 && L > 2.0 * deg / c->inst[ks[0]].nblk) break;
@@ -1060,6 +1031,11 @@ void autotune_shapes(infoli_ctx* c) {
         cc.best1024 = best1024;
         cc.bm256 = bm256;
         cc.bm1024 = bm1024;
+        // the bitmap evaluates every pair (8.3 issue slots) where the lists
+        // evaluate their edges (10.3): below a density of a fifth it does at
+        // least four times the work, so the whole step does not force it
+        cc.bits = bm256.block || bm1024.block;
+        for (int k : ks) cc.bits = cc.bits && c->deg_of[k] >= 0.2 * c->inst[k].n;
         chosen[key] = cc;
     }
 
@@ -1079,12 +1055,12 @@ void autotune_shapes(infoli_ctx* c) {
     // variant of the per-class choices: bit 0, each class in its best
     // 256-thread shape; bit 3, each class in its best 1024-thread shape;
     // bit 2, chunked gathers in 256 threads replaced by the best
-    // non-chunked 256-thread shape; bit 5, every class that has a bitmap
-    // shape takes it (in 1024 threads under bit 3 when timed, else in 256):
-    // timed alone a class can rank the bitmap and its gathers differently
-    // from the whole step
+    // non-chunked 256-thread shape; bit 5, every class with a bitmap shape
+    // and a density of a fifth or more takes it (in 1024 threads under bit 3
+    // when timed, else in 256): timed alone a class can rank the bitmap and its
+    // gathers differently from the whole step
     auto pick = [&](const ClassChoice& ch, int m) {
-        if ((m & 32) && (ch.bm256.block || ch.bm1024.block))
+        if ((m & 32) && ch.bits)
             return ((m & 8) && ch.bm1024.block) || !ch.bm256.block ? ch.bm1024 : ch.bm256;
         TuneChoice t = (m & 8) && ch.best1024.block == 1024 ? ch.best1024 : (m & 1) ? ch.best256 : ch.best;
         if ((m & 4) && t.bm == 3 && t.block == 256) t = ch.best256nc;
@@ -1111,7 +1087,7 @@ void autotune_shapes(infoli_ctx* c) {
     } else {
         bool wide = false, chunk = false, narrow = false, bits = false;   // variants that change something
         for (const auto& kv : chosen) {
-            bits = bits || kv.second.bm256.block || kv.second.bm1024.block;
+            bits = bits || kv.second.bits;
             wide = wide || kv.second.best.block != 256;
             narrow = narrow || (kv.second.best.block == 256 && kv.second.best1024.block == 1024);
             chunk = chunk || kv.second.best.bm == 3 || kv.second.best256.bm == 3;
@@ -1551,13 +1527,12 @@ void build_context(infoli_ctx* c, const infoli_network_spec* specs, int32_t nins
     HIPX(hipMemset(c->igap, 0, sizeof(float) * S));
     HIPX(hipDeviceSynchronize());
     build_bitmaps(c, specs);
-    build_blocks(c, specs);
     build_chunks(c, specs);
     build_sym(c);
     if (c->opt.autotune && c->opt.csr_path == 0) autotune(c);
     if (c->opt.csr_path == 3)
         for (int k = 0; k < ninst; ++k)
-            if (c->inst[k].blk_off >= 0) {
+            if (c->inst[k].cb_off >= 0) {
                 c->inst[k].blocked = 1;
                 c->inst[k].lanes_per_row = std::min(64, std::max(8, c->inst[k].lanes_per_row));
                 c->rows_of[k] = std::min(kMaxTileRows, 1024 / c->inst[k].lanes_per_row);
@@ -1603,7 +1578,6 @@ StepArgs infoli_rt::make_args(const infoli_ctx* c, bool device_step) {
     a.col = c->d_col;
     a.col16 = c->d_col16;
     a.bits = c->d_bits;
-    a.blk = c->d_blk;
     a.ca = c->d_ca;
     a.cb = c->d_cb;
     a.chk = c->d_chk;
@@ -2013,8 +1987,7 @@ infoli_status infoli_get_gap_path(const infoli_ctx* ctx, int32_t instance, int32
         check_instance(ctx, instance);
         // the step kernel's own dispatch: the bitmap first; column blocks
         // only in the wide launch group (chunked when the block-major chunk
-        // layout exists; simplified networks without it take row gathers);
-        // else chunked rows or plain gathers
+        // layout exists); else chunked rows or plain gathers
         const InstDesc& d = ctx->inst[instance];
         int32_t p = INFOLI_PATH_NONE, blk = 0;
         if (d.conn == CONN_UNIFORM)
@@ -2028,7 +2001,6 @@ infoli_status infoli_get_gap_path(const infoli_ctx* ctx, int32_t instance, int32
             else if (d.bitmap) p = INFOLI_PATH_CSR_BITMAP;
             else if (wide && d.blocked && d.stream && d.cb_off >= 0) p = INFOLI_PATH_CSR_STREAM, blk = 1;
             else if (wide && d.blocked && d.cb_off >= 0) p = INFOLI_PATH_CSR_CHUNKED, blk = 1;
-            else if (wide && d.blocked && !d.sgj) p = INFOLI_PATH_CSR_GATHER, blk = 1;
             else p = d.chunked && d.ca_off >= 0 ? INFOLI_PATH_CSR_CHUNKED : INFOLI_PATH_CSR_GATHER;
         }
         if (path) *path = p;

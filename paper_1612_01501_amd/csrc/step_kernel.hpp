@@ -20,8 +20,8 @@
 //                the groups; every pair is evaluated and masked.
 //   BLOCKED CSR  (networks too large for one LDS copy of Vd) Vd is staged in
 //                LDS one column block at a time; each row's edges of that
-//                block (precomputed offsets, columns sorted) gather from LDS;
-//                partial sums stay in registers across blocks.
+//                block (16-byte chunks of columns relative to the block)
+//                gather from LDS; partial sums stay in registers across blocks.
 //   CSR          groups of L lanes per row stride over the row's edges and
 //                gather Vd of the neighbours, from a copy of the network's
 //                Vd staged in LDS when the tile's edges outnumber the cells,
@@ -78,7 +78,6 @@ struct InstDesc {
                            // unordered pair once (k_pairs_sym), or for the simplified term the
                            // voltage sum (k_vsum)
     int64_t bits_off;      // bitmap: offset of the network's first word
-    int64_t blk_off;       // blocked: offset of the network's [n][nblk] block starts
     int64_t ca_off;        // chunked rows: offset of the [n + 1] row chunk starts, -1 none
     int64_t chk_off;       // chunked rows: first chunk of the network
     int64_t cb_off;        // chunked blocks: offset of the [n][nblk + 1] chunk starts, -1 none
@@ -116,7 +115,6 @@ struct StepArgs {
     const int32_t* col;        // CSR columns (local cell index)
     const uint16_t* col16;     // CSR columns, 16-bit form
     const uint32_t* bits;      // coupling bitmaps
-    const int32_t* blk;        // blocked CSR: per row, first edge of each column block
     int32_t blk_cols;          // blocked CSR: cells per column block
     const int32_t* ca;         // chunked rows: per row, first chunk (relative to the network's)
     const int32_t* cb;         // chunked blocks: per row and block, first chunk
@@ -595,101 +593,6 @@ __device__ __forceinline__ void gap_csr_impl(const StepArgs& a, const InstDesc& 
 }
 
 constexpr int kBlkPasses = 4;       // row passes per tile kept in registers
-
-template <int BLOCK, bool C16, bool HASW>
-__device__ __forceinline__ void gap_csr_blocked(const StepArgs& a, const InstDesc& d, const Tile& t,
-                                                const float* __restrict__ vd, float* s_vd, float* s_part,
-                                                float* s_ig) {
-    const int L = d.lanes_per_row;
-    const int groups = BLOCK / L;
-    const int grp = threadIdx.x / L;
-    const int lig = threadIdx.x % L;
-    const int C = a.blk_cols;
-    const int64_t* rp = a.row_ptr + d.rp_off;
-    const int32_t* c32 = a.col + d.w_off;
-    const uint16_t* c16 = a.col16 + d.w_off;
-    const float* wv = a.w + d.w_off;
-    const int32_t* bo = a.blk + d.blk_off;
-    float acc[kBlkPasses], vi[kBlkPasses];
-#pragma unroll
-    for (int q = 0; q < kBlkPasses; ++q) {
-        acc[q] = 0.0f;
-        const int r = t.row0 + q * groups + grp;
-        vi[q] = r < t.row1 ? vd[r] * kPreScale : 0.0f;
-    }
-    for (int b = 0; b < d.nblk; ++b) {
-        const int j0 = b * C;
-        const int jn = min(C, d.n - j0);
-        __syncthreads();
-        for (int k = threadIdx.x; k < jn; k += BLOCK) s_vd[k] = vd[j0 + k] * kPreScale;
-        __syncthreads();
-        const float* sb = s_vd - j0;      // indexed by the global column
-#pragma unroll
-        for (int q = 0; q < kBlkPasses; ++q) {
-            const int r = t.row0 + q * groups + grp;
-            if (r >= t.row1) continue;
-            const int64_t rs = rp[r];
-            const int64_t e = b + 1 < d.nblk ? rs + bo[(int64_t)r * d.nblk + b + 1] : rp[r + 1];
-            int64_t k = rs + bo[(int64_t)r * d.nblk + b] + lig;
-            float a0 = 0.0f, a1 = 0.0f;
-            for (; k + (kBatch - 1) * L < e; k += kBatch * L) {
-                int j[kBatch];
-                float w[kBatch];
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    j[u] = C16 ? (int)c16[k + u * L] : c32[k + u * L];
-                    w[u] = HASW ? wv[k + u * L] : 1.0f;
-                }
-#pragma unroll
-                for (int u = 0; u < kBatch; u += 2) {
-                    const float d0 = vi[q] - sb[j[u]], d1 = vi[q] - sb[j[u + 1]];
-                    a0 = fmaf(w[u], d0 * gap_factor_ps(d0), a0);
-                    a1 = fmaf(w[u + 1], d1 * gap_factor_ps(d1), a1);
-                }
-            }
-            // the remaining (< kBatch) edges as one masked batch: loads in
-            // flight together; a masked entry reads slot 0 with weight 0
-            if (k < e) {
-                int j[kBatch];
-                float w[kBatch];
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    const bool ok = k + u * L < e;
-                    j[u] = ok ? (C16 ? (int)c16[k + u * L] : c32[k + u * L]) : j0;
-                    w[u] = ok ? (HASW ? wv[k + u * L] : 1.0f) : 0.0f;
-                }
-#pragma unroll
-                for (int u = 0; u < kBatch; u += 2) {
-                    const float d0 = vi[q] - sb[j[u]], d1 = vi[q] - sb[j[u + 1]];
-                    a0 = fmaf(w[u], d0 * gap_factor_ps(d0), a0);
-                    a1 = fmaf(w[u + 1], d1 * gap_factor_ps(d1), a1);
-                }
-            }
-            acc[q] += a0 + a1;
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < kBlkPasses; ++q) {
-        const int r = t.row0 + q * groups + grp;
-        float v = acc[q];
-        if (L <= 64) {
-            v = wave_sum_xor(v, L) * kInvPreScale;
-            if (r < t.row1 && lig == 0) s_ig[r - t.row0] = HASW ? v : d.g * v;
-        } else {
-            v = wave_sum_xor(v, 64);
-            const int wave = threadIdx.x >> 6;
-            __syncthreads();
-            if ((threadIdx.x & 63) == 0) s_part[wave] = v;
-            __syncthreads();
-            if (lig == 0 && r < t.row1) {
-                float tot = 0.0f;
-                for (int w = 0; w < L / 64; ++w) tot += s_part[wave + w];
-                tot *= kInvPreScale;
-                s_ig[r - t.row0] = HASW ? tot : d.g * tot;
-            }
-        }
-    }
-}
 
 // ---------------------------------------------------------------- chunked CSR
 // Column lists in 16-byte chunks of eight 16-bit columns, read with one
@@ -1173,9 +1076,7 @@ __device__ __forceinline__ void by_weights(const InstDesc& d, F&& f) {
     f(std::false_type{});
 }
 
-// CSR paths of one gap form (SGJ: simplified). The old column-blocked
-// gathers (no chunked copy of the lists) exist for the realistic form only;
-// a simplified network without chunks takes the plain gathers.
+// CSR paths of one gap form (SGJ: simplified).
 template <int BLOCK, bool SGJ, bool W>
 __device__ __forceinline__ void gap_csr_form(const StepArgs& a, const InstDesc& d, const Tile& t,
                                              const float* __restrict__ vd, float* s_vd, float* s_part,
@@ -1189,15 +1090,6 @@ __device__ __forceinline__ void gap_csr_form(const StepArgs& a, const InstDesc& 
                 gap_chunks_blocked<BLOCK, decltype(hw)::value, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
             });
             return;
-        }
-        if constexpr (!SGJ) {
-            if (d.blocked) {
-                by_weights<W>(d, [&](auto hw) {
-                    if (d.col16) gap_csr_blocked<BLOCK, true, decltype(hw)::value>(a, d, t, vd, s_vd, s_part, s_ig);
-                    else gap_csr_blocked<BLOCK, false, decltype(hw)::value>(a, d, t, vd, s_vd, s_part, s_ig);
-                });
-                return;
-            }
         }
     }
     if (d.vd_lds) {
