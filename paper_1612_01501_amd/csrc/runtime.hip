@@ -184,16 +184,24 @@ void infoli_rt::launch_tiles(infoli_ctx* c, hipStream_t st, const StepArgs& a, i
     else if (block == 1024 && var == kVarStream)
         hipLaunchKernelGGL((k_step<1024, kVarStream>), dim3(ntiles), dim3(1024), lds, st, a, xin, xout, step_arg,
                            off);
+    else if (block == 512 && var == kVarBoth)
+        hipLaunchKernelGGL((k_step<512, kVarBoth>), dim3(ntiles), dim3(512), lds, st, a, xin, xout, step_arg, off);
     else if (block == 512 && var == kVarNoW)
         hipLaunchKernelGGL((k_step<512, kVarNoW>), dim3(ntiles), dim3(512), lds, st, a, xin, xout, step_arg, off);
     else if (block == 512)
         hipLaunchKernelGGL((k_step<512, kVarAll>), dim3(ntiles), dim3(512), lds, st, a, xin, xout, step_arg, off);
+    else if (block == 1024 && var == kVarBoth)
+        hipLaunchKernelGGL((k_step<1024, kVarBoth>), dim3(ntiles), dim3(1024), lds, st, a, xin, xout, step_arg, off);
     else if (block == 1024 && var == kVarNoW)
         hipLaunchKernelGGL((k_step<1024, kVarNoW>), dim3(ntiles), dim3(1024), lds, st, a, xin, xout, step_arg, off);
     else if (block == 1024)
         hipLaunchKernelGGL((k_step<1024, kVarAll>), dim3(ntiles), dim3(1024), lds, st, a, xin, xout, step_arg, off);
     else if (var == kVarNoGap)
         hipLaunchKernelGGL((k_step<256, kVarNoGap>), dim3(ntiles), dim3(256), lds, st, a, xin, xout, step_arg, off);
+    else if (var == kVarDense)
+        hipLaunchKernelGGL((k_step<256, kVarDense>), dim3(ntiles), dim3(256), lds, st, a, xin, xout, step_arg, off);
+    else if (var == kVarBoth)
+        hipLaunchKernelGGL((k_step<256, kVarBoth>), dim3(ntiles), dim3(256), lds, st, a, xin, xout, step_arg, off);
     else if (var == kVarNoW)
         hipLaunchKernelGGL((k_step<256, kVarNoW>), dim3(ntiles), dim3(256), lds, st, a, xin, xout, step_arg, off);
     else
@@ -338,15 +346,22 @@ void finalize_tiles(infoli_ctx* c) {
         std::stable_sort(planned[g].begin(), planned[g].end(),
                          [](const auto& x, const auto& y) { return x.first > y.first; });
         tg.tiles.clear();
-        bool nogap = true, now = true, stream = !planned[g].empty();
+        bool nogap = true, now = true, both = false, dense = tg.block == 256, stream = !planned[g].empty();
         for (const auto& pt : planned[g]) {
             tg.tiles.push_back(pt.second);
             const InstDesc& d = c->inst[pt.second.inst];
             if (d.conn != CONN_NONE || d.pcell) nogap = false;
-            if (d.has_w || d.pcell) now = false;
+            if (d.has_w || d.pcell || d.conn == CONN_DENSE) now = false;
+            if (d.conn == CONN_CSR && d.sgj) both = true;
+            if ((d.conn != CONN_DENSE && d.conn != CONN_NONE) || d.pcell) dense = false;
             if (!d.stream) stream = false;
         }
-        tg.var = nogap ? kVarNoGap : stream && tg.block >= 512 ? kVarStream : now ? kVarNoW : kVarAll;
+        tg.var = nogap                       ? kVarNoGap
+                 : dense                     ? kVarDense
+                 : stream && tg.block >= 512 ? kVarStream
+                 : now && both               ? kVarBoth
+                 : now                       ? kVarNoW
+                                             : kVarAll;
         if (tg.tiles.size() > (size_t)INT32_MAX / 2) fail(INFOLI_E_INVALID_ARG, "too many tiles");
         if (!tg.tiles.empty()) {
             if (tg.tiles.size() > tg.cap) {
@@ -769,6 +784,7 @@ float time_shape(infoli_ctx* c, const std::vector<int>& ks, const TuneChoice& t,
     for (int k : ks) {
         InstDesc d = c->inst[k];
         if (d.has_w || d.pcell) var = kVarAll;
+        else if (d.sgj && var == kVarNoW) var = kVarBoth;
         d.lanes_per_row = t.L;
         d.vd_lds = t.lds;
         d.bitmap = t.bm == 1;
@@ -1383,7 +1399,7 @@ void build_context(infoli_ctx* c, const infoli_network_spec* specs, int32_t nins
                 rows = sum_once(c, d) ? kMaxTileRows : kUniformRows;
                 c->deg_of[k] = d.n;
                 break;
-            case CONN_DENSE: rows = c->opt.tile_rows ? c->opt.tile_rows : 16; c->deg_of[k] = d.n; break;
+            case CONN_DENSE: rows = c->opt.tile_rows ? c->opt.tile_rows : kDenseRows; c->deg_of[k] = d.n; break;
             case CONN_CSR: {
                 const double deg = (double)specs[k].nnz / d.n;
                 c->deg_of[k] = deg;
@@ -1494,7 +1510,8 @@ void build_context(infoli_ctx* c, const infoli_network_spec* specs, int32_t nins
         c->d_col = c->alloc<int32_t>(h_col.size());
         c->d_col16 = c->alloc<uint16_t>(1);
     }
-    c->d_w = c->alloc<float>(h_w.size());
+    c->d_w = c->alloc<float>(h_w.size() + kDenseSlack);
+    HIPX(hipMemset(c->d_w + h_w.size(), 0, sizeof(float) * kDenseSlack));
     c->d_stream = c->alloc<float>(h_stream.size());
     c->d_spk_count = c->alloc<int32_t>(S);
     const int cap = c->opt.max_spikes_per_cell;

@@ -479,27 +479,88 @@ static __global__ __launch_bounds__(256) void k_vsum(const float* __restrict__ v
     if (threadIdx.x == 0) out[blockIdx.x] = ((s_w[0] + s_w[1]) + s_w[2]) + s_w[3];
 }
 
-template <int BLOCK>
+// ---------------------------------------------------------------- dense weights
+// The weight matrix is read once per step, 4 bytes a pair, so the loads bound
+// the tile and have to be in flight together. A tile takes kDenseRows rows;
+// the workgroup's waves split the columns into stretches of 256 (four
+// consecutive columns a lane, 16-byte loads; a row may start at any 4-byte
+// boundary), kDenseSteps stretches of all rows loaded before the first is
+// used, the voltages of a stretch loaded once for all rows. Columns past n
+// (the last stretch only) load whatever follows the row (the weight array has
+// kDenseSlack spare entries, the voltage row is followed by other state rows)
+// and count as the row's own voltage, whose term is zero. Four rows and two
+// stretches (ten 16-byte loads a lane in flight, 960 workgroups at 3,840
+// cells): 74.8 -> 14.3 us per step there, where one row per wave with a
+// 4-byte load per pair waited for each load in turn; eight rows 15.6 us, two
+// rows 17.7, four stretches 15.5. The weights are read once per step, so they
+// are loaded past the caches' reuse order (14.8 us without).
+constexpr int kDenseRows = 4;
+constexpr int kDenseSteps = 2;
+constexpr int kDenseSlack = 4;
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int BLOCK, bool SGJ>
 __device__ __forceinline__ void gap_dense(const StepArgs& a, const InstDesc& d, const Tile& t,
-                                          const float* __restrict__ vd, float* s_ig) {
+                                          const float* __restrict__ vd, float* s_part, float* s_ig) {
     constexpr int W = BLOCK / 64;
+    constexpr int R = kDenseRows, U = kDenseSteps;
+    static_assert(W * R <= BLOCK, "a partial sum per wave and row");
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = d.n;
-    for (int r = t.row0 + wave; r < t.row1; r += W) {
-        const float vi = vd[r];
-        const float* wr = a.w + d.w_off + (int64_t)r * n;
-        float acc = 0.0f;
-        if (d.sgj) {
-            for (int j = lane; j < n; j += 64) acc = fmaf(wr[j], vi - vd[j], acc);
-        } else {
-            for (int j = lane; j < n; j += 64) {
-                const float dv = vi - vd[j];
-                acc = fmaf(wr[j], dv * gap_factor(dv), acc);
+    const int steps = (n + 255) / 256;                    // stretches of 256 columns
+    const int per = (steps + W - 1) / W;                  // per wave
+    const int s0 = min(steps, wave * per), s1 = min(steps, s0 + per);
+    const float* w = a.w + d.w_off;
+    for (int r0 = t.row0; r0 < t.row1; r0 += R) {
+        float vi[R], acc[R];
+        const float* wr[R];
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int r = min(r0 + q, t.row1 - 1);
+            vi[q] = vd[r];
+            acc[q] = 0.0f;
+            wr[q] = w + (int64_t)r * n;
+        }
+        for (int s = s0; s < s1; s += U) {
+            f32x4u wv[U][R], v[U];
+            // a step past the wave's last one loads the last one again
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int c = min(s + u, s1 - 1) * 256 + 4 * lane;
+                v[u] = *reinterpret_cast<const f32x4u*>(vd + min(c, n - 1));
+#pragma unroll
+                for (int q = 0; q < R; ++q) wv[u][q] = __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(wr[q] + min(c, n - 1)));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (s + u >= s1) break;
+                const int c = (s + u) * 256 + 4 * lane;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float vj = v[u][e];
+                    const bool in = c + e < n;
+#pragma unroll
+                    for (int q = 0; q < R; ++q) {
+                        const float dv = in ? vi[q] - vj : 0.0f;
+                        acc[q] = fmaf(wv[u][q][e], dv * pair_factor<SGJ, false>(dv), acc[q]);
+                    }
+                }
             }
         }
-        acc = wave_sum_xor(acc, 64);
-        if (lane == 0) s_ig[r - t.row0] = acc;
+#pragma unroll
+        for (int q = 0; q < R; ++q) acc[q] = wave_sum_xor(acc[q], 64);
+        if (lane == 0)
+#pragma unroll
+            for (int q = 0; q < R; ++q) s_part[wave * R + q] = acc[q];
+        __syncthreads();
+        if ((int)threadIdx.x < R && r0 + (int)threadIdx.x < t.row1) {
+            float tot = 0.0f;
+            for (int k = 0; k < W; ++k) tot += s_part[k * R + threadIdx.x];
+            s_ig[r0 + threadIdx.x - t.row0] = tot;
+        }
+        __syncthreads();
     }
 }
 
@@ -1113,12 +1174,18 @@ __device__ __forceinline__ void gap_csr_form(const StepArgs& a, const InstDesc& 
 
 // W: the launch may hold networks with per-edge weights (their paths are
 // compiled in; they hold a batch of weights in registers).
-template <int BLOCK, bool W>
+// L: it may hold networks with the simplified term.
+template <int BLOCK, bool W, bool L>
 __device__ __forceinline__ void gap_csr(const StepArgs& a, const InstDesc& d, const Tile& t,
                                         const float* __restrict__ vd, float* s_vd, float* s_part,
                                         float* s_ig) {
-    if (d.sgj) gap_csr_form<BLOCK, true, W>(a, d, t, vd, s_vd, s_part, s_ig);
-    else gap_csr_form<BLOCK, false, W>(a, d, t, vd, s_vd, s_part, s_ig);
+    if constexpr (L) {
+        if (d.sgj) {
+            gap_csr_form<BLOCK, true, W>(a, d, t, vd, s_vd, s_part, s_ig);
+            return;
+        }
+    }
+    gap_csr_form<BLOCK, false, W>(a, d, t, vd, s_vd, s_part, s_ig);
 }
 
 // Bitmap words of a network: group gr (128 senders), row r (padded to a
@@ -1242,15 +1309,17 @@ __device__ __forceinline__ float evoked_input(const StepArgs& a, const InstDesc&
     return iapp;
 }
 
-// Kernel variants by the tiles a launch holds. kVarAll: any tile. kVarNoGap:
-// every tile belongs to a network without gap junctions (the compartment
-// update alone). kVarNoW: no network has per-edge weights. The narrow
-// variants are compiled without the paths they exclude and their registers
-// (kVarNoW: 85 VGPRs against 124 in 256-thread workgroups), so that more
-// waves per SIMD keep loads in flight. kVarStream: every tile is a chunk
-// stream tile (column blocks, no per-edge weights, no per-cell parameters),
-// the only gap path it compiles.
-enum : int { kVarAll = 0, kVarNoGap = 1, kVarNoW = 2, kVarStream = 3 };
+// Kernel variants by the tiles a launch holds; the narrow ones are compiled
+// without the paths they exclude and their registers, so that more waves per
+// SIMD keep loads in flight. kVarAll: any tile. kVarNoGap: every tile belongs
+// to a network without gap junctions (the compartment update alone). kVarNoW:
+// no per-edge weights, per-cell parameters or dense matrices, and no CSR
+// network with the simplified term. kVarBoth: the same with it. kVarStream:
+// every tile is a chunk stream tile (column blocks, no per-edge weights, no
+// per-cell parameters), the only gap path it compiles. kVarDense: every tile
+// belongs to a network with a dense weight matrix or without gap junctions
+// (256-thread workgroups).
+enum : int { kVarAll = 0, kVarNoGap = 1, kVarNoW = 2, kVarStream = 3, kVarDense = 4, kVarBoth = 5 };
 
 template <int BLOCK, int VAR>
 __device__ __forceinline__ void step_body(const StepArgs& a, const float* __restrict__ xin, float* __restrict__ xout,
@@ -1287,16 +1356,29 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const float* __rest
         else gap_stream_blocked<BLOCK, false>(a, d, t, vd, reinterpret_cast<float*>(s_v4), s_ig);
     } else if constexpr (VAR == kVarNoGap) {
         for (int k = threadIdx.x; k < nrows; k += BLOCK) s_ig[k] = 0.0f;
+    } else if constexpr (VAR == kVarDense) {
+        if (d.conn != CONN_DENSE) {
+            for (int k = threadIdx.x; k < nrows; k += BLOCK) s_ig[k] = 0.0f;
+        } else if (d.sgj) {
+            gap_dense<BLOCK, true>(a, d, t, vd, s_part, s_ig);
+        } else {
+            gap_dense<BLOCK, false>(a, d, t, vd, s_part, s_ig);
+        }
     } else {
         switch (d.conn) {
             case CONN_UNIFORM:
                 if (d.sgj && d.sym) gap_uniform_sum<BLOCK>(a, d, t, vd, s_ig, s_red);
                 else gap_uniform<BLOCK>(a, d, t, vd, s_ig, s_v4, s_part, s_red);
                 break;
-            case CONN_DENSE: gap_dense<BLOCK>(a, d, t, vd, s_ig); break;
+            case CONN_DENSE:
+                if constexpr (VAR != kVarNoW) {
+                    if (d.sgj) gap_dense<BLOCK, true>(a, d, t, vd, s_part, s_ig);
+                    else gap_dense<BLOCK, false>(a, d, t, vd, s_part, s_ig);
+                }
+                break;
             case CONN_CSR:
                 if (d.bitmap) gap_bitmap<BLOCK>(a, d, t, vd, reinterpret_cast<float*>(s_v4), s_part, s_ig);
-                else gap_csr<BLOCK, VAR != kVarNoW>(a, d, t, vd, reinterpret_cast<float*>(s_v4), s_part, s_ig);
+                else gap_csr<BLOCK, VAR == kVarAll, VAR != kVarNoW>(a, d, t, vd, reinterpret_cast<float*>(s_v4), s_part, s_ig);
                 break;
             default:
                 for (int k = threadIdx.x; k < nrows; k += BLOCK) s_ig[k] = 0.0f;
