@@ -197,13 +197,32 @@ def ingest_traffic(run_root):
     print(json.dumps({key: entry}))
 
 
+# All-to-all networks with the realistic term from this size on take their
+# sums on the voltage grid by default (a context's only network from 4,096
+# cells on by a kernel ahead of the step, which gap_path reports as
+# "uniform_sym"; the others tile by tile).
+GRID_CELLS = 512
+
+
+def gap_paths(info, sim, nets):
+    """The library's gap path per network, all-to-all networks on the voltage
+    grid named apart (contexts made with the default pair_path)."""
+    paths = []
+    for k, n in enumerate(nets):
+        p = sim.gap_path(k)[0]
+        if n.conn == "uniform" and n.gap == "rgj" and info["step_mode"] != 3:
+            p = "uniform_grid_ahead" if p == "uniform_sym" else "uniform_grid" if n.n >= GRID_CELLS else p
+        paths.append(p)
+    return paths
+
+
 def tuned_config(info, sim, nets):
     """What the library runs for these networks, as chosen at init."""
     return {"tiles": info["n_tiles"], "tiles_wide": info["n_tiles_wide"], "wide_threads": info["wide_threads"],
             "csr_bitmap_networks": info["n_bitmap"], "csr_blocked_networks": info["n_blocked"],
             "lanes_per_row": info["lanes_per_row"], "tile_rows": info["tile_rows"],
-            "gap_paths": sorted(set(sim.gap_path(k)[0] for k in range(len(nets)))),
-            "step_kernel": step_kernel_name(info, nets, [sim.gap_path(k)[0] for k in range(len(nets))]),
+            "gap_paths": sorted(set(gap_paths(info, sim, nets))),
+            "step_kernel": step_kernel_name(info, nets, gap_paths(info, sim, nets)),
             "tuned_networks": info["tuned"], "tune_cached_networks": info["tune_cached"],
             "csr_stream_networks": info["n_stream"], "tune_mode": info["tune_mode"],
             "stream_round": info["stream_round"], "unordered_pair_networks": info["n_sym"]}
@@ -351,6 +370,8 @@ def slots_of(n, path=None):
     if n.conn == "uniform" and path == "uniform_sym":
         own = (n.n + 63) // 64 * 64 * 64
         s += SYM_SLOTS_PER_PAIR * (n.n * n.n - own) / 2 + UNIFORM_SLOTS_PER_PAIR * own
+    elif n.conn == "uniform" and path in ("uniform_grid", "uniform_grid_ahead"):
+        pass        # O(n) fp64 sums at the grid points, not counted
     elif n.conn == "uniform":
         s += UNIFORM_SLOTS_PER_PAIR * n.n * n.n
     elif n.conn == "csr" and path == "csr_bitmap":
@@ -363,8 +384,10 @@ def slots_of(n, path=None):
 def step_kernel_name(info, nets, paths=None):
     """The kernel(s) one step launches, from the context's launch groups and
     the variant the runtime picks for them: 1 when no network has gap
-    junctions, 3 when every network runs the chunk stream (the wide group
-    only), 2 when none has per-edge weights or per-cell parameters, else 0."""
+    junctions, 4 when every one has a dense weight matrix or none, 3 when
+    every network runs the chunk stream (the wide group only), 0 when one has
+    per-edge weights or per-cell parameters, 5 when one is a simplified CSR
+    network or on the voltage grid, else 2."""
     if info["step_mode"] == 3:
         return "infoli::k_persist"
     if paths and any(p == "uniform_sym" for p in paths):
@@ -373,22 +396,29 @@ def step_kernel_name(info, nets, paths=None):
     if paths and any(p == "uniform_sum" for p in paths):
         rest = step_kernel_name(info, nets, [p if p != "uniform_sum" else "uniform" for p in paths])
         return "infoli::k_vsum + " + rest
+    if paths and any(p == "uniform_grid_ahead" for p in paths):
+        rest = step_kernel_name(info, nets, [p if p != "uniform_grid_ahead" else "uniform_grid" for p in paths])
+        return "infoli::k_grid_sums + " + rest
     if paths and all(p == "csr_stream" for p in paths):
         return f"infoli::k_step<{info.get('wide_threads', 1024)}, 3>"
     if all(n.conn == "none" and n.cell_params is None for n in nets):
         var = 1
-    elif all(n.w_csr is None and n.cell_params is None for n in nets):
-        var = 2
-    else:
+    elif all(n.conn in ("dense", "none") and n.cell_params is None for n in nets):
+        var = 4
+    elif any(n.w_csr is not None or n.cell_params is not None or n.conn == "dense" for n in nets):
         var = 0
+    elif any(n.conn == "csr" and n.gap == "sgj" for n in nets) or "uniform_grid" in (paths or []):
+        var = 5
+    else:
+        var = 2
     wide, total = info["n_tiles_wide"], info["n_tiles"]
     wblock = info.get("wide_threads", 1024)
     narrow = f"infoli::k_step<256, {var}>"
     if wide == 0:
         return narrow
     if wide == total:
-        return f"infoli::k_step<{wblock}, {2 if var == 2 else 0}>"
-    return f"{narrow} + infoli::k_step<{wblock}, {2 if var == 2 else 0}> (concurrent graph branches)"
+        return f"infoli::k_step<{wblock}, {var if var in (2, 5) else 0}>"
+    return f"{narrow} + infoli::k_step<{wblock}, {var if var in (2, 5) else 0}> (concurrent graph branches)"
 
 
 def roofline(nets, launch_s, kernel="infoli::k_step<256, 2>", paths=None):
@@ -426,7 +456,7 @@ def roofline(nets, launch_s, kernel="infoli::k_step<256, 2>", paths=None):
                 "frac": achieved / peak, "traffic": None, "kernel": kernel, "slots_per_launch": slots,
                 "slots_per_unordered_pair": SYM_SLOTS_PER_PAIR, "gap_paths": ["uniform_sym"],
                 "ordered_pair_frac": ordered / (LANE_SLOTS_PER_S / UNIFORM_SLOTS_PER_PAIR)}
-    if all(n.conn == "uniform" and n.gap == "rgj" for n in nets):
+    if all(n.conn == "uniform" and n.gap == "rgj" for n in nets) and not any("grid" in (p or "") for p in paths):
         pairs = sum(n.n * n.n for n in nets)       # the kernel evaluates the diagonal too
         achieved = pairs / launch_s / 1e9
         peak = LANE_SLOTS_PER_S / UNIFORM_SLOTS_PER_PAIR / 1e9
@@ -459,7 +489,7 @@ def roofline(nets, launch_s, kernel="infoli::k_step<256, 2>", paths=None):
     out = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": achieved / HBM_PEAK_GBS, "traffic": None, "kernel": kernel,
            "algorithmic_bytes_per_launch": abytes}
-    if all(n.conn == "none" or (n.conn == "uniform" and n.gap == "sgj") for n in nets):
+    if all(n.conn in ("none", "uniform") for n in nets):
         # issue-slot use of the compartment update's own arithmetic
         cells = sum(n.n for n in nets)
         out["alu_frac"] = CELL_SLOTS * cells / launch_s / LANE_SLOTS_PER_S
@@ -754,7 +784,7 @@ def run_c4(nets, desc, steps, warmup, args, torch, infoli):
     sim = infoli.Simulator(net, init_states=[x0], stream=stream, step_mode=mode, graph_chunk=chunk,
                            csr_path=args.csr_path)
     info = sim.info()
-    paths = [sim.gap_path(0)[0]]
+    paths = gap_paths(info, sim, nets)
     log(f"c4: context ready ({info['n_tiles']} tiles, graph chunk {chunk})")
     wall, dev_ms = time_plain(sim, steps, warmup, torch)
     launch_s = dev_ms * 1e-3 / steps
@@ -1011,7 +1041,7 @@ def main():
     sim = infoli.Simulator(nets, init_states=x0s, stream=stream, step_mode=mode, graph_chunk=chunk,
                            csr_path=args.csr_path)
     info = sim.info()
-    paths = [sim.gap_path(k)[0] for k in range(len(nets))]
+    paths = gap_paths(info, sim, nets)
     wall, dev_ms = time_plain(sim, steps, warmup, torch)
     tuned = tuned_config(info, sim, nets)
     sim.close()

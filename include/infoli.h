@@ -179,9 +179,13 @@ typedef struct infoli_options {
                                     networks of >= 4,096 cells, column blocks, wide bitmap
                                     tiles): 0 => timed by the tuner (else 1024); 512 or 1024 */
     int32_t pair_path;           /* all-to-all networks with the realistic gap term:
-                                    0 => library choice (each unordered pair once for a
-                                    context's only network from 4,096 cells on, every
-                                    ordered pair below and in batches); 1 => every
+                                    0 => library choice (every ordered pair below 512
+                                    cells; from there on the sum over the cells as a
+                                    function of the voltage, taken in fp64 at whole
+                                    millivolts and interpolated at every cell: by each
+                                    tile, or for a context's only network from 4,096
+                                    cells on by a kernel ahead of the step, 2,568 bytes
+                                    for each of at most 128 shares of the cells); 1 => every
                                     ordered pair; 2 => each unordered pair once (the pair
                                     term of Section 2.3.1, Algorithm 1, is odd in dV,
                                     so the pair (j, i) gives minus the term of (i, j)).
@@ -313,8 +317,8 @@ typedef struct infoli_info {
                                    fifth or more on it)                                   */
     int32_t stream_round;       /* chunks per round of the chunk stream networks (the
                                    largest; 8,192 or 4,096 as the tuner timed), 0 none    */
-    int32_t n_sym;              /* all-to-all networks taking each unordered pair once,
-                                   or (simplified term) their voltage sum once per step  */
+    int32_t n_sym;              /* all-to-all networks whose sums a kernel ahead of the
+                                   step takes (UNIFORM_SYM and UNIFORM_SUM paths)        */
 } infoli_info;
 infoli_status infoli_get_info(const infoli_ctx *ctx, infoli_info *info);
 
@@ -333,9 +337,10 @@ infoli_status infoli_get_info(const infoli_ctx *ctx, infoli_info *info);
  *   CSR_STREAM  the CSR_CHUNKED columns of each column block (relative to
  *               the block) as one contiguous run per tile, plus one byte per
  *               chunk naming its row (Vd staged block by block).
- *   UNIFORM_SYM all-to-all, each unordered pair once: a separate kernel
- *               writes per-block partial sums, the step adds them per cell
- *               in a fixed order (option pair_path).
+ *   UNIFORM_SYM all-to-all: a separate kernel ahead of the step writes
+ *               partial sums, which the step adds in a fixed order (sums on
+ *               the voltage grid by default, per-block sums of each unordered
+ *               pair once with option pair_path 2).
  *   UNIFORM_SUM all-to-all with the simplified term: a separate kernel
  *               writes fp64 sums of the voltages of each 4,096 cells, and
  *               every tile adds those instead of all n voltages (option

@@ -210,12 +210,18 @@ void infoli_rt::launch_tiles(infoli_ctx* c, hipStream_t st, const StepArgs& a, i
 
 void infoli_rt::launch_groups(infoli_ctx* c, hipStream_t st, const StepArgs& a, int from, int64_t step_arg,
                               int32_t off, bool fork) {
-    // the unordered pairs of all-to-all networks first: their step reads the sums
+    // the sums all-to-all networks take ahead of their step
     for (int k = 0; k < c->n_inst; ++k) {
         const InstDesc& d = c->inst[k];
         if (!d.sym) continue;
         if (d.sgj) {
             hipLaunchKernelGGL(k_vsum, dim3((unsigned)vsum_groups(d.n)), dim3(256), 0, st,
+                               c->state[from] + (int64_t)SV_VD * c->stride + d.cell_off, d.n,
+                               reinterpret_cast<double*>(c->d_psym + d.psym_off));
+            continue;
+        }
+        if (d.grid) {
+            hipLaunchKernelGGL(k_grid_sums, dim3((unsigned)grid_chunks(d.n)), dim3(512), 0, st,
                                c->state[from] + (int64_t)SV_VD * c->stride + d.cell_off, d.n,
                                reinterpret_cast<double*>(c->d_psym + d.psym_off));
             continue;
@@ -267,6 +273,7 @@ void append_tiles(std::vector<std::pair<double, Tile>>& out, int k, int n, int r
 // otherwise.
 int group_for(const InstDesc& d) {
     if (d.conn == CONN_CSR && (d.blocked || d.wide)) return 1;
+    if (d.conn == CONN_UNIFORM && d.grid) return d.wide;
     if (d.conn == CONN_UNIFORM && !(d.sgj && d.sym) && (d.n >= 4096 || d.wide)) return 1;
     return 0;
 }
@@ -297,6 +304,7 @@ size_t lds_floats_for(const infoli_ctx* c, const InstDesc& d, int block) {
     if (d.conn == CONN_CSR && d.blocked)   // the column block, then the tile rows' own voltages
         return (size_t)c->blk_cols + kSelfSlots;
     if (d.conn == CONN_UNIFORM && d.sgj && d.sym) return 4;
+    if (d.conn == CONN_UNIFORM && d.grid) return 2 * (size_t)grid_lds_doubles(block / 64);
     if (d.conn == CONN_UNIFORM) return (size_t)std::min(d.n, kChunk) + 8 * (size_t)(block / 64);
     if (d.conn == CONN_CSR && d.bitmap) return bitmap_lds_floats(d.n);
     if (d.conn == CONN_CSR && d.vd_lds) return (size_t)d.n;
@@ -352,7 +360,7 @@ void finalize_tiles(infoli_ctx* c) {
             const InstDesc& d = c->inst[pt.second.inst];
             if (d.conn != CONN_NONE || d.pcell) nogap = false;
             if (d.has_w || d.pcell || d.conn == CONN_DENSE) now = false;
-            if (d.conn == CONN_CSR && d.sgj) both = true;
+            if ((d.conn == CONN_CSR && d.sgj) || d.grid) both = true;
             if ((d.conn != CONN_DENSE && d.conn != CONN_NONE) || d.pcell) dense = false;
             if (!d.stream) stream = false;
         }
@@ -424,6 +432,16 @@ bool sum_once(const infoli_ctx* c, const InstDesc& d) {
     return d.conn == CONN_UNIFORM && d.sgj && want && c->opt.step_mode != INFOLI_MODE_PERSISTENT;
 }
 
+// All-to-all networks on the voltage grid (the realistic term, tiled steps, the
+// library's choice of pair_path): 2, with k_grid_sums ahead of the step, for a
+// context's only network from kSymCells cells on; 1, each tile its own sums,
+// from kGridCells on; 0 below, where the pairs themselves are fewer.
+int grid_kind(const infoli_ctx* c, const InstDesc& d) {
+    if (d.conn != CONN_UNIFORM || d.sgj || c->opt.pair_path != 0) return 0;
+    if (d.n >= kSymCells && c->n_inst == 1 && c->opt.step_mode != INFOLI_MODE_PERSISTENT) return 2;
+    return d.n >= kGridCells ? 1 : 0;
+}
+
 // All-to-all networks whose pairs are taken once (k_pairs_sym): the
 // realistic gap term, tiled steps; by default a context's only network, from
 // kSymCells cells on. Row blocks per workgroup: the most of 16, 8, 4 that
@@ -437,10 +455,7 @@ void build_sym(infoli_ctx* c) {
         d.sym = 0;
         d.psym_off = 0;
         d.sym_ki = 0;
-        // by default only a lone network: in a batch the ordered tiles share one
-        // launch with the other networks' tiles, which measured faster than the
-        // pair kernel running ahead of that launch (Table 4's batches of 5,760
-        // and 7,680 cells: 41.6 / 61.8 us per step against 47.5 / 70.5)
+        d.grid = 0;
         if (d.sgj) {
             if (!sum_once(c, d)) continue;
             d.sym = 1;
@@ -448,8 +463,14 @@ void build_sym(infoli_ctx* c) {
             total += vsum_floats(d.n);
             continue;
         }
-        const bool want = c->opt.pair_path == 2 || (c->opt.pair_path == 0 && d.n >= kSymCells && c->n_inst == 1);
-        if (d.conn != CONN_UNIFORM || !want || c->opt.step_mode == INFOLI_MODE_PERSISTENT) continue;
+        d.grid = grid_kind(c, d);
+        if (d.grid) {
+            d.sym = d.grid == 2;
+            d.psym_off = total;
+            if (d.sym) total += grid_floats(d.n);
+            continue;
+        }
+        if (d.conn != CONN_UNIFORM || c->opt.pair_path != 2 || c->opt.step_mode == INFOLI_MODE_PERSISTENT) continue;
         d.sym = 1;
         d.psym_off = total;
         d.sym_ki = 4;
@@ -1396,8 +1417,8 @@ void build_context(infoli_ctx* c, const infoli_network_spec* specs, int32_t nins
         int rows;
         switch (d.conn) {
             case CONN_UNIFORM:   // one row per lane; a row per thread when the sum is taken once
-                rows = sum_once(c, d) ? kMaxTileRows : kUniformRows;
-                c->deg_of[k] = d.n;
+                rows = sum_once(c, d) || grid_kind(c, d) ? kMaxTileRows : kUniformRows;
+                c->deg_of[k] = grid_kind(c, d) ? d.n / 32.0 : d.n;
                 break;
             case CONN_DENSE: rows = c->opt.tile_rows ? c->opt.tile_rows : kDenseRows; c->deg_of[k] = d.n; break;
             case CONN_CSR: {

@@ -35,6 +35,7 @@
 #include <stdint.h>
 
 #include "cell_model.hpp"
+#include "gap_grid.hpp"
 
 namespace infoli {
 
@@ -88,7 +89,8 @@ struct InstDesc {
     int64_t p0_n0, p0_n1;  // the first pulse (StepArgs::pulses[pulse_off]), an empty window without
     float p0_amp;          // pulses: read with the descriptor, not by a load of its own that the
     int32_t p0_c0, p0_c1;  // cells' waves would wait for before their gap work
-    int32_t pad0;
+    int32_t grid;          // UNIFORM, realistic: sums on the voltage grid, 1 each tile its own, 2
+                           // k_grid_sums ahead of the step (partial sums at psym_off)
     CellParams p;
 };
 
@@ -330,6 +332,122 @@ __device__ __forceinline__ void gap_uniform_sum(const StepArgs& a, const InstDes
     for (int w = 0; w < W; ++w) tot += s_red[w];
     for (int k = threadIdx.x; k < t.row1 - t.row0; k += BLOCK)
         s_ig[k] = d.g * (float)((double)d.n * (double)vd[t.row0 + k] - tot);
+}
+
+// All-to-all networks with the realistic term on the voltage grid
+// (gap_grid.hpp): up to BLOCK rows, one per thread. The tile takes the grid
+// points its own rows' voltages need; it sums the cells' terms there itself,
+// or (AHEAD) adds the shares' sums k_grid_sums wrote, in a fixed order either
+// way. A tile whose rows are too far apart for its grid, or hold a voltage that
+// is not finite, takes every pair instead (a thread per row).
+template <int BLOCK>
+__device__ __forceinline__ void gap_uniform_grid(const StepArgs& a, const InstDesc& d, const Tile& t,
+                                                 const float* __restrict__ vd, float* s_ig, float* s_part,
+                                                 double* s_red, double* s_g) {
+    constexpr int W = BLOCK / 64;
+    constexpr int GP = kGridMaxGroups * kGridGroup;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = d.n;
+    const int nrows = t.row1 - t.row0;
+    const float v = vd[t.row0 + min((int)threadIdx.x, nrows - 1)];
+    float lo = v, hi = v;
+    for (int m = 32; m > 0; m >>= 1) {
+        lo = fminf(lo, __shfl_xor(lo, m, 64));
+        hi = fmaxf(hi, __shfl_xor(hi, m, 64));
+    }
+    if (lane == 0) {
+        s_part[wave] = lo;
+        s_part[W + wave] = hi;
+    }
+    const bool far = __syncthreads_or(!(fabsf(v) <= 1.0e6f));   // (a NaN too: min and max pass it by)
+    for (int w = 0; w < W; ++w) {
+        lo = fminf(lo, s_part[w]);
+        hi = fmaxf(hi, s_part[W + w]);
+    }
+    int g0 = far ? 0 : (int)floorf(lo) - kGridLeft;             // first grid point
+    const int g1 = far ? 0 : (int)floorf(hi) + kGridQ - kGridLeft;   // one past the last
+    bool ok = !far;
+    if (d.grid == 2) {
+        ok = ok && g0 >= kGridAheadLo && g1 <= kGridAheadLo + kGridAheadGroups * kGridGroup;
+        g0 -= (g0 - kGridAheadLo) & (kGridGroup - 1);           // whole groups of k_grid_sums
+    }
+    const int groups = __builtin_amdgcn_readfirstlane((g1 - g0 + kGridGroup - 1) / kGridGroup);
+    ok = ok && groups <= kGridMaxGroups;
+    double vsum = 0.0;
+    if (!ok) {
+        if ((int)threadIdx.x < nrows) {
+            const float vs = v * kPreScale;
+            float acc = 0.0f;
+            for (int j = 0; j < n; ++j) {
+                const float dv = vs - vd[j] * kPreScale;
+                acc = fmaf(dv, __builtin_amdgcn_exp2f(-(dv * dv)), acc);
+                vsum += (double)vd[j];
+            }
+            const float lin = (float)((double)n * (double)v - vsum);
+            s_ig[threadIdx.x] = d.g * (0.8f * (acc * kInvPreScale) + 0.2f * lin);
+        }
+        return;
+    }
+    if (d.grid == 2) {
+        // thread: two grid points, every (BLOCK / 8)-th share
+        const double* P = reinterpret_cast<const double*>(a.psym + d.psym_off);
+        const int C = grid_chunks(n);
+        const int np = threadIdx.x & 7, c0 = threadIdx.x >> 3;
+        const int gb = (g0 - kGridAheadLo) / kGridGroup;
+        for (int g = 0; g < groups; ++g) {
+            const double2* q = reinterpret_cast<const double2*>(P + (int64_t)(gb + g) * C * kGridGroup) + np;
+            double2 s = make_double2(0.0, 0.0);
+#pragma unroll
+            for (int u = 0; u < (kGridChunks + BLOCK / 8 - 1) / (BLOCK / 8); ++u) {
+                const int c = c0 + u * (BLOCK / 8);
+                const double2 x = q[(int64_t)min(c, C - 1) * 8];
+                s.x += c < C ? x.x : 0.0;
+                s.y += c < C ? x.y : 0.0;
+            }
+            for (int m = 8; m < 64; m <<= 1) {
+                s.x += __shfl_xor(s.x, m, 64);
+                s.y += __shfl_xor(s.y, m, 64);
+            }
+            if (lane < 8) {
+                s_g[wave * GP + g * kGridGroup + 2 * np] = s.x;
+                s_g[wave * GP + g * kGridGroup + 2 * np + 1] = s.y;
+            }
+        }
+        const double* vs = P + (int64_t)kGridAheadGroups * C * kGridGroup;
+        for (int c = threadIdx.x; c < C; c += BLOCK) vsum += vs[c];
+    } else {
+        const double ck = grid_exp((double)((lane & 15) * (lane & 15)) * -0.01);
+        for (int g = 0; g < groups; ++g) {
+            const double t0 = g0 + g * kGridGroup;
+            double acc[kGridGroup];
+#pragma unroll
+            for (int k = 0; k < kGridGroup; ++k) acc[k] = 0.0;
+            for (int j = threadIdx.x; j < n; j += BLOCK) {
+                const float vj = vd[j];
+                grid_add(acc, t0, vj);
+                if (g == 0) vsum += (double)vj;
+            }
+            const double s = grid_lane_sum(acc, lane) * ck;
+            if (lane < kGridGroup) s_g[wave * GP + g * kGridGroup + lane] = s;
+        }
+    }
+    for (int m = 32; m > 0; m >>= 1) vsum += __shfl_xor(vsum, m, 64);
+    if (lane == 0) s_red[wave] = vsum;
+    __syncthreads();
+    double* s_f = s_g + W * GP;
+    for (int k = threadIdx.x; k < groups * kGridGroup; k += BLOCK) {
+        double f = s_g[k];
+        for (int w = 1; w < W; ++w) f += s_g[w * GP + k];
+        s_f[k] = f;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < nrows) {
+        double tot = 0.0;
+        for (int w = 0; w < W; ++w) tot += s_red[w];
+        const double lin = (double)n * (double)v - tot;
+        s_ig[threadIdx.x] = (float)((double)d.g * (0.8 * grid_value(s_f, g0, v) + 0.2 * lin));
+    }
 }
 
 // ---------------------------------------------------------------- all-to-all, each unordered pair once
@@ -1313,8 +1431,9 @@ __device__ __forceinline__ float evoked_input(const StepArgs& a, const InstDesc&
 // without the paths they exclude and their registers, so that more waves per
 // SIMD keep loads in flight. kVarAll: any tile. kVarNoGap: every tile belongs
 // to a network without gap junctions (the compartment update alone). kVarNoW:
-// no per-edge weights, per-cell parameters or dense matrices, and no CSR
-// network with the simplified term. kVarBoth: the same with it. kVarStream:
+// no per-edge weights, per-cell parameters or dense matrices, no CSR network
+// with the simplified term and no voltage grid. kVarBoth: the same with those
+// two. kVarStream:
 // every tile is a chunk stream tile (column blocks, no per-edge weights, no
 // per-cell parameters), the only gap path it compiles. kVarDense: every tile
 // belongs to a network with a dense weight matrix or without gap junctions
@@ -1367,6 +1486,12 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const float* __rest
     } else {
         switch (d.conn) {
             case CONN_UNIFORM:
+                if constexpr (VAR != kVarNoW) {
+                    if (d.grid) {
+                        gap_uniform_grid<BLOCK>(a, d, t, vd, s_ig, s_part, s_red, reinterpret_cast<double*>(s_v4));
+                        break;
+                    }
+                }
                 if (d.sgj && d.sym) gap_uniform_sum<BLOCK>(a, d, t, vd, s_ig, s_red);
                 else gap_uniform<BLOCK>(a, d, t, vd, s_ig, s_v4, s_part, s_red);
                 break;
@@ -1458,7 +1583,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const float* __rest
 // voltages start at LDS address 0 (a gather's address is its column times
 // four, with no base to add) and its row sums follow the stream's region.
 template <int BLOCK, int VAR = kVarAll>
-__global__ __launch_bounds__(BLOCK) void k_step(StepArgs a, const float* __restrict__ xin,
+__global__ __launch_bounds__(BLOCK, VAR == kVarBoth ? 5 : 1) void k_step(StepArgs a, const float* __restrict__ xin,
                                                 float* __restrict__ xout, int64_t step_arg,
                                                 int32_t step_off) {
     extern __shared__ float4 s_v4[];

@@ -42,3 +42,70 @@ def test_dense_stretches(infoli, o64, n, rows, gap):
     for k, (net, x0) in enumerate(zip(nets[::-1], x0s[::-1])):
         check_gap(sim, k, net, x0[0], o64)
     sim.close()
+
+
+# name, sizes, voltages: one tile and several, the edge of a share, one and many
+# groups of grid points, voltages at whole millivolts, tiles too wide for the grid
+SPREADS = {
+    "jitter": lambda rs, n: -60.0 + rs.uniform(-1.0, 1.0, n),
+    "wide": lambda rs, n: rs.uniform(-95.0, 60.0, n),
+    "near": lambda rs, n: -60.0 + rs.uniform(-1e-4, 1e-4, n),
+    "whole": lambda rs, n: rs.integers(-70, -40, n).astype(np.float64),
+    "far": lambda rs, n: np.where(rs.random(n) < 0.02, rs.uniform(-4000.0, 4000.0, n), rs.uniform(-61.0, -59.0, n)),
+}
+
+
+@pytest.mark.parametrize("spread", sorted(SPREADS))
+@pytest.mark.parametrize("n", [512, 513, 1000, 4095, 4096, 8193, 16385])
+def test_voltage_grid(infoli, o64, n, spread):
+    """All-to-all networks on the voltage grid, alone (each tile its own sums
+    below 4,096 cells, the sums ahead of the step from there on) and in a
+    batch behind an odd number of cells."""
+    rs = I.rng(n + len(spread))
+    net = I.Network(n=n, conn="uniform", g=0.04 * 96 / n, label=spread)
+    x0 = infoli.initial_state(net)
+    x0[0] = SPREADS[spread](rs, n)
+    small = I.Network(n=33, conn="none")
+    for nets, k in (([net], 0), ([small, net], 1)):
+        sim = infoli.Simulator(nets, init_states=[infoli.initial_state(m) if m is small else x0 for m in nets],
+                               step_mode="graph", autotune=0)
+        check_gap(sim, k, net, x0[0], o64)
+        sim.close()
+
+
+def test_voltage_grid_spiking_trajectory(infoli, o32, o64):
+    """5,000 cells under a 25 ms pulse (every cell fires, dendrites up to tens
+    of millivolts apart) for 1,000 steps with the sums ahead of the step, and
+    bitwise repeatable."""
+    from test_gpu_parity import check_state_bounds, compare_spikes, gpu_trace
+    net = I.config2(seed=6, n=5000, pulse=True)
+    net.pulses = [I.Pulse(100, 600, 6.0)]
+    x0 = infoli.initial_state(net)
+    got, c, t = gpu_trace(infoli, net, 1000, 100, x0, step_mode="graph", graph_chunk=50)
+    again, _, _ = gpu_trace(infoli, net, 1000, 100, x0, step_mode="launch")
+    np.testing.assert_array_equal(got, again)
+    ref = o32.run(net, 1000, x0=x0, trace_every=100, trace_cells=net.n)
+    r64 = o64.run(net, 1000, x0=x0.astype(np.float64), trace_every=100, trace_cells=net.n)
+    check_state_bounds(got, ref["trace"], r64["trace"], "grid 5000")
+    compare_spikes(c, t, ref["counts"], ref["times"], 64)
+    assert c.min() >= 1
+
+
+@pytest.mark.parametrize("n", [600, 5000])
+def test_voltage_grid_keeps_a_bad_voltage_visible(infoli, n):
+    """A cell whose voltage has become infinite or NaN reaches every cell's
+    current, as its pair terms would."""
+    net = I.Network(n=n, conn="uniform", g=0.01)
+    x0 = infoli.initial_state(net)
+    sim = infoli.Simulator(net, init_states=[x0], step_mode="graph", check_finite=1)
+    sim.step(2)
+    assert np.all(np.isfinite(sim.read_gap_current(0)))
+    sim.close()
+    bad = I.Network(n=n, conn="uniform", g=0.01, pulses=[I.Pulse(0, 1, 3e38, 5, 6), I.Pulse(0, 1, 3e38, 5, 6)])
+    sim = infoli.Simulator(bad, init_states=[x0], step_mode="graph", check_finite=1)
+    sim.step(2)
+    with pytest.raises(infoli.InfoliError) as e:
+        sim.sync()
+    assert e.value.status == 5
+    assert not np.any(np.isfinite(sim.read_gap_current(0)))
+    sim.close()
