@@ -209,7 +209,9 @@ def gap_paths(info, sim, nets):
     grid named apart (contexts made with the default pair_path)."""
     paths = []
     for k, n in enumerate(nets):
-        p = sim.gap_path(k)[0]
+        p, blocked = sim.gap_path(k)
+        if p == "csr_chunked" and blocked:
+            p = "csr_chunked_blocked"
         if n.conn == "uniform" and n.gap == "rgj" and info["step_mode"] != 3:
             p = "uniform_grid_ahead" if p == "uniform_sym" else "uniform_grid" if n.n >= GRID_CELLS else p
         paths.append(p)
@@ -385,9 +387,10 @@ def step_kernel_name(info, nets, paths=None):
     """The kernel(s) one step launches, from the context's launch groups and
     the variant the runtime picks for them: 1 when no network has gap
     junctions, 4 when every one has a dense weight matrix or none, 3 when
-    every network runs the chunk stream (the wide group only), 0 when one has
-    per-edge weights or per-cell parameters, 5 when one is a simplified CSR
-    network or on the voltage grid, else 2."""
+    every network runs the chunk stream (the wide group only), 2 when every
+    CSR network runs flat chunked rows (7 beside all-to-all networks, 6 with
+    per-edge weights or per-cell parameters), 5 for the other CSR paths, 0 for
+    them with weights or per-cell parameters."""
     if info["step_mode"] == 3:
         return "infoli::k_persist"
     if paths and any(p == "uniform_sym" for p in paths):
@@ -401,24 +404,28 @@ def step_kernel_name(info, nets, paths=None):
         return "infoli::k_grid_sums + " + rest
     if paths and all(p == "csr_stream" for p in paths):
         return f"infoli::k_step<{info.get('wide_threads', 1024)}, 3>"
+    own = [p or "csr_chunked" for p in paths] if paths else ["csr_chunked"] * len(nets)
+    flat = all(n.conn == "none" or p == "csr_chunked" for n, p in zip(nets, own) if n.conn in ("none", "csr"))
+    plain = all(n.w_csr is None and n.cell_params is None and n.conn != "dense" for n in nets)
     if all(n.conn == "none" and n.cell_params is None for n in nets):
         var = 1
     elif all(n.conn in ("dense", "none") and n.cell_params is None for n in nets):
         var = 4
-    elif any(n.w_csr is not None or n.cell_params is not None or n.conn == "dense" for n in nets):
-        var = 0
-    elif any(n.conn == "csr" and n.gap == "sgj" for n in nets) or "uniform_grid" in (paths or []):
+    elif plain and flat:
+        var = 7 if any("uniform_grid" in p for p in own) or (paths and "uniform" in own) and \
+            not any(n.gap == "sgj" for n in nets) else 2
+    elif plain:
         var = 5
     else:
-        var = 2
+        var = 6 if paths and flat and all(n.conn in ("csr", "none") for n in nets) else 0
     wide, total = info["n_tiles_wide"], info["n_tiles"]
     wblock = info.get("wide_threads", 1024)
     narrow = f"infoli::k_step<256, {var}>"
     if wide == 0:
         return narrow
     if wide == total:
-        return f"infoli::k_step<{wblock}, {var if var in (2, 5) else 0}>"
-    return f"{narrow} + infoli::k_step<{wblock}, {var if var in (2, 5) else 0}> (concurrent graph branches)"
+        return f"infoli::k_step<{wblock}, {var if var != 1 else 0}>"
+    return f"{narrow} + infoli::k_step<{wblock}, {var if var != 1 else 0}> (concurrent graph branches)"
 
 
 def roofline(nets, launch_s, kernel="infoli::k_step<256, 2>", paths=None):

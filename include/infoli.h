@@ -314,7 +314,8 @@ typedef struct infoli_info {
                                    4 no chunked 256-thread gathers, 8 every class in its
                                    1024-thread shape, 16 wide group of 512 threads, 32
                                    every class with a bitmap shape and a density of a
-                                   fifth or more on it)                                   */
+                                   fifth or more on it, 64 every class in the highest
+                                   chunked tiles)                                         */
     int32_t stream_round;       /* chunks per round of the chunk stream networks (the
                                    largest; 8,192 or 4,096 as the tuner timed), 0 none    */
     int32_t n_sym;              /* all-to-all networks whose sums a kernel ahead of the

@@ -114,6 +114,7 @@ struct infoli_ctx {
     std::vector<int> group_of;      // launch group of each network
     std::vector<int> rows_of;       // tile rows per network
     std::vector<double> deg_of;     // mean gap-junction degree per network
+    std::vector<int32_t> h_ca;      // host copy of the chunked rows' chunk starts
     int tuned = 0;                  // networks whose tiles came from timing runs
     int tune_cached = 0;            // networks whose tiles came from the tuning cache
     int tune_mode = -1;             // whole-step launch mode the tuner chose (-1: none)

@@ -179,33 +179,36 @@ void infoli_rt::launch_tiles(infoli_ctx* c, hipStream_t st, const StepArgs& a, i
     if (ntiles == 0) return;
     const float* xin = c->state[from];
     float* xout = c->state[from ^ 1];
-    if (block == 512 && var == kVarStream)
-        hipLaunchKernelGGL((k_step<512, kVarStream>), dim3(ntiles), dim3(512), lds, st, a, xin, xout, step_arg, off);
-    else if (block == 1024 && var == kVarStream)
-        hipLaunchKernelGGL((k_step<1024, kVarStream>), dim3(ntiles), dim3(1024), lds, st, a, xin, xout, step_arg,
-                           off);
-    else if (block == 512 && var == kVarBoth)
-        hipLaunchKernelGGL((k_step<512, kVarBoth>), dim3(ntiles), dim3(512), lds, st, a, xin, xout, step_arg, off);
-    else if (block == 512 && var == kVarNoW)
-        hipLaunchKernelGGL((k_step<512, kVarNoW>), dim3(ntiles), dim3(512), lds, st, a, xin, xout, step_arg, off);
-    else if (block == 512)
-        hipLaunchKernelGGL((k_step<512, kVarAll>), dim3(ntiles), dim3(512), lds, st, a, xin, xout, step_arg, off);
-    else if (block == 1024 && var == kVarBoth)
-        hipLaunchKernelGGL((k_step<1024, kVarBoth>), dim3(ntiles), dim3(1024), lds, st, a, xin, xout, step_arg, off);
-    else if (block == 1024 && var == kVarNoW)
-        hipLaunchKernelGGL((k_step<1024, kVarNoW>), dim3(ntiles), dim3(1024), lds, st, a, xin, xout, step_arg, off);
-    else if (block == 1024)
-        hipLaunchKernelGGL((k_step<1024, kVarAll>), dim3(ntiles), dim3(1024), lds, st, a, xin, xout, step_arg, off);
-    else if (var == kVarNoGap)
-        hipLaunchKernelGGL((k_step<256, kVarNoGap>), dim3(ntiles), dim3(256), lds, st, a, xin, xout, step_arg, off);
-    else if (var == kVarDense)
-        hipLaunchKernelGGL((k_step<256, kVarDense>), dim3(ntiles), dim3(256), lds, st, a, xin, xout, step_arg, off);
-    else if (var == kVarBoth)
-        hipLaunchKernelGGL((k_step<256, kVarBoth>), dim3(ntiles), dim3(256), lds, st, a, xin, xout, step_arg, off);
-    else if (var == kVarNoW)
-        hipLaunchKernelGGL((k_step<256, kVarNoW>), dim3(ntiles), dim3(256), lds, st, a, xin, xout, step_arg, off);
-    else
-        hipLaunchKernelGGL((k_step<256, kVarAll>), dim3(ntiles), dim3(256), lds, st, a, xin, xout, step_arg, off);
+    StepArgs ag = a;
+    if (var_vd_first(var)) {
+        ag.lds_floats = (int32_t)(lds / sizeof(float));
+        lds += vd_first_bytes(block);
+    }
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(ntiles), dim3(block), lds, st, ag, xin, xout, step_arg, off);
+    };
+    const auto wide = [&](auto blk) {       // 512- or 1024-thread workgroups
+        constexpr int B = decltype(blk)::value;
+        switch (var) {
+            case kVarStream: return go(k_step<B, kVarStream>);
+            case kVarFlat: return go(k_step<B, kVarFlat>);
+            case kVarFlatW: return go(k_step<B, kVarFlatW>);
+            case kVarFlatUni: return go(k_step<B, kVarFlatUni>);
+            case kVarNoW: return go(k_step<B, kVarNoW>);
+            default: return go(k_step<B, kVarAll>);
+        }
+    };
+    if (block == 512) return wide(std::integral_constant<int, 512>{});
+    if (block == 1024) return wide(std::integral_constant<int, 1024>{});
+    switch (var) {
+        case kVarNoGap: return go(k_step<256, kVarNoGap>);
+        case kVarDense: return go(k_step<256, kVarDense>);
+        case kVarFlat: return go(k_step<256, kVarFlat>);
+        case kVarFlatW: return go(k_step<256, kVarFlatW>);
+        case kVarFlatUni: return go(k_step<256, kVarFlatUni>);
+        case kVarNoW: return go(k_step<256, kVarNoW>);
+        default: return go(k_step<256, kVarAll>);
+    }
 }
 
 void infoli_rt::launch_groups(infoli_ctx* c, hipStream_t st, const StepArgs& a, int from, int64_t step_arg,
@@ -260,11 +263,46 @@ size_t bitmap_lds_floats(int n) {
     return (size_t)std::min(groups, kBitChunkGroups) * kBitGroup;
 }
 
-void append_tiles(std::vector<std::pair<double, Tile>>& out, int k, int n, int rows, double deg) {
+Tile make_tile(const infoli_ctx* c, int k, int r0, int r1) {
+    const InstDesc& d = c->inst[k];
+    Tile t{};
+    t.inst = k;
+    t.row0 = r0;
+    t.row1 = r1;
+    t.n = d.n;
+    t.cell_off = d.cell_off;
+    if (d.conn == CONN_CSR && d.ca_off >= 0) {
+        t.row_chk = d.ca_off + r0;
+        t.chk_base = c->h_ca[(size_t)t.row_chk];
+        t.chunks = c->h_ca[(size_t)(d.ca_off + r1)] - t.chk_base;
+        t.chk0 = d.chk_off + t.chk_base;
+    }
+    return t;
+}
+
+void append_tiles(const infoli_ctx* c, std::vector<std::pair<double, Tile>>& out, int k, int rows, double deg) {
+    const int n = c->inst[k].n;
     for (int r = 0; r < n; r += rows) {
         const int r1 = std::min(n, r + rows);
-        out.push_back({(r1 - r) * (deg * 8.0 + 400.0), Tile{k, r, r1, 0}});
+        out.push_back({(r1 - r) * (deg * 8.0 + 400.0), make_tile(c, k, r, r1)});
     }
+}
+
+// LDS floats of a chunked-rows network's tiles: its voltages and the sums of
+// the chunks of its largest tile of `rows` rows.
+size_t flat_lds_floats(const infoli_ctx* c, int k, int rows) {
+    const InstDesc& d = c->inst[k];
+    int most = 0;
+    for (int r = 0; r < d.n; r += rows)
+        most = std::max(most, c->h_ca[(size_t)(d.ca_off + std::min(d.n, r + rows))] - c->h_ca[(size_t)(d.ca_off + r)]);
+    return (size_t)flat_vd_floats(d.n) + most;
+}
+
+// A network's chunked rows can run as flat tiles of `rows` rows.
+bool flat_ok(const infoli_ctx* c, int k, int rows) {
+    const InstDesc& d = c->inst[k];
+    return d.conn == CONN_CSR && d.ca_off >= 0 && d.n <= kFlatCells && c->d_rtag &&
+           flat_lds_floats(c, k, rows) * sizeof(float) + kStaticLds <= (size_t)c->lds_max;
 }
 
 // Launch group of a network: the wide group (1024- or 512-thread
@@ -278,26 +316,38 @@ int group_for(const InstDesc& d) {
     return 0;
 }
 
-// The chunk stream's gathers address LDS by column alone, which holds while
-// its kernel variants have no static LDS (their staged block starts at LDS
-// address 0); read from the compiled kernels once.
-bool stream_kernels_ok() {
-    static const bool ok = [] {
-        hipFuncAttributes a1{}, a2{};
-        if (hipFuncGetAttributes(&a1, reinterpret_cast<const void*>(&k_step<1024, kVarStream>)) != hipSuccess ||
-            hipFuncGetAttributes(&a2, reinterpret_cast<const void*>(&k_step<512, kVarStream>)) != hipSuccess) {
+// The chunk stream's and the flat tiles' gathers address LDS by column alone,
+// which holds while their kernel variants have no static LDS (their staged
+// voltages start at LDS address 0); read from the compiled kernels once.
+template <typename... K>
+bool no_static_lds(K... kernels) {
+    bool ok = true;
+    for (const void* k : {reinterpret_cast<const void*>(kernels)...}) {
+        hipFuncAttributes at{};
+        if (hipFuncGetAttributes(&at, k) != hipSuccess) {
             (void)hipGetLastError();
             return false;
         }
-        return a1.sharedSizeBytes == 0 && a2.sharedSizeBytes == 0;
-    }();
+        ok = ok && at.sharedSizeBytes == 0;
+    }
+    return ok;
+}
+bool stream_kernels_ok() {
+    static const bool ok = no_static_lds(&k_step<1024, kVarStream>, &k_step<512, kVarStream>);
+    return ok;
+}
+bool flat_kernels_ok() {
+    static const bool ok =
+        no_static_lds(&k_step<256, kVarFlat>, &k_step<512, kVarFlat>, &k_step<1024, kVarFlat>, &k_step<256, kVarFlatW>,
+                      &k_step<512, kVarFlatW>, &k_step<1024, kVarFlatW>, &k_step<256, kVarFlatUni>,
+                      &k_step<512, kVarFlatUni>, &k_step<1024, kVarFlatUni>);
     return ok;
 }
 
 // The chunk stream can run with this context's column blocks.
 bool stream_ok(const infoli_ctx* c) { return c->blk_cols == kStreamCols && stream_kernels_ok(); }
 
-size_t lds_floats_for(const infoli_ctx* c, const InstDesc& d, int block) {
+size_t lds_floats_for(const infoli_ctx* c, int k, const InstDesc& d, int block) {
     if (d.conn == CONN_CSR && d.blocked && d.stream && d.cb_off >= 0)   // block, own voltages, sums, offsets
         return (size_t)(block >= 1024 ? stream_lds_floats<1024>(c->blk_cols) : stream_lds_floats<512>(c->blk_cols)) +
                kMaxTileRows;   // the row sums (no static LDS in the stream variant)
@@ -307,6 +357,7 @@ size_t lds_floats_for(const infoli_ctx* c, const InstDesc& d, int block) {
     if (d.conn == CONN_UNIFORM && d.grid) return 2 * (size_t)grid_lds_doubles(block / 64);
     if (d.conn == CONN_UNIFORM) return (size_t)std::min(d.n, kChunk) + 8 * (size_t)(block / 64);
     if (d.conn == CONN_CSR && d.bitmap) return bitmap_lds_floats(d.n);
+    if (d.conn == CONN_CSR && d.flat) return flat_lds_floats(c, k, c->rows_of[k]);
     if (d.conn == CONN_CSR && d.vd_lds) return (size_t)d.n;
     return 4;
 }
@@ -337,16 +388,17 @@ void finalize_tiles(infoli_ctx* c) {
         }
     }
     for (int k = 0; k < c->n_inst; ++k) {
-        const InstDesc& d = c->inst[k];
+        InstDesc& d = c->inst[k];
         const int g = group_for(d);
         c->group_of[k] = g;
         int rows = c->rows_of[k];
+        d.flat = !d.blocked && !d.bitmap && d.chunked && flat_ok(c, k, rows);
         if (d.conn == CONN_CSR && d.blocked && d.stream && d.cb_off >= 0)   // one owner group per row
             rows = std::min(rows, kSelfSlots);
         else if (d.conn == CONN_CSR && d.blocked)   // rows the column-blocked passes of this workgroup size cover
             rows = std::min(rows, kBlkPasses * std::max(1, c->grp[g].block / std::max(1, d.lanes_per_row)));
-        append_tiles(planned[g], k, d.n, rows, c->deg_of[k]);
-        floats[g] = std::max(floats[g], lds_floats_for(c, d, c->grp[g].block));
+        append_tiles(c, planned[g], k, rows, c->deg_of[k]);
+        floats[g] = std::max(floats[g], lds_floats_for(c, k, d, c->grp[g].block));
     }
     for (int g = 0; g < 2; ++g) {
         TileGroup& tg = c->grp[g];
@@ -354,20 +406,24 @@ void finalize_tiles(infoli_ctx* c) {
         std::stable_sort(planned[g].begin(), planned[g].end(),
                          [](const auto& x, const auto& y) { return x.first > y.first; });
         tg.tiles.clear();
-        bool nogap = true, now = true, both = false, dense = tg.block == 256, stream = !planned[g].empty();
+        bool nogap = true, now = true, flat = true, uni = false, dense = true, stream = !planned[g].empty();
         for (const auto& pt : planned[g]) {
             tg.tiles.push_back(pt.second);
             const InstDesc& d = c->inst[pt.second.inst];
-            if (d.conn != CONN_NONE || d.pcell) nogap = false;
+            const bool none = d.conn == CONN_NONE;
+            if (!none || d.pcell) nogap = false;
             if (d.has_w || d.pcell || d.conn == CONN_DENSE) now = false;
-            if ((d.conn == CONN_CSR && d.sgj) || d.grid) both = true;
-            if ((d.conn != CONN_DENSE && d.conn != CONN_NONE) || d.pcell) dense = false;
+            if (d.conn == CONN_UNIFORM && !(d.sgj && d.sym)) uni = true;
+            if (d.conn == CONN_DENSE || (d.conn == CONN_CSR && !d.flat)) flat = false;
+            if ((!none && d.conn != CONN_DENSE) || d.pcell) dense = false;
             if (!d.stream) stream = false;
         }
-        tg.var = nogap                       ? kVarNoGap
-                 : dense                     ? kVarDense
+        tg.var = nogap && tg.block == 256    ? kVarNoGap
+                 : dense && tg.block == 256  ? kVarDense
                  : stream && tg.block >= 512 ? kVarStream
-                 : now && both               ? kVarBoth
+                 : !flat_kernels_ok()        ? (now ? kVarNoW : kVarAll)
+                 : flat && now               ? (uni ? kVarFlatUni : kVarFlat)
+                 : flat && !uni              ? kVarFlatW
                  : now                       ? kVarNoW
                                              : kVarAll;
         if (tg.tiles.size() > (size_t)INT32_MAX / 2) fail(INFOLI_E_INVALID_ARG, "too many tiles");
@@ -625,10 +681,14 @@ void build_chunks(infoli_ctx* c, const infoli_network_spec* specs) {
             }
         }
     }
-    // per chunk of the blocks layout, its row mod 256 (the chunk stream's row tag)
+    // per chunk its row mod 256 (the row tag)
     std::vector<uint8_t> ht((size_t)nchunks, 0);
     for (int k = 0; k < c->n_inst; ++k) {
         const InstDesc& d = c->inst[k];
+        if (d.ca_off >= 0)
+            for (int i = 0; i < d.n; ++i)
+                for (int32_t x = ha[(size_t)(d.ca_off + i)]; x < ha[(size_t)(d.ca_off + i + 1)]; ++x)
+                    ht[(size_t)(d.chk_off + x)] = (uint8_t)(i & (kSelfSlots - 1));
         if (d.cb_off < 0) continue;
         for (int b = 0; b < d.nblk; ++b)
             for (int i = 0; i < d.n; ++i)
@@ -649,6 +709,7 @@ void build_chunks(infoli_ctx* c, const infoli_network_spec* specs) {
     HIPX(hipMemcpy(c->d_chkw, hw.data(), sizeof(float) * hw.size(), hipMemcpyHostToDevice));
     c->d_ca = c->alloc<int32_t>(ha.size());
     HIPX(hipMemcpy(c->d_ca, ha.data(), sizeof(int32_t) * ha.size(), hipMemcpyHostToDevice));
+    c->h_ca = std::move(ha);
     c->d_cb = c->alloc<int32_t>(hb.size());
     HIPX(hipMemcpy(c->d_cb, hb.data(), sizeof(int32_t) * hb.size(), hipMemcpyHostToDevice));
 }
@@ -685,8 +746,8 @@ std::string tune_key(const infoli_ctx* c, const InstDesc& d, double deg) {
     return buf;
 }
 
-// Whole-step launch modes: six bits (see the tuner below), so 0..63.
-constexpr int kStepModes = 64;
+// Whole-step launch modes: seven bits (see the tuner below), so 0..127.
+constexpr int kStepModes = 128;
 
 // Lines "<class key>|L R lds bm block" (the class's best shape),
 // "<class key>#256|..." (its best shape in 256-thread workgroups) and
@@ -801,11 +862,10 @@ float time_replayed(infoli_ctx* c, F&& launch, int reps, int trials) {
 float time_shape(infoli_ctx* c, const std::vector<int>& ks, const TuneChoice& t, Tile* d_tmp) {
     std::vector<std::pair<double, Tile>> planned;
     size_t lds = 16;
-    int var = t.bm == 4 ? kVarStream : kVarNoW;   // the variant the step will launch these tiles with
+    bool weights = false, flat = t.bm == 3;
     for (int k : ks) {
         InstDesc d = c->inst[k];
-        if (d.has_w || d.pcell) var = kVarAll;
-        else if (d.sgj && var == kVarNoW) var = kVarBoth;
+        weights = weights || d.has_w || d.pcell;
         d.lanes_per_row = t.L;
         d.vd_lds = t.lds;
         d.bitmap = t.bm == 1;
@@ -813,13 +873,16 @@ float time_shape(infoli_ctx* c, const std::vector<int>& ks, const TuneChoice& t,
         d.stream = t.bm == 4;
         d.stream_round = t.bm == 4 ? t.rnd : kStreamRound;
         d.chunked = t.bm == 3;
+        d.flat = t.bm == 3 && flat_ok(c, k, t.R);
+        flat = flat && d.flat;
         HIPX(hipMemcpy(c->d_inst + k, &d, sizeof(d), hipMemcpyHostToDevice));
-        append_tiles(planned, k, d.n, t.R, 0.0);
+        append_tiles(c, planned, k, t.R, 0.0);
         if (t.bm == 1) lds = std::max(lds, ((bitmap_lds_floats(d.n) + 3) / 4) * sizeof(float4));
         else if (t.bm == 2)
             lds = std::max(lds, ((size_t)(c->blk_cols + kSelfSlots + 3) / 4) * sizeof(float4));
         else if (t.bm == 4)
-            lds = std::max(lds, ((lds_floats_for(c, d, t.block) + 3) / 4) * sizeof(float4));
+            lds = std::max(lds, ((lds_floats_for(c, k, d, t.block) + 3) / 4) * sizeof(float4));
+        else if (d.flat) lds = std::max(lds, ((flat_lds_floats(c, k, t.R) + 3) / 4) * sizeof(float4));
         else if (t.lds) lds = std::max(lds, ((size_t)(d.n + 3) / 4) * sizeof(float4));
     }
     std::vector<Tile> tl;
@@ -829,6 +892,11 @@ float time_shape(infoli_ctx* c, const std::vector<int>& ks, const TuneChoice& t,
     a.tiles = d_tmp;
     a.dry = 1;
     const int block = t.block;
+    // the variant a step of these tiles alone launches
+    const int var = t.bm == 4                   ? kVarStream
+                    : flat && flat_kernels_ok() ? (weights ? kVarFlatW : kVarFlat)
+                    : weights                   ? kVarAll
+                                                : kVarNoW;
     const unsigned ntiles = (unsigned)tl.size();
     return time_replayed(
         c, [&](hipStream_t st, int from) { launch_tiles(c, st, a, block, ntiles, lds, from, c->step, 0, var); }, 10,
@@ -925,6 +993,7 @@ void autotune_shapes(infoli_ctx* c) {
         TuneChoice best, best256, best256nc;   // overall; in 256 threads; in 256 threads, not chunked
         TuneChoice best1024;                   // in 1024 threads (block 0: none timed)
         TuneChoice bm256, bm1024;              // the bitmap path in 256 / 1024 threads (block 0: none)
+        TuneChoice tall{0, 0, 0, 0, 0};        // flat tiles of up to eight chunks per thread (block 0: none)
         bool bits = false;                     // a bitmap shape that the whole step may force (bit 5)
         TuneChoice alt[kAlts];                 // the fastest distinct 256-thread shapes, fastest first
         int nalt = 0;
@@ -972,6 +1041,11 @@ void autotune_shapes(infoli_ctx* c) {
             std::vector<std::pair<float, TuneChoice>> timed, all, all256, all256nc, all1024;
             bool all_rows = c->d_ca != nullptr;    // every network of the class has the chunked rows layout
             for (int k : ks) all_rows = all_rows && c->inst[k].ca_off >= 0;
+            auto all_flat = [&](int R) {
+                bool ok = all_rows;
+                for (int k : ks) ok = ok && flat_ok(c, k, R);
+                return ok;
+            };
             // every shape timed; the class's choices picked at the end (ties
             // by the fixed preference), best256 also as the search goes on
             auto consider = [&](const TuneChoice& t) {
@@ -996,7 +1070,7 @@ void autotune_shapes(infoli_ctx* c) {
                     if (R > kMaxTileRows) continue;
                     for (int lds = 0; lds <= (n <= kChunk ? 1 : 0); ++lds) {
                         consider(TuneChoice{L, R, lds, 0, 256});
-                        if (all_rows) consider(TuneChoice{L, R, lds, 3, 256});
+                        if (all_rows && !all_flat(R)) consider(TuneChoice{L, R, lds, 3, 256});
                     }
                 }
             }
@@ -1009,9 +1083,17 @@ void autotune_shapes(infoli_ctx* c) {
                     const int R = std::max(1, 1024 / L) * m;
                     if (R > kMaxTileRows) continue;
                     consider(TuneChoice{L, R, best256.lds, 0, 1024});
-                    if (all_rows) consider(TuneChoice{L, R, best256.lds, 3, 1024});
+                    if (all_rows && !all_flat(R)) consider(TuneChoice{L, R, best256.lds, 3, 1024});
                 }
             }
+            // the chunked rows as flat runs: a quarter to sixteen chunks per thread
+            if (all_rows)
+                for (int blk : {256, 1024})
+                    for (int R = 8; R <= kMaxTileRows; R *= 2) {
+                        const double chunks = R * (deg / kChunkCols + 0.5);
+                        if ((chunks > 16.0 * blk && R > 8) || (chunks < 0.25 * blk && R < kMaxTileRows)) continue;
+                        if (all_flat(R)) consider(TuneChoice{64, R, 1, 3, blk});
+                    }
             // the bitmap path, when every network of the class has one
             bool all_bits = c->d_bits != nullptr;
             for (int k : ks) all_bits = all_bits && c->inst[k].bits_off >= 0;
@@ -1027,7 +1109,7 @@ void autotune_shapes(infoli_ctx* c) {
                 for (int blk : {1024, 512}) {
                     InstDesc d = c->inst[ks[0]];
                     d.blocked = d.stream = 1;
-                    if (lds_floats_for(c, d, blk) * sizeof(float) + kStaticLds <= (size_t)c->lds_max)
+                    if (lds_floats_for(c, ks[0], d, blk) * sizeof(float) + kStaticLds <= (size_t)c->lds_max)
                         for (int rnd : {kStreamRound, kStreamRound / 2})
                             consider(TuneChoice{64, kSelfSlots, 0, 4, blk, rnd});
                 }
@@ -1073,6 +1155,14 @@ void autotune_shapes(infoli_ctx* c) {
         // least four times the work, so the whole step does not force it
         cc.bits = bm256.block || bm1024.block;
         for (int k : ks) cc.bits = cc.bits && c->deg_of[k] >= 0.2 * c->inst[k].n;
+        // a step of many networks fills the chip however high its tiles are:
+        // there the highest tiles of at most eight chunks per thread spend the
+        // least on staging voltages and on half-empty compartment waves
+        int tall = kMaxTileRows;
+        while (tall > 8 && tall * (c->deg_of[ks[0]] / kChunkCols + 0.5) > 8.0 * 256) tall /= 2;
+        bool tall_ok = true;
+        for (int k : ks) tall_ok = tall_ok && flat_ok(c, k, tall);
+        if (tall_ok) cc.tall = TuneChoice{64, tall, 1, 3, 256};
         chosen[key] = cc;
     }
 
@@ -1095,10 +1185,12 @@ void autotune_shapes(infoli_ctx* c) {
     // non-chunked 256-thread shape; bit 5, every class with a bitmap shape
     // and a density of a fifth or more takes it (in 1024 threads under bit 3
     // when timed, else in 256): timed alone a class can rank the bitmap and its
-    // gathers differently from the whole step
+    // gathers differently from the whole step; bit 6 (alone or with bit 1),
+    // every class in its highest flat tiles
     auto pick = [&](const ClassChoice& ch, int m) {
         if ((m & 32) && ch.bits)
             return ((m & 8) && ch.bm1024.block) || !ch.bm256.block ? ch.bm1024 : ch.bm256;
+        if ((m & 64) && ch.tall.block) return ch.tall;
         TuneChoice t = (m & 8) && ch.best1024.block == 1024 ? ch.best1024 : (m & 1) ? ch.best256 : ch.best;
         if ((m & 4) && t.bm == 3 && t.block == 256) t = ch.best256nc;
         return t;
@@ -1122,9 +1214,10 @@ void autotune_shapes(infoli_ctx* c) {
         mode = mh->second[0];
         for (int i = 0; i < ncls; ++i) refine[i] = mh->second[1 + i];
     } else {
-        bool wide = false, chunk = false, narrow = false, bits = false;   // variants that change something
+        bool wide = false, chunk = false, narrow = false, bits = false, tall = false;   // variants that change something
         for (const auto& kv : chosen) {
             bits = bits || kv.second.bits;
+            tall = tall || kv.second.tall.block;
             wide = wide || kv.second.best.block != 256;
             narrow = narrow || (kv.second.best.block == 256 && kv.second.best1024.block == 1024);
             chunk = chunk || kv.second.best.bm == 3 || kv.second.best256.bm == 3;
@@ -1136,6 +1229,7 @@ void autotune_shapes(infoli_ctx* c) {
             for (int m = 0; m < kStepModes; ++m) {
                 if (((m & 1) && !wide) || ((m & 4) && !chunk) || ((m & 8) && (!narrow || (m & 1)))) continue;
                 if ((m & 32) && !bits) continue;
+                if ((m & 64) && (!tall || (m & ~66))) continue;
                 if ((m & 16) && c->opt.wide_threads) continue;
                 apply_all(m);
                 c->grp[1].block = wide_block(m);
@@ -1585,9 +1679,9 @@ void build_context(infoli_ctx* c, const infoli_network_spec* specs, int32_t nins
                 InstDesc d = c->inst[k];
                 d.blocked = d.stream = 1;
                 const int blk = c->opt.wide_threads ? c->opt.wide_threads : 1024;
-                if (lds_floats_for(c, d, blk) * sizeof(float) + kStaticLds > (size_t)c->lds_max)
+                if (lds_floats_for(c, k, d, blk) * sizeof(float) + kStaticLds > (size_t)c->lds_max)
                     fail(INFOLI_E_UNSUPPORTED, "the chunk stream needs %zu bytes of LDS per workgroup, the device "
-                         "gives %d", lds_floats_for(c, d, blk) * sizeof(float) + kStaticLds, c->lds_max);
+                         "gives %d", lds_floats_for(c, k, d, blk) * sizeof(float) + kStaticLds, c->lds_max);
                 c->inst[k].blocked = c->inst[k].stream = 1;
                 c->rows_of[k] = kSelfSlots;
             }

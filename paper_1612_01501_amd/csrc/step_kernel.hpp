@@ -22,6 +22,8 @@
 //                LDS one column block at a time; each row's edges of that
 //                block (16-byte chunks of columns relative to the block)
 //                gather from LDS; partial sums stay in registers across blocks.
+//   CHUNKED CSR  Vd of the network in LDS; a tile's column chunks as one flat
+//                run, a chunk per thread, the rows' sums from LDS slots.
 //   CSR          groups of L lanes per row stride over the row's edges and
 //                gather Vd of the neighbours, from a copy of the network's
 //                Vd staged in LDS when the tile's edges outnumber the cells,
@@ -45,6 +47,7 @@ constexpr int kMaxTileRows = 256;   // rows (cells) per tile, any layout (<= BLO
 constexpr int kUniformRows = 64;    // rows per UNIFORM_ALL tile (one per lane)
 constexpr int kChunk = 8192;        // Vd values staged in LDS per pass
 constexpr int kBatch = 16;          // CSR edges per lane per batch of loads
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // 16 bytes at any 4-byte boundary
 
 // log2(e)/100: exp(-dV^2/100) = 2^(-(dV*a)^2) with a = sqrt(log2(e)/100).
 constexpr float kL2eOver100 = 0.014426950408889634f;
@@ -71,7 +74,8 @@ struct InstDesc {
     int32_t blocked;       // CSR: Vd staged in LDS one column block at a time
     int32_t nblk;          // blocked: number of column blocks
     int32_t wide;          // bitmap: run in the 1024-thread launch group
-    int32_t chunked;       // CSR gathers from the chunked rows layout
+    int32_t chunked;       // CSR from the chunked rows layout
+    int32_t flat;          //   as one flat run of chunks per tile, Vd in LDS
     int32_t sgj;           // simplified (linear) gap junctions: term w * dV
     int32_t pcell;         // per-cell parameters in StepArgs::cparams
     int32_t stream;        // blocked: the flat chunk stream (row tags) instead of row groups
@@ -94,11 +98,18 @@ struct InstDesc {
     CellParams p;
 };
 
+// Rows [row0, row1) of a network, and what its first loads need, so that they
+// wait for this record only and not for the descriptor behind it.
 struct Tile {
     int32_t inst;
     int32_t row0;
     int32_t row1;
-    int32_t pad0;
+    int32_t n;             // the network's cells
+    int64_t cell_off;      // its cell 0
+    int64_t chk0;          // chunked CSR in LDS: the tile's first chunk
+    int64_t row_chk;       //   where the chunk starts of its rows are in StepArgs::ca
+    int32_t chunks;        //   and its chunks
+    int32_t chk_base;      //   the first one's index in the network
 };
 
 struct DevPulse {
@@ -140,7 +151,38 @@ struct StepArgs {
     float* out_ring;           // [out_slots][stride]: Va after step s in slot s mod out_slots
     const float* cparams;      // [20][stride]: per-cell parameters (networks with pcell)
     const float* psym;         // partial row sums of the sym networks (k_pairs_sym)
+    int32_t lds_floats;        // LDS floats of the launch's staged region (var_vd_first variants)
 };
+
+// Kernel variants by the tiles a launch holds; the narrow ones are compiled
+// without the paths they exclude and their registers, so that more waves per
+// SIMD keep loads in flight.
+//   kVarAll      any tile
+//   kVarNoGap    networks without gap junctions (the compartment update alone)
+//   kVarFlat     those, flat chunked rows without per-edge weights, and the
+//                simplified all-to-all form with the sum taken once
+//   kVarStream   chunk stream tiles (column blocks) only
+//   kVarDense    dense weight matrices or no gap junctions (256 threads)
+//   kVarNoW      no per-edge weights, per-cell parameters or dense matrices
+//   kVarFlatW    flat chunked rows or no gap junctions, with per-edge weights or
+//                per-cell parameters
+//   kVarFlatUni  kVarFlat's tiles and all-to-all networks
+enum : int {
+    kVarAll = 0, kVarNoGap = 1, kVarFlat = 2, kVarStream = 3, kVarDense = 4, kVarNoW = 5, kVarFlatW = 6, kVarFlatUni = 7
+};
+constexpr bool var_weights(int v) { return v == kVarAll || v == kVarFlatW; }      // per-edge weights
+constexpr bool var_cells(int v) { return v == kVarAll || v == kVarFlatW; }        // per-cell parameters
+constexpr bool var_uniform(int v) { return v == kVarAll || v == kVarNoW || v == kVarFlatUni; }
+constexpr bool var_gathers(int v) { return v == kVarAll || v == kVarNoW; }        // CSR forms beside the flat one
+// the staged voltages first in LDS (no static LDS; the sums' arrays follow the
+// launch's region, lds_floats from its start): a gather's LDS address is then its
+// column times four, with no base to add
+constexpr bool var_vd_first(int v) { return v == kVarFlat || v == kVarFlatW || v == kVarFlatUni; }
+constexpr size_t vd_first_bytes(int block) {       // the arrays behind the region
+    return block / 64 * sizeof(double) + (block + kMaxTileRows) * sizeof(float);
+}
+// waves per SIMD the register allocator aims at (1: its own choice)
+constexpr int var_waves(int v) { return v == kVarNoW ? 5 : v == kVarFlatUni ? 6 : 1; }
 
 // The parameters of one cell: the network's, or the cell's own (SoA rows).
 __device__ __forceinline__ CellParams cell_params_of(const StepArgs& a, const InstDesc& d, int64_t cell) {
@@ -356,14 +398,18 @@ __device__ __forceinline__ void gap_uniform_grid(const StepArgs& a, const InstDe
         lo = fminf(lo, __shfl_xor(lo, m, 64));
         hi = fmaxf(hi, __shfl_xor(hi, m, 64));
     }
+    const bool bad = __any(!(fabsf(v) <= 1.0e6f));      // (a NaN too: min and max pass it by)
     if (lane == 0) {
         s_part[wave] = lo;
         s_part[W + wave] = hi;
+        s_part[2 * W + wave] = bad ? 1.0f : 0.0f;
     }
-    const bool far = __syncthreads_or(!(fabsf(v) <= 1.0e6f));   // (a NaN too: min and max pass it by)
+    __syncthreads();
+    bool far = false;
     for (int w = 0; w < W; ++w) {
         lo = fminf(lo, s_part[w]);
         hi = fmaxf(hi, s_part[W + w]);
+        far = far || s_part[2 * W + w] != 0.0f;
     }
     int g0 = far ? 0 : (int)floorf(lo) - kGridLeft;             // first grid point
     const int g1 = far ? 0 : (int)floorf(hi) + kGridQ - kGridLeft;   // one past the last
@@ -615,7 +661,6 @@ static __global__ __launch_bounds__(256) void k_vsum(const float* __restrict__ v
 constexpr int kDenseRows = 4;
 constexpr int kDenseSteps = 2;
 constexpr int kDenseSlack = 4;
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int BLOCK, bool SGJ>
 __device__ __forceinline__ void gap_dense(const StepArgs& a, const InstDesc& d, const Tile& t,
@@ -814,11 +859,123 @@ __device__ __forceinline__ void chunk_pair_terms(const uint4 q0, const uint4 q1,
     }
 }
 
-// Gathers over whole rows (networks of at most 65,536 cells): row r's chunks
+// Byte offset 4*j of the 16-bit column j in the low or high half of w: one
+// instruction (a shift reading one half-word of its operand), where the
+// plain form takes an extract and a shift.
+__device__ __forceinline__ uint32_t col_lo_bytes(uint32_t w) {
+    uint32_t r;
+    asm("v_lshlrev_b32_sdwa %0, 2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
+        : "=v"(r) : "v"(w));
+    return r;
+}
+__device__ __forceinline__ uint32_t col_hi_bytes(uint32_t w) {
+    uint32_t r;
+    asm("v_lshlrev_b32_sdwa %0, 2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+        : "=v"(r) : "v"(w));
+    return r;
+}
+
+typedef const __attribute__((address_space(3))) float lds_float;
+
+// ---------------------------------------------------------------- chunked rows
+// A tile's rows are one contiguous run of chunks (rows layout, padded with the
+// row itself). Every thread takes chunks of the run, whatever row they belong
+// to: no lane is idle on short rows, and the loads need no row pointers. A
+// one-byte tag (row mod 256) names a chunk's row; its eight terms' sum goes to
+// an LDS slot of its own, and the rows' owners (consecutive threads, as many
+// as the tile's rows leave) add their row's slots in a fixed order. Vd of the
+// whole network is staged in LDS (prescaled). kFlatChunks chunks per thread
+// are in flight, the first ones while Vd is staged.
+constexpr int kFlatChunks = 4;
+constexpr int kFlatCells = 32768;       // networks up to this size (128 KB of Vd)
+
+__host__ __device__ constexpr int flat_vd_floats(int n) { return (n + 3) & ~3; }
+
+template <int BLOCK, bool HASW, bool SGJ, bool VD0>
+__device__ __forceinline__ void gap_flat(const StepArgs& a, const InstDesc& d, const Tile& t,
+                                         const float* __restrict__ vd, float* s_vd, float* s_ig) {
+    constexpr int K = HASW ? kFlatChunks / 2 : kFlatChunks;
+    const int m = t.chunks;
+    const int nrows = t.row1 - t.row0;
+    const uint4* ch = a.chk + t.chk0;
+    const uint8_t* tag = a.rtag + t.chk0;
+    const float4* cw = reinterpret_cast<const float4*>(a.chkw) + 2 * t.chk0;
+    float* s_sums = s_vd + flat_vd_floats(t.n);
+    const uint32_t vd_lds = VD0 ? 0u : (uint32_t)(size_t)(lds_float*)s_vd;   // VD0: Vd is first in LDS
+    uint4 q[K];
+    uint32_t tg[K];
+    float4 w4[K][2];
+    auto load = [&](int base) {
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            const int i = max(0, min(base + u * BLOCK + (int)threadIdx.x, m - 1));
+            q[u] = ch[i];
+            tg[u] = tag[i];
+            if (HASW) {
+                w4[u][0] = cw[2 * (int64_t)i];
+                w4[u][1] = cw[2 * (int64_t)i + 1];
+            }
+        }
+    };
+    load(0);
+    // the owners of a row: OWN consecutive threads (a power of two, at most a wave)
+    const int own = max(1, min(64, BLOCK >> (nrows <= 1 ? 0 : 32 - __builtin_clz(nrows - 1))));
+    const int orow = threadIdx.x / own, oq = threadIdx.x & (own - 1);
+    int lo = 0, hi = 0;
+    if (orow < nrows) {
+        lo = a.ca[t.row_chk + orow] - t.chk_base;
+        hi = a.ca[t.row_chk + orow + 1] - t.chk_base;
+    }
+    // (up to three values past the last cell: the next state rows follow Vd)
+    for (int k = 4 * threadIdx.x; k < t.n; k += 4 * BLOCK) {
+        const f32x4u v = *reinterpret_cast<const f32x4u*>(vd + k);
+        *reinterpret_cast<float4*>(s_vd + k) =
+            make_float4(v[0] * kPreScale, v[1] * kPreScale, v[2] * kPreScale, v[3] * kPreScale);
+    }
+    __syncthreads();
+    for (int base = 0; base < m; base += K * BLOCK) {
+        if (base) load(base);
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            const int i = base + u * BLOCK + threadIdx.x;
+            if (i < m) {
+                const float vi = s_vd[t.row0 + (int)((tg[u] - (uint32_t)t.row0) & 255u)];
+                const uint32_t wd[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
+                float v[kChunkCols];
+#pragma unroll
+                for (int e = 0; e < kChunkCols; ++e)
+                    v[e] = *(lds_float*)(size_t)(vd_lds + ((e & 1) ? col_hi_bytes(wd[e >> 1]) : col_lo_bytes(wd[e >> 1])));
+                float a0 = 0.0f, a1 = 0.0f;
+#pragma unroll
+                for (int e = 0; e < kChunkCols; e += 2) {
+                    const float d0 = vi - v[e], d1 = vi - v[e + 1];
+                    const float f0 = pair_factor<SGJ, true>(d0), f1 = pair_factor<SGJ, true>(d1);
+                    if (HASW) {
+                        const float4 wa = w4[u][e >> 2];
+                        a0 = fmaf((e & 2) ? wa.z : wa.x, d0 * f0, a0);
+                        a1 = fmaf((e & 2) ? wa.w : wa.y, d1 * f1, a1);
+                    } else {
+                        a0 = fmaf(d0, f0, a0);
+                        a1 = fmaf(d1, f1, a1);
+                    }
+                }
+                s_sums[i] = a0 + a1;
+            }
+        }
+    }
+    __syncthreads();
+    float part = 0.0f;
+    for (int c = lo + oq; c < hi; c += own) part += s_sums[c];
+    for (int h = own >> 1; h > 0; h >>= 1) part += __shfl_xor(part, h, 64);
+    if (orow < nrows && oq == 0) s_ig[orow] = (HASW ? 1.0f : d.g) * part * kInvPreScale;
+}
+
+// Chunked rows of networks beyond kFlatCells (at most 65,536 cells): L lanes
+// per row, the neighbours' voltages gathered from global memory. Row r's chunks
 // [ca[r], ca[r + 1]), padded with r itself.
-template <int BLOCK, bool LDS, bool HASW, bool SGJ>
+template <int BLOCK, bool HASW, bool SGJ>
 __device__ __forceinline__ void gap_chunks(const StepArgs& a, const InstDesc& d, const Tile& t,
-                                           const float* __restrict__ vd, const float* s_vd, float* s_part,
+                                           const float* __restrict__ vd, float* s_part,
                                            float* s_ig) {
     const int L = d.lanes_per_row;
     const int groups = BLOCK / L;
@@ -827,13 +984,11 @@ __device__ __forceinline__ void gap_chunks(const StepArgs& a, const InstDesc& d,
     const int32_t* ca = a.ca + d.ca_off;
     const uint4* ch = a.chk + d.chk_off;
     const float4* cw = reinterpret_cast<const float4*>(a.chkw) + 2 * d.chk_off;
-    const float* src = LDS ? s_vd : vd;
-    const float back = LDS ? kInvPreScale : 1.0f;
     for (int r0 = t.row0; r0 < t.row1; r0 += groups) {
         const int r = r0 + grp;
         float acc0 = 0.0f, acc1 = 0.0f;
         if (r < t.row1) {
-            const float vi = src[r];
+            const float vi = vd[r];
             const uint4 padc = pad_chunk((uint32_t)r);
             const int ce = ca[r + 1];
             for (int c = ca[r] + lig; c < ce; c += 2 * L) {
@@ -847,12 +1002,12 @@ __device__ __forceinline__ void gap_chunks(const StepArgs& a, const InstDesc& d,
                     w4[2] = ok1 ? cw[2 * (int64_t)(c + L)] : make_float4(0.f, 0.f, 0.f, 0.f);
                     w4[3] = ok1 ? cw[2 * (int64_t)(c + L) + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
                 }
-                chunk_pair_terms<LDS, HASW, SGJ>(q0, q1, w4, src, vi, acc0, acc1);
+                chunk_pair_terms<false, HASW, SGJ>(q0, q1, w4, vd, vi, acc0, acc1);
             }
         }
         float acc = acc0 + acc1;
         if (L <= 64) {
-            acc = wave_sum_xor(acc, L) * back;
+            acc = wave_sum_xor(acc, L);
             if (r < t.row1 && lig == 0) s_ig[r - t.row0] = HASW ? acc : d.g * acc;
         } else {
             acc = wave_sum_xor(acc, 64);
@@ -862,7 +1017,6 @@ __device__ __forceinline__ void gap_chunks(const StepArgs& a, const InstDesc& d,
             if (lig == 0 && r < t.row1) {
                 float tot = 0.0f;
                 for (int w = 0; w < L / 64; ++w) tot += s_part[wave + w];
-                tot *= back;
                 s_ig[r - t.row0] = HASW ? tot : d.g * tot;
             }
             __syncthreads();
@@ -982,27 +1136,10 @@ __host__ __device__ constexpr int stream_lds_floats(int C) {
 // zeroed ones): a wave's share is rounded up to whole pieces
 constexpr int kStreamSlack = (1024 / 64 + kStreamSweeps) * 64;
 
-// Byte offset 4*j of the 16-bit column j in the low or high half of w: one
-// instruction (a shift reading one half-word of its operand), where the
-// plain form takes an extract and a shift.
-__device__ __forceinline__ uint32_t col_lo_bytes(uint32_t w) {
-    uint32_t r;
-    asm("v_lshlrev_b32_sdwa %0, 2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
-        : "=v"(r) : "v"(w));
-    return r;
-}
-__device__ __forceinline__ uint32_t col_hi_bytes(uint32_t w) {
-    uint32_t r;
-    asm("v_lshlrev_b32_sdwa %0, 2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
-        : "=v"(r) : "v"(w));
-    return r;
-}
-
 // One chunk's eight terms (voltages prescaled, staged in LDS). The staged
 // block is the first thing in LDS (the stream variant of k_step has no
 // static LDS; the runtime checks it before it offers the stream), so a
 // column's LDS address is the column times four, with no base to add.
-typedef const __attribute__((address_space(3))) float lds_float;
 template <bool SGJ>
 __device__ __forceinline__ float chunk_terms(const uint4 q, float vi) {
     const uint32_t wd[4] = {q.x, q.y, q.z, q.w};
@@ -1256,54 +1393,54 @@ __device__ __forceinline__ void by_weights(const InstDesc& d, F&& f) {
 }
 
 // CSR paths of one gap form (SGJ: simplified).
-template <int BLOCK, bool SGJ, bool W>
+template <int BLOCK, bool SGJ, int VAR>
 __device__ __forceinline__ void gap_csr_form(const StepArgs& a, const InstDesc& d, const Tile& t,
                                              const float* __restrict__ vd, float* s_vd, float* s_part,
                                              float* s_ig) {
-    // column-blocked tiles run in the wide launch group only (512- or
-    // 1024-thread workgroups; the runtime places them there); elsewhere the
-    // same rows take the gathers below
-    if constexpr (BLOCK >= 512) {
-        if (d.blocked && d.cb_off >= 0) {
-            by_weights<W>(d, [&](auto hw) {
-                gap_chunks_blocked<BLOCK, decltype(hw)::value, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
-            });
+    constexpr bool W = var_weights(VAR);
+    if constexpr (!var_gathers(VAR)) {
+        by_weights<W>(d, [&](auto hw) { gap_flat<BLOCK, decltype(hw)::value, SGJ, var_vd_first(VAR)>(a, d, t, vd, s_vd, s_ig); });
+    } else {
+        // column-blocked tiles run in the wide launch group only (512- or
+        // 1024-thread workgroups; the runtime places them there); elsewhere the
+        // same rows take the gathers below
+        if constexpr (BLOCK >= 512) {
+            if (d.blocked && d.cb_off >= 0) {
+                by_weights<W>(d, [&](auto hw) {
+                    gap_chunks_blocked<BLOCK, decltype(hw)::value, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
+                });
+                return;
+            }
+        }
+        if (d.flat) {
+            by_weights<W>(d, [&](auto hw) { gap_flat<BLOCK, decltype(hw)::value, SGJ, var_vd_first(VAR)>(a, d, t, vd, s_vd, s_ig); });
             return;
         }
-    }
-    if (d.vd_lds) {
-        for (int k = threadIdx.x; k < d.n; k += BLOCK) s_vd[k] = vd[k] * kPreScale;
-        __syncthreads();
-    }
-    by_weights<W>(d, [&](auto hw) {
-        constexpr bool HW = decltype(hw)::value;
-        if (d.chunked && d.ca_off >= 0) {
-            if (d.vd_lds) gap_chunks<BLOCK, true, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
-            else gap_chunks<BLOCK, false, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
-        } else if (d.vd_lds) {
-            if (d.col16) gap_csr_impl<BLOCK, true, true, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
-            else gap_csr_impl<BLOCK, true, false, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
-        } else {
-            if (d.col16) gap_csr_impl<BLOCK, false, true, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
-            else gap_csr_impl<BLOCK, false, false, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
+        if (d.vd_lds) {
+            for (int k = threadIdx.x; k < d.n; k += BLOCK) s_vd[k] = vd[k] * kPreScale;
+            __syncthreads();
         }
-    });
+        by_weights<W>(d, [&](auto hw) {
+            constexpr bool HW = decltype(hw)::value;
+            if (d.chunked && d.ca_off >= 0) {
+                gap_chunks<BLOCK, HW, SGJ>(a, d, t, vd, s_part, s_ig);
+            } else if (d.vd_lds) {
+                if (d.col16) gap_csr_impl<BLOCK, true, true, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
+                else gap_csr_impl<BLOCK, true, false, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
+            } else {
+                if (d.col16) gap_csr_impl<BLOCK, false, true, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
+                else gap_csr_impl<BLOCK, false, false, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
+            }
+        });
+    }
 }
 
-// W: the launch may hold networks with per-edge weights (their paths are
-// compiled in; they hold a batch of weights in registers).
-// L: it may hold networks with the simplified term.
-template <int BLOCK, bool W, bool L>
+template <int BLOCK, int VAR>
 __device__ __forceinline__ void gap_csr(const StepArgs& a, const InstDesc& d, const Tile& t,
                                         const float* __restrict__ vd, float* s_vd, float* s_part,
                                         float* s_ig) {
-    if constexpr (L) {
-        if (d.sgj) {
-            gap_csr_form<BLOCK, true, W>(a, d, t, vd, s_vd, s_part, s_ig);
-            return;
-        }
-    }
-    gap_csr_form<BLOCK, false, W>(a, d, t, vd, s_vd, s_part, s_ig);
+    if (d.sgj) gap_csr_form<BLOCK, true, VAR>(a, d, t, vd, s_vd, s_part, s_ig);
+    else gap_csr_form<BLOCK, false, VAR>(a, d, t, vd, s_vd, s_part, s_ig);
 }
 
 // Bitmap words of a network: group gr (128 senders), row r (padded to a
@@ -1427,19 +1564,6 @@ __device__ __forceinline__ float evoked_input(const StepArgs& a, const InstDesc&
     return iapp;
 }
 
-// Kernel variants by the tiles a launch holds; the narrow ones are compiled
-// without the paths they exclude and their registers, so that more waves per
-// SIMD keep loads in flight. kVarAll: any tile. kVarNoGap: every tile belongs
-// to a network without gap junctions (the compartment update alone). kVarNoW:
-// no per-edge weights, per-cell parameters or dense matrices, no CSR network
-// with the simplified term and no voltage grid. kVarBoth: the same with those
-// two. kVarStream:
-// every tile is a chunk stream tile (column blocks, no per-edge weights, no
-// per-cell parameters), the only gap path it compiles. kVarDense: every tile
-// belongs to a network with a dense weight matrix or without gap junctions
-// (256-thread workgroups).
-enum : int { kVarAll = 0, kVarNoGap = 1, kVarNoW = 2, kVarStream = 3, kVarDense = 4, kVarBoth = 5 };
-
 template <int BLOCK, int VAR>
 __device__ __forceinline__ void step_body(const StepArgs& a, const float* __restrict__ xin, float* __restrict__ xout,
                                           int64_t step_arg, int32_t step_off, float* s_ig, float* s_part,
@@ -1448,7 +1572,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const float* __rest
     const Tile t = a.tiles[blockIdx.x];
     const InstDesc& d = a.inst[t.inst];
     const int64_t step = (a.d_step ? *a.d_step : step_arg) + step_off;
-    const float* vd = xin + (int64_t)SV_VD * a.stride + d.cell_off;
+    const float* vd = xin + (int64_t)SV_VD * a.stride + t.cell_off;
     const int nrows = t.row1 - t.row0;
 
     // The compartment update of cell row0 + k: with at most 64 rows, lane k
@@ -1461,7 +1585,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const float* __rest
     const int part = split ? (int)(threadIdx.x >> 6) : 0;   // 0: dendrite + axon (or all), 1: soma
     const bool own = k_own < nrows && part < 2 && !a.gap_only;
     const int li = t.row0 + k_own;
-    const int64_t cell = d.cell_off + li;
+    const int64_t cell = t.cell_off + li;
     float x[NSV];
     float iapp = 0.0f;
     if (own) {
@@ -1486,24 +1610,29 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const float* __rest
     } else {
         switch (d.conn) {
             case CONN_UNIFORM:
-                if constexpr (VAR != kVarNoW) {
-                    if (d.grid) {
-                        gap_uniform_grid<BLOCK>(a, d, t, vd, s_ig, s_part, s_red, reinterpret_cast<double*>(s_v4));
-                        break;
-                    }
+                if (d.sgj && d.sym) {
+                    gap_uniform_sum<BLOCK>(a, d, t, vd, s_ig, s_red);
+                    break;
                 }
-                if (d.sgj && d.sym) gap_uniform_sum<BLOCK>(a, d, t, vd, s_ig, s_red);
-                else gap_uniform<BLOCK>(a, d, t, vd, s_ig, s_v4, s_part, s_red);
+                if constexpr (var_uniform(VAR)) {
+                    if (d.grid) gap_uniform_grid<BLOCK>(a, d, t, vd, s_ig, s_part, s_red, reinterpret_cast<double*>(s_v4));
+                    else gap_uniform<BLOCK>(a, d, t, vd, s_ig, s_v4, s_part, s_red);
+                }
                 break;
             case CONN_DENSE:
-                if constexpr (VAR != kVarNoW) {
+                if constexpr (VAR == kVarAll) {
                     if (d.sgj) gap_dense<BLOCK, true>(a, d, t, vd, s_part, s_ig);
                     else gap_dense<BLOCK, false>(a, d, t, vd, s_part, s_ig);
                 }
                 break;
             case CONN_CSR:
-                if (d.bitmap) gap_bitmap<BLOCK>(a, d, t, vd, reinterpret_cast<float*>(s_v4), s_part, s_ig);
-                else gap_csr<BLOCK, VAR == kVarAll, VAR != kVarNoW>(a, d, t, vd, reinterpret_cast<float*>(s_v4), s_part, s_ig);
+                if constexpr (var_gathers(VAR)) {
+                    if (d.bitmap) {
+                        gap_bitmap<BLOCK>(a, d, t, vd, reinterpret_cast<float*>(s_v4), s_part, s_ig);
+                        break;
+                    }
+                }
+                gap_csr<BLOCK, VAR>(a, d, t, vd, reinterpret_cast<float*>(s_v4), s_part, s_ig);
                 break;
             default:
                 for (int k = threadIdx.x; k < nrows; k += BLOCK) s_ig[k] = 0.0f;
@@ -1513,13 +1642,13 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const float* __rest
     __syncthreads();
 
     if (a.gap_only) {
-        for (int k = threadIdx.x; k < nrows; k += BLOCK) a.igap_out[d.cell_off + t.row0 + k] = s_ig[k];
+        for (int k = threadIdx.x; k < nrows; k += BLOCK) a.igap_out[t.cell_off + t.row0 + k] = s_ig[k];
         return;
     }
     // per-cell parameters exist in the general variant only (the runtime
     // launches networks that have them with it)
     CellParams pc = d.p;
-    if constexpr (VAR == kVarAll) {
+    if constexpr (var_cells(VAR)) {
         if (own) pc = cell_params_of(a, d, cell);
     }
     if (own && split) {
@@ -1581,15 +1710,20 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const float* __rest
 // all-to-all chunk (min(n, kChunk) + 8 per wave) or the largest LDS-staged
 // CSR network. The chunk stream variant has no static LDS, so its staged
 // voltages start at LDS address 0 (a gather's address is its column times
-// four, with no base to add) and its row sums follow the stream's region.
+// four, with no base to add) and its row sums follow the stream's region; the
+// same holds for the var_vd_first variants.
 template <int BLOCK, int VAR = kVarAll>
-__global__ __launch_bounds__(BLOCK, VAR == kVarBoth ? 5 : 1) void k_step(StepArgs a, const float* __restrict__ xin,
+__global__ __launch_bounds__(BLOCK, var_waves(VAR)) void k_step(StepArgs a, const float* __restrict__ xin,
                                                 float* __restrict__ xout, int64_t step_arg,
                                                 int32_t step_off) {
     extern __shared__ float4 s_v4[];
     if constexpr (VAR == kVarStream) {
         float* s_ig = reinterpret_cast<float*>(s_v4) + stream_lds_floats<BLOCK>(kStreamCols);
         step_body<BLOCK, VAR>(a, xin, xout, step_arg, step_off, s_ig, nullptr, nullptr, s_v4);
+    } else if constexpr (var_vd_first(VAR)) {
+        double* s_red = reinterpret_cast<double*>(reinterpret_cast<float*>(s_v4) + a.lds_floats);
+        float* s_part = reinterpret_cast<float*>(s_red + BLOCK / 64);
+        step_body<BLOCK, VAR>(a, xin, xout, step_arg, step_off, s_part + BLOCK, s_part, s_red, s_v4);
     } else {
         __shared__ float s_ig[kMaxTileRows];
         __shared__ float s_part[BLOCK];

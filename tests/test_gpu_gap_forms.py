@@ -109,3 +109,39 @@ def test_voltage_grid_keeps_a_bad_voltage_visible(infoli, n):
     assert e.value.status == 5
     assert not np.any(np.isfinite(sim.read_gap_current(0)))
     sim.close()
+
+
+def er_net(n, deg, seed, **kw):
+    rp, col = I.erdos_renyi_csr(n, min(1.0, deg / max(n - 1, 1)), seed)
+    rs = I.rng(seed + 1)
+    return I.Network(n=n, conn="csr", g=0.04 * 96 / max(deg, 96.0), row_ptr=rp, col=col,
+                     jitter=rs.uniform(-15, 15, (3, n)), **kw)
+
+
+@pytest.mark.parametrize("gap", ["rgj", "sgj"])
+@pytest.mark.parametrize("weights", [False, True])
+@pytest.mark.parametrize("n,deg,rows", [(2, 1, 0), (255, 3, 256), (257, 40, 7), (1001, 200, 256),
+                                             (1500, 1400, 8), (4099, 60, 100), (8193, 20, 256),
+                                             (20001, 30, 64), (33000, 10, 32)])
+def test_flat_chunked_rows(infoli, o64, n, deg, rows, weights, gap):
+    """Chunked rows as flat runs (csr_path=4): rows without connections, tiles
+    of one and of many chunks per thread, tile heights that are no power of
+    two, the largest network staged whole and one beyond it; alone, and
+    behind an odd number of cells beside all-to-all networks with and without
+    the voltage grid."""
+    net = er_net(n, deg, n, gap=gap)
+    if weights:
+        net.w_csr = (I.rng(n).uniform(0.5, 1.5, len(net.col)) * net.g).astype(np.float32)
+    x0 = infoli.initial_state(net)
+    sim = infoli.Simulator(net, init_states=[x0], csr_path=4, tile_rows=rows, step_mode="graph")
+    assert sim.gap_path(0) == ("csr_chunked", False)
+    check_gap(sim, 0, net, x0[0], o64)
+    sim.close()
+    others = [I.Network(n=m, conn="uniform", g=0.01, jitter=I.voltage_jitter(m, m, 15.0)) for m in (33, 600)]
+    x0s = [infoli.initial_state(o) for o in others]
+    sim = infoli.Simulator(others + [net], init_states=x0s + [x0], csr_path=4, tile_rows=rows, step_mode="graph")
+    for k, (m, x) in enumerate(zip(others + [net], x0s + [x0])):
+        check_gap(sim, k, m, x[0], o64)
+    sim.step(1)
+    assert np.all(np.isfinite(sim.read_state(2)))
+    sim.close()
