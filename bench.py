@@ -394,7 +394,7 @@ def step_kernel_name(info, nets, paths=None):
     if info["step_mode"] == 3:
         return "infoli::k_persist"
     if paths and any(p == "uniform_sym" for p in paths):
-        rest = step_kernel_name(info, nets, [p if p != "uniform_sym" else "uniform" for p in paths])
+        rest = step_kernel_name(info, nets, [p if p != "uniform_sym" else "" for p in paths])
         return "infoli::k_pairs_sym + " + rest
     if paths and any(p == "uniform_sum" for p in paths):
         rest = step_kernel_name(info, nets, [p if p != "uniform_sum" else "uniform" for p in paths])
@@ -404,7 +404,7 @@ def step_kernel_name(info, nets, paths=None):
         return "infoli::k_grid_sums + " + rest
     if paths and all(p == "csr_stream" for p in paths):
         return f"infoli::k_step<{info.get('wide_threads', 1024)}, 3>"
-    own = [p or "csr_chunked" for p in paths] if paths else ["csr_chunked"] * len(nets)
+    own = [p or ("csr_chunked" if n.conn == "csr" else "") for n, p in zip(nets, paths)] if paths else ["csr_chunked"] * len(nets)
     flat = all(n.conn == "none" or p == "csr_chunked" for n, p in zip(nets, own) if n.conn in ("none", "csr"))
     plain = all(n.w_csr is None and n.cell_params is None and n.conn != "dense" for n in nets)
     if all(n.conn == "none" and n.cell_params is None for n in nets):
