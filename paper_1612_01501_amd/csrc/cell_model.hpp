@@ -77,10 +77,16 @@ __device__ __forceinline__ float ratio_expm1(float x, float s) {
 // each compartment's next state is a function of x alone; the three parts
 // below write disjoint entries of y and together are cell_step.
 
-// Dendrite part: y[Vd, Ca, r, s, q]. igap: gap current leaving the dendrite,
-// iapp: evoked input into the dendrite, dt in ms.
-__device__ __forceinline__ void cell_step_dendrite(const CellParams& p, const float* __restrict__ x,
-                                                   float igap, float iapp, float dt, float* __restrict__ y) {
+// The high-threshold Ca current of the dendrite.
+__device__ __forceinline__ float dendrite_icah(const CellParams& p, const float* __restrict__ x) {
+#pragma clang fp contract(on)
+    return p.gCaH * x[SV_R] * x[SV_R] * (x[SV_VD] - p.eCa);
+}
+
+// Dendrite voltage: y[Vd]. igap: gap current leaving the dendrite, iapp: evoked
+// input into the dendrite, dt in ms.
+__device__ __forceinline__ void cell_step_vd(const CellParams& p, const float* __restrict__ x, float igap,
+                                             float iapp, float dt, float* __restrict__ y) {
 #pragma clang fp contract(on)
     const float vd = x[SV_VD], vs = x[SV_VS];
 
@@ -88,14 +94,21 @@ __device__ __forceinline__ void cell_step_dendrite(const CellParams& p, const fl
     // leak, coupling to the soma, gap junctions and the evoked input.
     // (each current's conductance factor times its driving force, the net
     // current accumulated with fused multiply-adds)
-    const float icah = p.gCaH * x[SV_R] * x[SV_R] * (vd - p.eCa);
-    float dvd = iapp - igap - icah;
+    float dvd = iapp - igap - dendrite_icah(p, x);
     dvd = fmaf(-(p.gInt * rcp(1.0f - p.p1)), vd - vs, dvd);       // to the soma
     dvd = fmaf(-(p.gKCa * x[SV_S]), vd - p.eK, dvd);                // Ca-activated K
     dvd = fmaf(-(p.gH * x[SV_Q]), vd - p.eH, dvd);                  // h current
     dvd = fmaf(-p.gLd, vd - p.eL, dvd);                             // leak
+    // C_m = 1 uF/cm^2: dV/dt equals the net inward current density.
+    y[SV_VD] = fmaf(dt, dvd, vd);
+}
 
-    const float dca = fmaf(-3.0f, icah, -0.075f * x[SV_CA]);
+// Dendrite without its voltage: y[Ca, r, s, q] (no gap current).
+__device__ __forceinline__ void cell_step_dgates(const CellParams& p, const float* __restrict__ x, float dt,
+                                                 float* __restrict__ y) {
+#pragma clang fp contract(on)
+    const float vd = x[SV_VD];
+    const float dca = fmaf(-3.0f, dendrite_icah(p, x), -0.075f * x[SV_CA]);
 
     const float ar = 1.7f * boltz(vd, 5.0f, l2(-1.0 / 13.9));
     const float br = 0.02f * ratio_expm1(vd + 8.5f, 5.0f);
@@ -109,12 +122,17 @@ __device__ __forceinline__ void cell_step_dendrite(const CellParams& p, const fl
     const float rq = exp_aff(vd, float(-14.6 / 0.086), l2(-0.086)) + exp_aff(vd, float(1.87 / 0.070), l2(0.070));
     const float dq = (qinf - x[SV_Q]) * rq;
 
-    // C_m = 1 uF/cm^2: dV/dt equals the net inward current density.
-    y[SV_VD] = fmaf(dt, dvd, vd);
     y[SV_CA] = fmaf(dt, dca, x[SV_CA]);
     y[SV_R] = fmaf(dt, dr, x[SV_R]);
     y[SV_S] = fmaf(dt, ds, x[SV_S]);
     y[SV_Q] = fmaf(dt, dq, x[SV_Q]);
+}
+
+// Dendrite part: y[Vd, Ca, r, s, q].
+__device__ __forceinline__ void cell_step_dendrite(const CellParams& p, const float* __restrict__ x,
+                                                   float igap, float iapp, float dt, float* __restrict__ y) {
+    cell_step_vd(p, x, igap, iapp, dt, y);
+    cell_step_dgates(p, x, dt, y);
 }
 
 // Soma part: y[Vs, k, l, h, n, x].

@@ -104,7 +104,7 @@ struct infoli_ctx {
     int64_t stride = 0;
     int64_t pairs_per_step = 0;
     float dt = 0.05f;
-    int persist_cpt = 1;            // cells per thread of the persistent kernel
+    int persist_cells = 1;          // cells of the largest network (the persistent kernel's variant)
     // tiles of one step, in two launches: [0] 256-thread workgroups (edge
     // gathers, small networks), [1] the wide group, 1024- or 512-thread
     // workgroups (column blocks, wide bitmaps, large all-to-all networks, or

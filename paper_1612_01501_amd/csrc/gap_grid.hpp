@@ -97,17 +97,42 @@ __device__ __forceinline__ void grid_add(double (&acc)[kGridGroup], double t0, f
     }
 }
 
+// Exchanges within the 16 lanes of a row by DPP, without a trip through LDS.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor7 = 0x141, kDppXor8 = 0x128;
+template <int CTRL>
+__device__ __forceinline__ float dpp_lane(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_lane(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+// op over the 64 lanes, the same in each (op: +, min or max)
+template <typename T, typename F>
+__device__ __forceinline__ T grid_wave(T v, F&& op) {
+    v = op(v, dpp_lane<kDppXor1>(v));
+    v = op(v, dpp_lane<kDppXor2>(v));
+    v = op(v, dpp_lane<kDppXor7>(v));
+    v = op(v, dpp_lane<kDppXor8>(v));
+    v = op(v, __shfl_xor(v, 16, 64));
+    return op(v, __shfl_xor(v, 32, 64));
+}
+
 // Sum over the 64 lanes: lane l ends with point (l & 15)'s sum (four exchanges
-// that halve the points a lane holds, then two that add the four groups of
+// that halve the points a lane holds, each with a lane whose bit H differs and
+// whose higher bits below 16 do not, then two that add the four groups of
 // sixteen lanes).
 template <int H>
 __device__ __forceinline__ void grid_halve(double (&v)[kGridGroup], int lane) {
+    constexpr int ctrl = H == 8 ? kDppXor8 : H == 4 ? kDppXor7 : H == 2 ? kDppXor2 : kDppXor1;
     const bool hi = (lane & H) != 0;
 #pragma unroll
     for (int i = 0; i < H; ++i) {
         const double send = hi ? v[i] : v[i + H];
         const double keep = hi ? v[i + H] : v[i];
-        v[i] = keep + __shfl_xor(send, H, 64);
+        v[i] = keep + dpp_lane<ctrl>(send);
     }
 }
 __device__ __forceinline__ double grid_lane_sum(double (&acc)[kGridGroup], int lane) {
@@ -177,7 +202,7 @@ static __global__ __launch_bounds__(512) void k_grid_sums(const float* __restric
     if (wave == 7) {
         double s = 0.0;
         for (int j = j0 + lane; j < j1; j += 64) s += (double)vd[j];
-        for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
+        s = grid_wave(s, [](double x, double y) { return x + y; });
         if (lane == 0) P[(int64_t)kGridAheadGroups * C * kGridGroup + c] = s;
     }
 }

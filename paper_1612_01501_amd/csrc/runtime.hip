@@ -1495,8 +1495,7 @@ void build_context(infoli_ctx* c, const infoli_network_spec* specs, int32_t nins
         if (c->opt.autotune) persist_candidate = true;
         else if (cheap_rows) c->opt.step_mode = INFOLI_MODE_PERSISTENT;
     }
-    c->persist_cpt = 1;
-    while (c->persist_cpt * kPersistBlock < max_n) c->persist_cpt *= 2;
+    c->persist_cells = max_n;
     c->total_cells = cells;
     c->stride = (cells + 63) & ~int64_t(63);
 
@@ -1762,12 +1761,29 @@ void launch_persistent(infoli_ctx* c, int64_t n_steps, bool dry) {
     const dim3 grid((unsigned)c->n_inst), block(kPersistBlock);
     const float* xin = c->state[c->cur];
     float* xout = c->state[c->cur ^ 1];
-    switch (c->persist_cpt) {
-        case 1: hipLaunchKernelGGL(k_persist<1>, grid, block, 0, c->stream, a, xin, xout, c->step, n_steps); break;
-        case 2: hipLaunchKernelGGL(k_persist<2>, grid, block, 0, c->stream, a, xin, xout, c->step, n_steps); break;
-        case 4: hipLaunchKernelGGL(k_persist<4>, grid, block, 0, c->stream, a, xin, xout, c->step, n_steps); break;
-        default: hipLaunchKernelGGL(k_persist<8>, grid, block, 0, c->stream, a, xin, xout, c->step, n_steps); break;
-    }
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, c->stream, a, xin, xout, c->step, n_steps);
+    };
+    int form = kFormNone;
+    for (const InstDesc& d : c->inst)
+        if (d.conn == CONN_CSR || d.conn == CONN_DENSE) form |= kFormRows;
+        else if (d.conn == CONN_UNIFORM && !d.sgj) form |= kFormPairs;
+    if (c->n_inst > 1 && form != kFormNone) form = kFormAny;
+    const auto by_form = [&](auto cpt, auto split) {
+        constexpr int C = decltype(cpt)::value;
+        constexpr bool S = decltype(split)::value;
+        switch (form) {
+            case kFormNone: return go(k_persist<C, S, kFormNone>);
+            case kFormPairs: return go(k_persist<C, S, kFormPairs>);
+            case kFormRows: return go(k_persist<C, S, kFormRows>);
+            default: return go(k_persist<C, S, kFormAny>);
+        }
+    };
+    const std::integral_constant<int, 1> one{};
+    const std::integral_constant<int, 2> two{};
+    if (c->persist_cells <= kPersistSplit) by_form(one, std::true_type{});
+    else if (c->persist_cells <= kPersistBlock) by_form(one, std::false_type{});
+    else by_form(two, std::false_type{});
     if (dry) return;
     c->cur ^= 1;
     c->step += n_steps;

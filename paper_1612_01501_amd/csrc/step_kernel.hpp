@@ -393,11 +393,8 @@ __device__ __forceinline__ void gap_uniform_grid(const StepArgs& a, const InstDe
     const int n = d.n;
     const int nrows = t.row1 - t.row0;
     const float v = vd[t.row0 + min((int)threadIdx.x, nrows - 1)];
-    float lo = v, hi = v;
-    for (int m = 32; m > 0; m >>= 1) {
-        lo = fminf(lo, __shfl_xor(lo, m, 64));
-        hi = fmaxf(hi, __shfl_xor(hi, m, 64));
-    }
+    float lo = grid_wave(v, [](float x, float y) { return fminf(x, y); });
+    float hi = grid_wave(v, [](float x, float y) { return fmaxf(x, y); });
     const bool bad = __any(!(fabsf(v) <= 1.0e6f));      // (a NaN too: min and max pass it by)
     if (lane == 0) {
         s_part[wave] = lo;
@@ -478,7 +475,7 @@ __device__ __forceinline__ void gap_uniform_grid(const StepArgs& a, const InstDe
             if (lane < kGridGroup) s_g[wave * GP + g * kGridGroup + lane] = s;
         }
     }
-    for (int m = 32; m > 0; m >>= 1) vsum += __shfl_xor(vsum, m, 64);
+    vsum = grid_wave(vsum, [](double x, double y) { return x + y; });
     if (lane == 0) s_red[wave] = vsum;
     __syncthreads();
     double* s_f = s_g + W * GP;

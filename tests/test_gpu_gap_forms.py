@@ -145,3 +145,40 @@ def test_flat_chunked_rows(infoli, o64, n, deg, rows, weights, gap):
     sim.step(1)
     assert np.all(np.isfinite(sim.read_state(2)))
     sim.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 191, 192, 193, 1024, 1025, 2048])
+@pytest.mark.parametrize("conn", ["uniform", "sgj", "csr", "dense", "none"])
+def test_persistent_sizes(infoli, o32, o64, conn, n):
+    """The persistent kernel at the sizes where its arrangement changes (a wave
+    per part, split up to 192 cells, one or two cells per thread), with
+    pulses, input stream and output ring: 60 steps in launches of odd lengths
+    against the oracle and against one launch, bitwise."""
+    from test_gpu_parity import check_state_bounds
+    rs = I.rng(n + 3)
+    kw = dict(jitter=rs.uniform(-10, 10, (3, n)), bias=I.input_bias(n, n), g=0.04 * 96 / max(n, 96),
+              pulses=[I.Pulse(5, 30, 6.0), I.Pulse(20, 50, -2.0, 0, max(1, n // 2))])
+    if conn == "csr":
+        net = er_net(n, 20, n + 5)
+        net.pulses, net.bias = kw["pulses"], kw["bias"]
+    elif conn == "dense":
+        net = I.Network(n=n, conn="dense", w_dense=rs.uniform(0, 2 * kw["g"], (n, n)).astype(np.float32), **kw)
+    else:
+        net = I.Network(n=n, conn="uniform" if conn == "sgj" else conn, gap="sgj" if conn == "sgj" else "rgj", **kw)
+    stream = rs.normal(0.0, 1.0, (40, n)).astype(np.float32)
+    x0 = infoli.initial_state(net)
+    ends = []
+    for lengths in ((60,), (7, 1, 52)):
+        sim = infoli.Simulator(net, init_states=[x0], i_streams=[stream], step_mode="persistent", output_ring_steps=16)
+        for k in lengths:
+            sim.step(k)
+        out = np.zeros((16, n), np.float32)
+        sim.output_copy_async(44, 16, out.ctypes.data, out.size)
+        sim.output_wait()
+        ends.append(sim.read_state(0))
+        np.testing.assert_array_equal(out[-1], ends[-1][11])
+        sim.close()
+    np.testing.assert_array_equal(ends[0], ends[1])
+    ref = o32.run(net, 60, x0=x0, i_stream=stream)["x"]
+    r64 = o64.run(net, 60, x0=x0.astype(np.float64), i_stream=stream.astype(np.float64))["x"]
+    check_state_bounds(ends[0][None], ref[None], r64[None], f"persistent {conn} {n}")
