@@ -77,8 +77,6 @@ struct SurrogateState {
     float norm[64] = {0};               // in_mean[16] in_rstd[16] out_mean[16] out_std[16]
     int32_t* hold = nullptr;            // [cells]
     unsigned long long* counters = nullptr;   // [4] plain, checked, flagged, guarded
-    void* list = nullptr;               // [cells] cells for the plain method this macro step
-    unsigned int* list_count = nullptr;
 };
 
 }  // namespace infoli_rt

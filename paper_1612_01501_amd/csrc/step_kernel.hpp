@@ -140,7 +140,6 @@ struct StepArgs {
     float* spike_times;        // [cells][spike_cap]
     int32_t* flags;            // [0]: non-finite state seen
     float* igap_out;           // gap-only mode: [cells]
-    unsigned int* list_reset;  // when set, workgroup 0 zeroes it (the surrogate's plain-cell list)
     const int64_t* d_step;     // when set, step = *d_step + step offset
     int64_t stride;            // state row stride (floats)
     float dt;
@@ -1548,9 +1547,8 @@ __device__ __forceinline__ void gap_bitmap(const StepArgs& a, const InstDesc& d,
     }
 }
 
-__device__ __forceinline__ float evoked_input(const StepArgs& a, const InstDesc& d, int64_t step,
-                                              int li, int64_t cell) {
-    float iapp = a.bias[cell];
+// Evoked input of a cell at a step, `iapp` its bias.
+__device__ __forceinline__ float evoked_from(float iapp, const StepArgs& a, const InstDesc& d, int64_t step, int li) {
     if (step >= d.p0_n0 && step < d.p0_n1 && li >= d.p0_c0 && li < d.p0_c1) iapp += d.p0_amp;
     for (int k = 1; k < d.n_pulses; ++k) {
         const DevPulse pl = a.pulses[d.pulse_off + k];
@@ -1560,12 +1558,15 @@ __device__ __forceinline__ float evoked_input(const StepArgs& a, const InstDesc&
         iapp += a.i_stream[d.stream_off + step * (int64_t)d.n + li];
     return iapp;
 }
+__device__ __forceinline__ float evoked_input(const StepArgs& a, const InstDesc& d, int64_t step,
+                                              int li, int64_t cell) {
+    return evoked_from(a.bias[cell], a, d, step, li);
+}
 
 template <int BLOCK, int VAR>
 __device__ __forceinline__ void step_body(const StepArgs& a, const float* __restrict__ xin, float* __restrict__ xout,
                                           int64_t step_arg, int32_t step_off, float* s_ig, float* s_part,
                                           double* s_red, float4* s_v4) {
-    if (a.list_reset && blockIdx.x == 0 && threadIdx.x == 0) *a.list_reset = 0u;
     const Tile t = a.tiles[blockIdx.x];
     const InstDesc& d = a.inst[t.inst];
     const int64_t step = (a.d_step ? *a.d_step : step_arg) + step_off;

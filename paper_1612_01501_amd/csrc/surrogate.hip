@@ -62,9 +62,6 @@ void ensure_surrogate_buffers(infoli_ctx* c) {
     s.counters = c->alloc<unsigned long long>(4);
     HIPX(hipMemset(s.hold, 0, sizeof(int32_t) * c->stride));
     HIPX(hipMemset(s.counters, 0, sizeof(unsigned long long) * 4));
-    s.list = c->alloc<PlainEntry>(c->stride);
-    s.list_count = c->alloc<unsigned int>(1);
-    HIPX(hipMemset(s.list_count, 0, sizeof(unsigned int)));
 }
 
 void check_params(const float* p, int64_t n) {
@@ -103,18 +100,7 @@ SurrArgs surr_args(infoli_ctx* c, const infoli_drift_cfg& dc, int64_t macro_inde
     a.z_max = dc.z_max;
     a.sample_every = dc.sample_every;
     a.hold_steps = dc.hold_steps;
-    a.mode = dc.mode;
     a.macro_index = macro_index;
-    a.list = static_cast<PlainEntry*>(c->surr.list);
-    a.list_count = c->surr.list_count;
-    // checked cells this macro step: (cell + macro_index) % sample_every == 0
-    a.check_first = 0;
-    a.n_checks = 0;
-    if (dc.mode == INFOLI_SURROGATE_MLP && dc.sample_every > 0) {
-        const int64_t S = dc.sample_every;
-        a.check_first = (S - macro_index % S) % S;
-        a.n_checks = a.check_first < c->total_cells ? (c->total_cells - 1 - a.check_first) / S + 1 : 0;
-    }
     return a;
 }
 
@@ -123,7 +109,6 @@ SurrArgs surr_args(infoli_ctx* c, const infoli_drift_cfg& dc, int64_t macro_inde
 void launch_macro(infoli_ctx* c, hipStream_t st, const infoli_drift_cfg& dc, int from, int64_t step0) {
     StepArgs g = make_args(c, false);
     g.gap_only = 1;
-    g.list_reset = c->surr.list_count;
     launch_groups(c, st, g, from, step0, 0, false);
     const StepArgs a = make_args(c, false);
     const int64_t cells = c->total_cells;
@@ -133,14 +118,18 @@ void launch_macro(infoli_ctx* c, hipStream_t st, const infoli_drift_cfg& dc, int
         return;
     }
     const SurrArgs s = surr_args(c, dc, step0 / kMacro);
-    // three workgroups (twelve waves, 148 VGPRs each) per compute unit: LDS
-    // holds three 42 KB weight copies (two per CU measured 1.6 % slower)
-    const unsigned blocks = (unsigned)std::min<int64_t>((cells + 63) / 64, 3 * (int64_t)c->n_cu);
-    hipLaunchKernelGGL(k_surrogate_step, dim3(blocks), dim3(256), 0, st, a, s, c->state[from],
-                       c->state[from ^ 1], step0, cells);
-    const unsigned lblocks = (unsigned)std::min<int64_t>((cells + 63) / 64, 2048);
-    hipLaunchKernelGGL(k_plain_list, dim3(lblocks), dim3(kListBlock), 0, st, a, s, c->state[from],
-                       c->state[from ^ 1], step0);
+    // Eight waves a workgroup share one copy of the weights and one plain phase,
+    // from where four-wave workgroups would already stand on every compute unit
+    // (16,384 cells 22.9 -> 22.3 us per macro step with the gap kernel, 32,768
+    // cells 27.8 -> 25.7, 65,536 cells 38.0 -> 36.4); below, they would leave
+    // compute units without work (2,000 cells: 20.3 us, 18.9 with four waves).
+    const auto go = [&](auto kernel, int block, int64_t most) {
+        const int64_t per = surr_cells(block);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)std::min<int64_t>((cells + per - 1) / per, most)), dim3(block), 0, st, a,
+                           s, c->state[from], c->state[from ^ 1], step0, cells);
+    };
+    if (cells >= (int64_t)surr_cells(256) * c->n_cu) go(k_surrogate_step<512>, 512, 2 * (int64_t)c->n_cu);
+    else go(k_surrogate_step<256>, 256, 3 * (int64_t)c->n_cu);
 }
 
 // ---------------------------------------------------------------- staging without allocation

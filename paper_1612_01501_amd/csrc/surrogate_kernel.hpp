@@ -41,20 +41,14 @@ struct SurrArgs {
     float z_max;                // normalised inputs beyond +-z_max: plain method (0: no bound)
     int32_t sample_every;       // check cells with (cell + macro) % sample_every == 0; 0 = never
     int32_t hold_steps;         // macro steps a flagged cell stays on the plain method
-    int32_t mode;               // 0 surrogate, 1 plain for every cell (gap held 4 steps)
     int64_t macro_index;
-    struct PlainEntry* list;    // cells for the plain method this macro step: the checked cells
-                                // first (cell check_first + i * sample_every at slot i), then
-                                // the others, appended
-    unsigned int* list_count;   // appended entries; zeroed by the macro step's gap launch
-    int64_t check_first;        // first checked cell of this macro step
-    int64_t n_checks;           // checked cells (0 when sample_every == 0)
 };
 
 // A cell handed to the plain method, with the MLP's candidate voltages (used
 // when the cell is checked).
 struct PlainEntry {
     int32_t cell;
+    int32_t check;
     float vd, vs, va;
 };
 
@@ -65,60 +59,179 @@ constexpr unsigned long long kCellLanes = 0x0001000100010001ull;
 
 constexpr int kMacro = 4;
 
-// One wave = 16 cells; four lanes per cell (feature groups of four).
-static __global__ __launch_bounds__(256) void k_surrogate_step(StepArgs a, SurrArgs s, const float* __restrict__ xin,
-                                                        float* __restrict__ xout, int64_t step0,
-                                                        int64_t n_cells_total) {
+constexpr int surr_cells(int block) { return block / 64 * 16; }    // cells per pass of a workgroup
+constexpr int surr_plain(int block) { return block / 128 * 64; }   // cells of one plain phase: 64 per pair of waves
+
+// One macro step. Each wave takes 16 cells per pass, four lanes per cell
+// (feature groups of four), through the MLP; the cells that need the plain
+// method gather in the workgroup's LDS list, and when the list could overflow
+// or the cells are done, pairs of waves advance 64 of them each: four plain
+// forward-Euler steps with the macro step's gap current held, the first wave
+// their dendrites and axons, the second their somas (cell_step's arithmetic,
+// split by compartment), the voltages exchanged through LDS after every step;
+// then spikes, and for checked cells the drift test against the MLP candidate
+// (past theta: hold_steps macro steps of plain method).
+//
+// One kernel, because the list of a kernel of its own cost more than its
+// cells' steps: every wave with such a cell waited for an atomic on one address
+// (16,384 cells of which a fifth were held: 17.3 us, 8.8 without any), and the
+// listed cells' kernel took another 8.0 us for four steps of any number of
+// cells. A macro step with its gap kernel and a rotating sixteenth checked:
+// 16,384 cells 40.4 -> 24.2 us, 65,536 cells 74.9 -> 38.3, 2,000 cells 22.5 ->
+// 18.9. What is left is a chain: weights to LDS, the layers' matrix products
+// each on the one before, then four dependent cell steps.
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK, 4) void k_surrogate_step(StepArgs a, SurrArgs s, const float* __restrict__ xin,
+                                                             float* __restrict__ xout, int64_t step0,
+                                                             int64_t n_cells_total) {
+    constexpr int PAIRS = BLOCK / 128;
+    constexpr int CELLS = surr_cells(BLOCK), PLAIN = surr_plain(BLOCK);
     __shared__ __align__(16) uint16_t s_w[kMlpLdsElems];
+    __shared__ PlainEntry s_list[PLAIN];
+    __shared__ float s_x[PAIRS][2][3][64];         // Vd, Vs, Va of a pair's cells, alternating steps
+    __shared__ int s_count;
+    __shared__ int s_sum[4];                       // plain, checked, flagged, guarded of this workgroup
     const MlpSmem sm = mlp_smem(s_w);
-    if (s.mode == 0) {
-        load_weights_lds(s.wb, sm);
-        __syncthreads();
-    }
     const int l = threadIdx.x & 63;
     const int g = l >> 4;
-    const int waves = blockDim.x >> 6;
-    for (int64_t base = ((int64_t)blockIdx.x * waves + (threadIdx.x >> 6)) * 16; base < n_cells_total;
-         base += (int64_t)gridDim.x * waves * 16) {
-        const int64_t cell = base + (l & 15);
+    const int wave = threadIdx.x >> 6;
+    const InstDesc& d = a.inst[0];                 // surrogate contexts hold one network
+
+    // what a pass reads of its cells (the first one's ahead of the weights)
+    struct Cell {
+        float ig, bias, vd, vs, va, ca;
+        int hold;
+        f32x4 x;               // the lane's feature group
+    };
+    auto load_cell = [&](int64_t pass) {
+        const int64_t c = min(pass + wave * 16 + (l & 15), n_cells_total - 1);
+        Cell q;
+        q.ig = s.igap[c];
+        q.bias = a.bias[c];
+        q.vd = xin[SV_VD * a.stride + c];
+        q.vs = xin[SV_VS * a.stride + c];
+        q.va = xin[SV_VA * a.stride + c];
+        q.ca = xin[SV_CA * a.stride + c];
+        q.hold = s.hold[c];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q.x[e] = 4 * g + e < NSV ? xin[(4 * g + e) * a.stride + c] : 0.0f;
+        return q;
+    };
+    Cell q = load_cell((int64_t)blockIdx.x * CELLS);
+    load_weights_lds(s.wb, sm);
+    if (threadIdx.x == 0) s_count = 0;
+    if (threadIdx.x < 4) s_sum[threadIdx.x] = 0;
+    __syncthreads();
+
+    auto plain_phase = [&]() {                     // s_count cells, after a barrier; ends with one
+        const int count = s_count;
+        const int pair = wave >> 1, part = wave & 1;
+        const bool act = pair * 64 + l < count;
+        PlainEntry e{0, 0, 0.0f, 0.0f, 0.0f};
+        if (act) e = s_list[pair * 64 + l];
+        const int64_t c = e.cell;                  // cell 0 for idle lanes: read, never written
+        const int li = (int)(c - d.cell_off);
+        const float ig = s.igap[c], bias = a.bias[c];
+        const int hold = s.hold[c];
+        float x[NSV], y[NSV];
+#pragma unroll
+        for (int v = 0; v < NSV; ++v) x[v] = xin[v * a.stride + c];
+        int cnt = part == 0 ? a.spike_count[c] : 0;
+        for (int k = 0; k < kMacro; ++k) {
+            const int64_t st = step0 + k;
+            if (part == 0) {
+                cell_step_dendrite(d.p, x, ig, evoked_from(bias, a, d, st, li), a.dt, y);
+                cell_step_axon(d.p, x, a.dt, y);
+                if (x[SV_VA] < 0.0f && y[SV_VA] >= 0.0f) {
+                    if (act && a.spike_cap > 0) {
+                        const float frac = (0.0f - x[SV_VA]) / (y[SV_VA] - x[SV_VA]);
+                        a.spike_times[c * a.spike_cap + (cnt % a.spike_cap)] = ((float)st + frac) * a.dt;
+                    }
+                    ++cnt;
+                }
+#pragma unroll
+                for (int v : {SV_VD, SV_CA, SV_R, SV_S, SV_Q, SV_VA, SV_HA, SV_XA}) x[v] = y[v];
+                s_x[pair][k & 1][0][l] = y[SV_VD];
+                s_x[pair][k & 1][2][l] = y[SV_VA];
+            } else {
+                cell_step_soma(d.p, x, a.dt, y);
+#pragma unroll
+                for (int v : {SV_VS, SV_K, SV_L, SV_H, SV_N, SV_X}) x[v] = y[v];
+                s_x[pair][k & 1][1][l] = y[SV_VS];
+            }
+            // one barrier per step: buffer k & 1 is rewritten two steps later,
+            // after every thread has passed the next barrier
+            __syncthreads();
+            x[SV_VD] = s_x[pair][k & 1][0][l];
+            x[SV_VS] = s_x[pair][k & 1][1][l];
+            x[SV_VA] = s_x[pair][k & 1][2][l];
+        }
+        bool flagged = false;
+        if (act) {
+            float chk = 0.0f;
+            if (part == 0) {
+                a.spike_count[c] = cnt;
+#pragma unroll
+                for (int v : {SV_VD, SV_CA, SV_R, SV_S, SV_Q, SV_VA, SV_HA, SV_XA}) {
+                    xout[v * a.stride + c] = x[v];
+                    chk += x[v];
+                }
+                int new_hold = hold > 0 ? hold - 1 : 0;
+                if (e.check) {
+                    const float dev =
+                        fmaxf(fabsf(e.vd - x[SV_VD]), fmaxf(fabsf(e.vs - x[SV_VS]), fabsf(e.va - x[SV_VA])));
+                    if (!(dev <= s.theta_mv)) {
+                        new_hold = s.hold_steps;
+                        flagged = true;
+                    }
+                }
+                if (new_hold != hold) s.hold[c] = new_hold;
+            } else {
+#pragma unroll
+                for (int v : {SV_VS, SV_K, SV_L, SV_H, SV_N, SV_X}) {
+                    xout[v * a.stride + c] = x[v];
+                    chk += x[v];
+                }
+            }
+            if (!isfinite(chk)) atomicOr(a.flags, 1);
+        }
+        const int n_flag = __popcll(__ballot(flagged)), n_check = __popcll(__ballot(act && part == 0 && e.check));
+        if (l == 0 && part == 0) {
+            if (n_check) atomicAdd(&s_sum[1], n_check);
+            if (n_flag) atomicAdd(&s_sum[2], n_flag);
+            if (pair == 0) s_sum[0] += count;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) s_count = 0;
+        __syncthreads();
+    };
+
+    for (int64_t pass = (int64_t)blockIdx.x * CELLS; pass < n_cells_total;
+         pass += (int64_t)gridDim.x * CELLS) {
+        const int64_t cell = pass + wave * 16 + (l & 15);
         const bool live = cell < n_cells_total;
         const int64_t c = live ? cell : n_cells_total - 1;
-        const InstDesc& d = a.inst[0];      // surrogate contexts hold one network
         const int li = (int)(c - d.cell_off);
-        const float ig = s.igap[c];
-        const float ia0 = evoked_input(a, d, step0, li, c);
+        if (pass != (int64_t)blockIdx.x * CELLS) q = load_cell(pass);
+        const float ia0 = evoked_from(q.bias, a, d, step0, li);
 
         // reasons known before the MLP runs (the same on the cell's four lanes)
-        const float vd0 = xin[SV_VD * a.stride + c];
-        const float vs0 = xin[SV_VS * a.stride + c];
-        const float va0 = xin[SV_VA * a.stride + c];
-        const float ca0 = xin[SV_CA * a.stride + c];
-        const bool in_regime = fmaxf(vd0, fmaxf(vs0, va0)) <= s.v_max && ca0 <= s.ca_max;
-        const int hold = s.hold[c];
-        const bool check = s.sample_every > 0 &&
-                           ((c + s.macro_index) % s.sample_every) == 0;
+        const bool in_regime = fmaxf(q.vd, fmaxf(q.vs, q.va)) <= s.v_max && q.ca <= s.ca_max;
+        const bool check = s.sample_every > 0 && ((c + s.macro_index) % s.sample_every) == 0;
 
         // MLP on every lane (the matrix cores need the whole wave)
-        f32x4 y = {0.0f, 0.0f, 0.0f, 0.0f};
-        f32x4 xg;
+        const f32x4 xg = q.x;
+        f32x4 xnv;
+        bool far = false;       // a normalised input of this lane's group outside the bound
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int v = 4 * g + e;
-            xg[e] = v < NSV ? xin[v * a.stride + c] : 0.0f;
+            const float raw = v < NSV ? xg[e] : (v == 14 ? q.ig : ia0);
+            xnv[e] = (raw - s.norm.in_mean[v]) * s.norm.in_rstd[v];
+            far = far || !(fabsf(xnv[e]) <= s.z_max);
         }
-        bool far = false;       // a normalised input of this lane's group outside the bound
-        if (s.mode == 0) {
-            f32x4 xnv;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int v = 4 * g + e;
-                const float raw = v < NSV ? xg[e] : (v == 14 ? ig : ia0);
-                xnv[e] = (raw - s.norm.in_mean[v]) * s.norm.in_rstd[v];
-                far = far || !(fabsf(xnv[e]) <= s.z_max);
-            }
-            if (!(s.z_max > 0.0f)) far = false;
-            y = mlp_forward(sm, s.params, pack_bf16(xnv), nullptr, nullptr);
-        }
+        if (!(s.z_max > 0.0f)) far = false;
+        const f32x4 y = mlp_forward(sm, s.params, pack_bf16(xnv), nullptr, nullptr);
         const bool cell_far = ((__ballot(far) >> (l & 15)) & kCellLanes) != 0;
         // MLP candidate: x + denormalised increment (lane holds 4 variables)
         f32x4 xm;
@@ -139,144 +252,45 @@ static __global__ __launch_bounds__(256) void k_surrogate_step(StepArgs a, SurrA
         const bool cand_bad = !(fabsf(mvd) <= kMlpVoltageBound && fabsf(mvs) <= kMlpVoltageBound &&
                                 fabsf(mva) <= kMlpVoltageBound) ||
                               fmaxf(mvd, fmaxf(mvs, mva)) > s.v_max;
-        const bool guard = s.mode == 0 && (!in_regime || cell_far || cand_bad);
-        const bool plain = s.mode == 1 || hold > 0 || check || guard;
-
-        // guarded cells counted with one atomic per wave that has any
+        const bool guard = !in_regime || cell_far || cand_bad;
+        const bool plain = q.hold > 0 || check || guard;
         const bool lead = g == 0 && live;
-        const unsigned long long n_guard = __popcll(__ballot(lead && guard));
-
-        if (!plain) {
-            if (live)
+        if (!plain && live) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int v = 4 * g + e;
-                    if (v < NSV) xout[v * a.stride + c] = xm[e];
-                }
+            for (int e = 0; e < 4; ++e) {
+                const int v = 4 * g + e;
+                if (v < NSV) xout[v * a.stride + c] = xm[e];
+            }
             // spike of an MLP cell: Va crossing 0 mV within the macro step
-            if (g == 0 && live) {
-                if (va0 < 0.0f && mva >= 0.0f) {
-                    const int cnt = a.spike_count[c];
-                    if (a.spike_cap > 0) {
-                        const float frac = (0.0f - va0) / (mva - va0);
-                        a.spike_times[c * a.spike_cap + (cnt % a.spike_cap)] =
-                            ((float)step0 + kMacro * frac) * a.dt;
-                    }
-                    a.spike_count[c] = cnt + 1;
+            if (g == 0 && q.va < 0.0f && mva >= 0.0f) {
+                const int cnt = a.spike_count[c];
+                if (a.spike_cap > 0) {
+                    const float frac = (0.0f - q.va) / (mva - q.va);
+                    a.spike_times[c * a.spike_cap + (cnt % a.spike_cap)] = ((float)step0 + kMacro * frac) * a.dt;
                 }
+                a.spike_count[c] = cnt + 1;
             }
         }
-        // cells for the plain method: a checked cell at its own slot (no
-        // atomic); the others appended after the checked ones, one atomic per
-        // wave that has any
-        if (lead && plain && check)
-            s.list[(int32_t)(c - s.check_first) / s.sample_every] = PlainEntry{(int32_t)c, mvd, mvs, mva};
-        const unsigned long long pmask = __ballot(lead && plain && !check);
+        const int n_guard = __popcll(__ballot(lead && guard));
+        if (l == 0 && n_guard) atomicAdd(&s_sum[3], n_guard);
+        const unsigned long long pmask = __ballot(lead && plain);
         if (pmask) {
-            unsigned int base = 0;
-            if (l == 0) base = atomicAdd(s.list_count, (unsigned int)__popcll(pmask));
+            int base = 0;
+            if (l == 0) base = atomicAdd(&s_count, (int)__popcll(pmask));
             base = __shfl(base, 0, 64);
-            if (lead && plain && !check) {
-                const unsigned int pos = base + (unsigned int)__popcll(pmask & ((1ull << l) - 1ull));
-                s.list[s.n_checks + pos] = PlainEntry{(int32_t)c, mvd, mvs, mva};
-            }
+            if (lead && plain)
+                s_list[base + __popcll(pmask & ((1ull << l) - 1ull))] =
+                    PlainEntry{(int32_t)c, check ? 1 : 0, mvd, mvs, mva};
         }
-        if (l == 0 && n_guard) atomicAdd(&s.counters[3], n_guard);
+        __syncthreads();
+        const int listed = s_count;
+        __syncthreads();                           // (read by all before the next pass adds to it)
+        if (listed > PLAIN - CELLS) plain_phase();
     }
-}
-
-// The listed cells: four plain forward-Euler steps with the macro step's gap
-// current held, spike detection, and for checked cells the drift test
-// against the MLP candidate (past theta: hold_steps macro steps of plain
-// method). A workgroup of two waves takes 64 listed cells: wave 0 advances
-// their dendrite and axon, wave 1 their soma (cell_step's arithmetic, split
-// by compartment); the state is exchanged through LDS after every step.
-constexpr int kListBlock = 128;
-
-static __global__ __launch_bounds__(kListBlock) void k_plain_list(StepArgs a, SurrArgs s,
-                                                                  const float* __restrict__ xin,
-                                                                  float* __restrict__ xout, int64_t step0) {
-    __shared__ float s_x[2][NSV][64];
-    const int64_t count = s.n_checks + *s.list_count;   // checked cells first, then the appended
-    const InstDesc& d = a.inst[0];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        atomicAdd(&s.counters[0], (unsigned long long)count);
-        if (s.n_checks) atomicAdd(&s.counters[1], (unsigned long long)s.n_checks);
-    }
-    const int lane = threadIdx.x & 63;
-    const int part = threadIdx.x >> 6;        // 0: dendrite and axon, 1: soma
-    for (int64_t b = (int64_t)blockIdx.x * 64; b < count; b += (int64_t)gridDim.x * 64) {
-        const int64_t i = b + lane;
-        const bool act = i < count;
-        PlainEntry e{0, 0.0f, 0.0f, 0.0f};
-        if (act) e = s.list[i];
-        const int64_t c = e.cell;            // cell 0 for idle lanes: read, never written
-        const int li = (int)(c - d.cell_off);
-        const float ig = s.igap[c];
-        float x[NSV], y[NSV];
-#pragma unroll
-        for (int v = 0; v < NSV; ++v) x[v] = xin[v * a.stride + c];
-        int cnt = part == 0 ? a.spike_count[c] : 0;
-        for (int k = 0; k < kMacro; ++k) {
-            const int64_t st = step0 + k;
-            if (part == 0) {
-                cell_step_dendrite(d.p, x, ig, evoked_input(a, d, st, li, c), a.dt, y);
-                cell_step_axon(d.p, x, a.dt, y);
-                if (x[SV_VA] < 0.0f && y[SV_VA] >= 0.0f) {
-                    if (act && a.spike_cap > 0) {
-                        const float frac = (0.0f - x[SV_VA]) / (y[SV_VA] - x[SV_VA]);
-                        a.spike_times[c * a.spike_cap + (cnt % a.spike_cap)] = ((float)st + frac) * a.dt;
-                    }
-                    ++cnt;
-                }
-#pragma unroll
-                for (int v : {SV_VD, SV_CA, SV_R, SV_S, SV_Q, SV_VA, SV_HA, SV_XA}) s_x[k & 1][v][lane] = y[v];
-            } else {
-                cell_step_soma(d.p, x, a.dt, y);
-#pragma unroll
-                for (int v : {SV_VS, SV_K, SV_L, SV_H, SV_N, SV_X}) s_x[k & 1][v][lane] = y[v];
-            }
-            // one barrier per step: buffer k & 1 is rewritten two steps later,
-            // after every thread has passed the next barrier
-            __syncthreads();
-#pragma unroll
-            for (int v = 0; v < NSV; ++v) x[v] = s_x[k & 1][v][lane];
-        }
-        bool flagged = false;
-        if (act) {
-            float chk = 0.0f;
-            if (part == 0) {
-                a.spike_count[c] = cnt;
-#pragma unroll
-                for (int v : {SV_VD, SV_CA, SV_R, SV_S, SV_Q, SV_VA, SV_HA, SV_XA}) {
-                    xout[v * a.stride + c] = x[v];
-                    chk += x[v];
-                }
-            } else {
-#pragma unroll
-                for (int v : {SV_VS, SV_K, SV_L, SV_H, SV_N, SV_X}) {
-                    xout[v * a.stride + c] = x[v];
-                    chk += x[v];
-                }
-            }
-            if (!isfinite(chk)) atomicOr(a.flags, 1);
-            if (part == 0) {
-                const int hold = s.hold[c];
-                int new_hold = hold > 0 ? hold - 1 : 0;
-                if (i < s.n_checks) {
-                    const float dev =
-                        fmaxf(fabsf(e.vd - x[SV_VD]), fmaxf(fabsf(e.vs - x[SV_VS]), fabsf(e.va - x[SV_VA])));
-                    if (!(dev <= s.theta_mv)) {
-                        new_hold = s.hold_steps;
-                        flagged = true;
-                    }
-                }
-                if (new_hold != hold) s.hold[c] = new_hold;
-            }
-        }
-        const unsigned long long fm = __ballot(flagged);
-        if (lane == 0 && fm) atomicAdd(&s.counters[2], (unsigned long long)__popcll(fm));
-    }
+    __syncthreads();
+    if (s_count > 0) plain_phase();
+    if (threadIdx.x < 4 && s_sum[threadIdx.x])
+        atomicAdd(&s.counters[threadIdx.x], (unsigned long long)s_sum[threadIdx.x]);
 }
 
 // Four plain forward-Euler steps per cell with the macro step's gap current
