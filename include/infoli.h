@@ -488,9 +488,8 @@ infoli_status infoli_mlp_adam_step(float *params, float *m, float *v, const floa
  *   batch: a multiple of 16, at most 8192 (else INFOLI_E_INVALID_ARG, with
  *   the limit in the message). Host or other-device pointers:
  *   INFOLI_E_INVALID_ARG; nothing is queued on any error.
- * The call allocates nothing: its staging (bf16 weights, split-K partial
- * gradients, transposed activations; 10,284,800 bytes) is a static device
- * array that each GPU holds from the first call on it until the process
+ * The call allocates nothing: its staging (transposed activations, loss sums;
+ * 8,914,944 bytes) is a static device array that each GPU holds from the first call on it until the process
  * ends. Every call on one GPU uses that one array: calls whose queued work
  * overlaps on a GPU (two streams, two threads) race and give wrong results;
  * serialise them. Each call writes all the staging it reads, so nothing

@@ -133,14 +133,8 @@ __device__ __forceinline__ f32x4 bias4(const float* b, int ob) {
 }
 
 // Forward pass of one wave. bx: B operand X^T (features 4*(lane/16).. of
-// sample lane%16). Keeps pre-activations z for the backward pass when given.
-struct MlpActs {
-    f32x4 z1[8], z2[8];
-    bf16x4 h1[8], h2[8];
-};
-
-__device__ __forceinline__ f32x4 mlp_forward(MlpSmem s, const float* __restrict__ params, bf16x4 bx,
-                                             MlpActs* keep, bf16x4* h2_out) {
+// sample lane%16).
+__device__ __forceinline__ f32x4 mlp_forward(MlpSmem s, const float* __restrict__ params, bf16x4 bx) {
     bf16x4 h1[8];
 #pragma unroll
     for (int ob = 0; ob < 8; ++ob) {
@@ -149,10 +143,6 @@ __device__ __forceinline__ f32x4 mlp_forward(MlpSmem s, const float* __restrict_
 #pragma unroll
         for (int e = 0; e < 4; ++e) h[e] = silu_f(z[e]);
         h1[ob] = pack_bf16(h);
-        if (keep) {
-            keep->z1[ob] = z;
-            keep->h1[ob] = h1[ob];
-        }
     }
     bf16x4 h2[8];
 #pragma unroll
@@ -165,18 +155,11 @@ __device__ __forceinline__ f32x4 mlp_forward(MlpSmem s, const float* __restrict_
 #pragma unroll
         for (int e = 0; e < 4; ++e) h[e] = silu_f(z[e]);
         h2[ob] = pack_bf16(h);
-        if (keep) {
-            keep->z2[ob] = z;
-            keep->h2[ob] = h2[ob];
-        }
     }
     f32x4 y = bias4(params + kOffB3, 0);
 #pragma unroll
     for (int kb = 0; kb < 8; kb += 2)
         y = mfma32(a_rows(s.w3, kS3, 0, kb), a_rows(s.w3, kS3, 0, kb + 1), h2[kb], h2[kb + 1], y);
-    if (h2_out)
-#pragma unroll
-        for (int kb = 0; kb < 8; ++kb) h2_out[kb] = h2[kb];
     return y;   // lane holds outputs 4*(lane/16)..+3 of sample lane%16
 }
 
@@ -187,16 +170,18 @@ static __global__ void k_mlp_to_bf16(const float* __restrict__ params, uint16_t*
 }
 
 // ---------------------------------------------------------------- training
-// Transposed activation buffers written by the forward/backward pass, read by
-// the weight-gradient GEMMs: [feature][batch] bf16.
+// Transposed activations written by the forward/backward pass, read by the
+// weight-gradient products: tiles of 16 features x 16 samples (512 contiguous
+// bytes, sample fastest), a feature block's tiles in sample order, so that a
+// wave of either kernel moves whole tiles.
 struct TrainBufs {
-    uint16_t* xT;     // [16][B]
-    uint16_t* h1T;    // [128][B]
-    uint16_t* h2T;    // [128][B]
-    uint16_t* dyT;    // [16][B]
-    uint16_t* dz2T;   // [128][B]
-    uint16_t* dz1T;   // [128][B]
-    float* loss_part; // [B/16] per-wave sums of squared errors
+    uint16_t* xT;     // [1][B/16][16][16]
+    uint16_t* h1T;    // [8][B/16][16][16]
+    uint16_t* h2T;    // [8]
+    uint16_t* dyT;    // [1]
+    uint16_t* dz2T;   // [8]
+    uint16_t* dz1T;   // [8]
+    float* loss_part; // [B/16] sums of squared errors of 16 samples
 };
 
 // Counter-based index draw: SplitMix64 finaliser (Steele, Lea, Flood 2014)
@@ -208,145 +193,239 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
     return z ^ (z >> 31);
 }
 
-// One wave per 16 samples: forward, loss, and back-propagation down to dz1.
+// Forward, loss and back-propagation down to dz1, 16 samples at a time: the
+// workgroup's eight waves take one block of 16 hidden features each, of every
+// layer and both directions, and pass the activations on through LDS. The
+// weights come from the fp32 masters, through LDS once; a wave keeps the
+// operands of its feature block in registers for all its samples.
 // Sample p of the batch is row idx(p) of the normalised data set (xn, tn:
 // [N][16] fp32); idx(p) = p when seed == 0, else a hashed draw.
-static __global__ __launch_bounds__(256) void k_mlp_fwd_bwd(const float* __restrict__ params,
-                                                     const uint16_t* __restrict__ wb,
-                                                     const float* __restrict__ xn,
-                                                     const float* __restrict__ tn, int64_t n_data,
-                                                     int batch, uint64_t seed, uint64_t step,
-                                                     TrainBufs buf) {
+//
+// Bound by latency: one read of the weights (82 KB from L2) and five dependent
+// products. A wave that took 16 samples alone through all blocks left 3/4 of
+// the waves' slots empty at a batch of 4,096 and needed the masters rounded by
+// a kernel before (together 15.3 us; now 7.5).
+constexpr int kFwdBwdBlock = 64 * (kHid / 16);
+
+static __global__ __launch_bounds__(kFwdBwdBlock, 2) void k_mlp_fwd_bwd(const float* __restrict__ params,
+                                                                 const float* __restrict__ xn,
+                                                                 const float* __restrict__ tn, int64_t n_data,
+                                                                 int batch, uint64_t seed, uint64_t step,
+                                                                 TrainBufs buf) {
     __shared__ __align__(16) uint16_t s_w[kMlpLdsElems];
+    __shared__ bf16x4 s_h1[8][64], s_h2[8][64], s_dz2[8][64];   // B operands by feature block
     const MlpSmem s = mlp_smem(s_w);
-    load_weights_lds(wb, s);
-    __syncthreads();
     const int l = threadIdx.x & 63;
     const int g = l >> 4;                       // feature group of this lane
-    const int wave_g = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int p = wave_g * 16 + (l & 15);       // position in the batch
-    if (wave_g * 16 >= batch) return;           // whole waves only (batch % 16 == 0)
-    const int64_t row = seed ? (int64_t)(mix64(seed ^ (step << 32) ^ (uint64_t)p) % (uint64_t)n_data) : p;
+    const int w = threadIdx.x >> 6;             // feature block of this wave
+    const int nb = batch / 16;
 
-    const f32x4 xv = *reinterpret_cast<const f32x4*>(xn + row * 16 + 4 * g);
-    const f32x4 tv = *reinterpret_cast<const f32x4*>(tn + row * 16 + 4 * g);
-    const bf16x4 bx = pack_bf16(xv);
-    MlpActs act;
-    const f32x4 y = mlp_forward(s, params, bx, &act, nullptr);
-
-    // loss = mean over batch and the 14 targets of (y - t)^2
-    const float scale = 2.0f / (float)(batch * kTargets);
-    f32x4 dy;
-    float sq = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const bool on = 4 * g + e < kTargets;
-        const float d = on ? y[e] - tv[e] : 0.0f;
-        sq += d * d;
-        dy[e] = d * scale;
-    }
-    for (int m = 32; m > 0; m >>= 1) sq += __shfl_xor(sq, m, 64);
-    if (l == 0) buf.loss_part[wave_g] = sq;
-    const bf16x4 dyq = pack_bf16(dy);
-
-    // dz2 = (W3^T dy) * silu'(z2)
-    bf16x4 dz2q[8];
-#pragma unroll
-    for (int ib = 0; ib < 8; ++ib) {
-        f32x4 dh = mfma16(a_cols(s.w3, kS3, ib, 0), dyq, f32x4{0.0f, 0.0f, 0.0f, 0.0f});
-        f32x4 dz;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) dz[e] = dh[e] * silu_grad_f(act.z2[ib][e]);
-        dz2q[ib] = pack_bf16(dz);
-    }
-    // dz1 = (W2^T dz2) * silu'(z1)
-    bf16x4 dz1q[8];
-#pragma unroll
-    for (int ib = 0; ib < 8; ++ib) {
-        f32x4 dh = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int kb = 0; kb < 8; kb += 2)
-            dh = mfma32(a_cols(s.w2, kS2, ib, kb), a_cols(s.w2, kS2, ib, kb + 1), dz2q[kb], dz2q[kb + 1], dh);
-        f32x4 dz;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) dz[e] = dh[e] * silu_grad_f(act.z1[ib][e]);
-        dz1q[ib] = pack_bf16(dz);
-    }
-
-    // transposed stores: element (feature f, position p)
-    auto put = [&](uint16_t* dst, int fb, bf16x4 v) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) dst[(int64_t)(fb * 16 + 4 * g + e) * batch + p] = (uint16_t)v[e];
+    struct Sample {
+        f32x4 x, t;
     };
-    put(buf.xT, 0, bx);
-    put(buf.dyT, 0, dyq);
+    const auto load = [&](int sb) {
+        const int p = sb * 16 + (l & 15);       // position in the batch
+        const int64_t row = seed ? (int64_t)(mix64(seed ^ (step << 32) ^ (uint64_t)p) % (uint64_t)n_data) : p;
+        return Sample{*reinterpret_cast<const f32x4*>(xn + row * 16 + 4 * g),
+                      *reinterpret_cast<const f32x4*>(tn + row * 16 + 4 * g)};
+    };
+
+    // four weights per thread and access, all of them in flight
+    constexpr int kPer2 = kHid * kHid / 4 / kFwdBwdBlock;
+    static_assert(kHid * kIn / 4 == kFwdBwdBlock && kOut * kHid / 4 == kFwdBwdBlock, "one access per thread");
+    const f32x4* m1 = reinterpret_cast<const f32x4*>(params + kOffW1);
+    const f32x4* m2 = reinterpret_cast<const f32x4*>(params + kOffW2);
+    const f32x4* m3 = reinterpret_cast<const f32x4*>(params + kOffW3);
+    f32x4 v2[kPer2];
+    const f32x4 v1 = m1[threadIdx.x], v3 = m3[threadIdx.x];
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        put(buf.h1T, b, act.h1[b]);
-        put(buf.h2T, b, act.h2[b]);
-        put(buf.dz2T, b, dz2q[b]);
-        put(buf.dz1T, b, dz1q[b]);
+    for (int u = 0; u < kPer2; ++u) v2[u] = m2[threadIdx.x + u * kFwdBwdBlock];
+    Sample cur = load(min((int)blockIdx.x, nb - 1));
+    const f32x4 b1 = bias4(params + kOffB1, w), b2 = bias4(params + kOffB2, w), b3 = bias4(params + kOffB3, 0);
+    const auto put_w = [&](uint16_t* dst, int S, int cols, int e, f32x4 v) {
+        *reinterpret_cast<bf16x4*>(dst + (e / (cols / 4)) * S + 4 * (e % (cols / 4))) = pack_bf16(v);
+    };
+    put_w(s.w1, kS1, kIn, threadIdx.x, v1);
+    put_w(s.w3, kS3, kHid, threadIdx.x, v3);
+#pragma unroll
+    for (int u = 0; u < kPer2; ++u) put_w(s.w2, kS2, kHid, threadIdx.x + u * kFwdBwdBlock, v2[u]);
+    __syncthreads();
+
+    const bf16x4 w1r = a_rows(s.w1, kS1, w, 0), w3c = a_cols(s.w3, kS3, w, 0);
+    bf16x4 w2r[8], w2c[8], w3r[8];
+#pragma unroll
+    for (int kb = 0; kb < 8; ++kb) {
+        w2r[kb] = a_rows(s.w2, kS2, w, kb);
+        w3r[kb] = a_rows(s.w3, kS3, 0, kb);
+        w2c[kb] = a_cols(s.w2, kS2, w, kb);
+    }
+    const float scale = 2.0f / (float)(batch * kTargets);
+
+    // An exchange buffer is written again one barrier or more after every wave
+    // has read it: its readers pass the next buffer's barrier first.
+    for (int sb = blockIdx.x; sb < nb; sb += gridDim.x) {
+        const auto put = [&](uint16_t* dst, int fb, bf16x4 v) {
+            uint16_t* tile = dst + ((int64_t)fb * nb + sb) * 256 + 64 * g + (l & 15);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tile[16 * e] = (uint16_t)v[e];
+        };
+        const f32x4 tv = cur.t;
+        const bf16x4 bx = pack_bf16(cur.x);
+        if (sb + (int)gridDim.x < nb) cur = load(sb + gridDim.x);
+
+        const f32x4 z1 = mfma16(w1r, bx, b1);
+        f32x4 h;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = silu_f(z1[e]);
+        const bf16x4 h1 = pack_bf16(h);
+        s_h1[w][l] = h1;
+        __syncthreads();
+
+        f32x4 z2 = b2;
+#pragma unroll
+        for (int kb = 0; kb < 8; kb += 2) z2 = mfma32(w2r[kb], w2r[kb + 1], s_h1[kb][l], s_h1[kb + 1][l], z2);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = silu_f(z2[e]);
+        const bf16x4 h2 = pack_bf16(h);
+        s_h2[w][l] = h2;
+        put(buf.h1T, w, h1);
+        __syncthreads();
+
+        // every wave the outputs: each needs their errors
+        f32x4 y = b3;
+#pragma unroll
+        for (int kb = 0; kb < 8; kb += 2) y = mfma32(w3r[kb], w3r[kb + 1], s_h2[kb][l], s_h2[kb + 1][l], y);
+        // loss = mean over batch and the 14 targets of (y - t)^2
+        f32x4 dy;
+        float sq = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool on = 4 * g + e < kTargets;
+            const float d = on ? y[e] - tv[e] : 0.0f;
+            sq += d * d;
+            dy[e] = d * scale;
+        }
+        const bf16x4 dyq = pack_bf16(dy);
+
+        // dz2 = (W3^T dy) * silu'(z2)
+        const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+        f32x4 dh = mfma16(w3c, dyq, zero), dz;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dz[e] = dh[e] * silu_grad_f(z2[e]);
+        const bf16x4 dz2 = pack_bf16(dz);
+        s_dz2[w][l] = dz2;
+        put(buf.h2T, w, h2);
+        __syncthreads();
+
+        // dz1 = (W2^T dz2) * silu'(z1)
+        dh = zero;
+#pragma unroll
+        for (int kb = 0; kb < 8; kb += 2) dh = mfma32(w2c[kb], w2c[kb + 1], s_dz2[kb][l], s_dz2[kb + 1][l], dh);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dz[e] = dh[e] * silu_grad_f(z1[e]);
+        put(buf.dz2T, w, dz2);
+        put(buf.dz1T, w, pack_bf16(dz));
+        if (w == 0) {
+            put(buf.xT, 0, bx);
+            for (int m = 32; m > 0; m >>= 1) sq += __shfl_xor(sq, m, 64);
+            if (l == 0) buf.loss_part[sb] = sq;
+        }
+        if (w == 1) put(buf.dyT, 0, dyq);
     }
 }
 
-// Weight and bias gradients as GEMMs over the batch: one wave per 16x16
-// output tile and slice of the batch (split K), each slice summed in order
-// into its own partial gradient [kGradSplits][kNumParams]; the partials are
-// added in slice order afterwards (deterministic). Tiles: dW1 8, dW2 64,
-// dW3 8, then bias rows as products with a ones vector: db1 8, db2 8, db3 1.
-constexpr int kGradTiles = 8 + 64 + 8 + 8 + 8 + 1;
-constexpr int kGradSplits = 16;
+// Weight and bias gradients as products over the batch: one workgroup per
+// 16x16 output tile (dW1 8, dW2 64, dW3 8), its sixteen waves a slice of the
+// batch each (split K), whose sums it adds in slice order through LDS
+// (deterministic). The workgroups of a bias row's first tile sum it as well, as
+// a product with a ones vector. `splits` such workgroups per tile share a
+// large batch; each then writes a partial gradient [splits][kNumParams], and
+// the workgroups of a split are neighbours modulo eight, so that one XCD's L2
+// holds its part of the activations for all tiles.
+//
+// Bound by what the XCDs read of the activations that others wrote (4,096
+// samples: 1.6 MB each). The slices as workgroups of one wave, their partials
+// added by a kernel of its own, took 13.7 us there (now 6.0), and 57 us at
+// 32,768 (now 19).
+constexpr int kGradTiles = 8 + 64 + 8;
+constexpr int kGradWaves = 16;
+constexpr int kGradLoads = 8;        // tiles of each operand in flight per wave
 
-static __global__ __launch_bounds__(64) void k_mlp_wgrad(TrainBufs buf, int batch, float* __restrict__ grad_part,
-                                                  float* __restrict__ loss_out) {
-    const int t = blockIdx.x % kGradTiles;
-    const int split = blockIdx.x / kGradTiles;
+static __global__ __launch_bounds__(64 * kGradWaves, 8) void k_mlp_wgrad(TrainBufs buf, int batch, int splits,
+                                                               float* __restrict__ grad_part,
+                                                               float* __restrict__ loss_out) {
+    __shared__ f32x4 s_acc[kGradWaves][64];
+    __shared__ float s_bias[kGradWaves][16];
+    const int t = blockIdx.x / splits;
+    const int split = blockIdx.x % splits;
     float* grad = grad_part + (int64_t)split * kNumParams;
     const int l = threadIdx.x & 63;
     const int g = l >> 4;
-    const uint16_t* A;   // [rows][batch]
-    const uint16_t* Bm;  // [cols][batch] or nullptr for the ones vector
-    int ib, jb, ncols, off;
+    const int w = threadIdx.x >> 6;
+    const int nb = batch / 16;
+    const uint16_t *A, *Bm;      // feature blocks of [B/16] tiles
+    int ib, jb, ncols, off, off_b;
     if (t < 8) {                 // dW1 = dz1^T x : [128][16]
-        A = buf.dz1T; Bm = buf.xT; ib = t; jb = 0; ncols = kIn; off = kOffW1;
+        A = buf.dz1T; Bm = buf.xT; ib = t; jb = 0; ncols = kIn; off = kOffW1; off_b = kOffB1;
     } else if (t < 72) {         // dW2 = dz2^T h1 : [128][128]
-        A = buf.dz2T; Bm = buf.h1T; ib = (t - 8) / 8; jb = (t - 8) % 8; ncols = kHid; off = kOffW2;
-    } else if (t < 80) {         // dW3 = dy^T h2 : [16][128]
-        A = buf.dyT; Bm = buf.h2T; ib = 0; jb = t - 72; ncols = kHid; off = kOffW3;
-    } else if (t < 88) {         // db1
-        A = buf.dz1T; Bm = nullptr; ib = t - 80; jb = 0; ncols = 1; off = kOffB1;
-    } else if (t < 96) {         // db2
-        A = buf.dz2T; Bm = nullptr; ib = t - 88; jb = 0; ncols = 1; off = kOffB2;
-    } else {                     // db3
-        A = buf.dyT; Bm = nullptr; ib = 0; jb = 0; ncols = 1; off = kOffB3;
+        A = buf.dz2T; Bm = buf.h1T; ib = (t - 8) / 8; jb = (t - 8) % 8; ncols = kHid; off = kOffW2; off_b = kOffB2;
+    } else {                     // dW3 = dy^T h2 : [16][128]
+        A = buf.dyT; Bm = buf.h2T; ib = 0; jb = t - 72; ncols = kHid; off = kOffW3; off_b = kOffB3;
     }
+    const bool bias = jb == 0;
     const bf16x4 ones = {(short)0x3f80, (short)0x3f80, (short)0x3f80, (short)0x3f80};
-    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    const uint16_t* arow = A + (int64_t)(ib * 16 + (l & 15)) * batch + 4 * g;
-    const uint16_t* brow = Bm ? Bm + (int64_t)(jb * 16 + (l & 15)) * batch + 4 * g : nullptr;
-    const int kb = batch / 16;
-    const int k0 = (int)((int64_t)split * kb / kGradSplits), k1 = (int)((int64_t)(split + 1) * kb / kGradSplits);
-    for (int k = 16 * k0; k < 16 * k1; k += 16) {
-        const bf16x4 av = *reinterpret_cast<const bf16x4*>(arow + k);
-        const bf16x4 bv = Bm ? *reinterpret_cast<const bf16x4*>(brow + k) : ones;
-        acc = mfma16(av, bv, acc);
-    }
-    // lane holds rows ib*16 + 4g + e, column jb*16 + l%16
-    if (ncols == 1) {
-        if ((l & 15) == 0)
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f}, accb = acc;
+    const uint16_t* at = A + (int64_t)ib * nb * 256 + (l & 15) * 16 + 4 * g;
+    const uint16_t* bt = Bm + (int64_t)jb * nb * 256 + (l & 15) * 16 + 4 * g;
+    const int64_t slices = (int64_t)splits * kGradWaves, slice = split * kGradWaves + w;
+    const int k0 = (int)(slice * nb / slices), k1 = (int)((slice + 1) * nb / slices);
+    for (int k = k0; k < k1; k += kGradLoads) {
+        bf16x4 av[kGradLoads], bv[kGradLoads];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) grad[off + ib * 16 + 4 * g + e] = acc[e];
-    } else {
+        for (int u = 0; u < kGradLoads; ++u) {
+            const int64_t kk = min(k + u, k1 - 1);
+            av[u] = *reinterpret_cast<const bf16x4*>(at + kk * 256);
+            bv[u] = *reinterpret_cast<const bf16x4*>(bt + kk * 256);
+        }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) grad[off + (ib * 16 + 4 * g + e) * ncols + jb * 16 + (l & 15)] = acc[e];
+        for (int u = 0; u < kGradLoads; ++u)
+            if (k + u < k1) {
+                acc = mfma16(av[u], bv[u], acc);
+                if (bias) accb = mfma16(av[u], ones, accb);
+            }
     }
-    if (t == 0 && split == 0 && loss_out) {   // whole wave: strided partial sums, fixed butterfly
-        float s = 0.0f;
-        for (int w = l; w < batch / 16; w += 64) s += buf.loss_part[w];
-        for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
-        if (l == 0) *loss_out = s / (float)(batch * kTargets);
+    // lane holds rows 4g + e of column l%16; the bias product has equal columns
+    s_acc[w][l] = acc;
+    if (bias && (l & 15) == 0)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s_bias[w][4 * g + e] = accb[e];
+    __syncthreads();
+    const int e = threadIdx.x;
+    if (e < 256) {
+        const int i = e >> 4, j = e & 15;
+        float sum = s_acc[0][j + 16 * (i >> 2)][i & 3];
+#pragma unroll
+        for (int k = 1; k < kGradWaves; ++k) sum += s_acc[k][j + 16 * (i >> 2)][i & 3];
+        grad[off + (ib * 16 + i) * ncols + jb * 16 + j] = sum;
+    } else if (bias && e < 256 + 16) {
+        float sum = s_bias[0][e - 256];
+        for (int k = 1; k < kGradWaves; ++k) sum += s_bias[k][e - 256];
+        grad[off_b + ib * 16 + e - 256] = sum;
+    } else if (w == kGradWaves - 1 && blockIdx.x == (unsigned)splits && loss_out) {
+        // whole wave: strided partial sums, fixed butterfly
+        float sum = 0.0f;
+        for (int k = l; k < nb; k += 64) sum += buf.loss_part[k];
+        for (int m = 32; m > 0; m >>= 1) sum += __shfl_xor(sum, m, 64);
+        if (l == 0) *loss_out = sum / (float)(batch * kTargets);
     }
 }
+
+// Workgroups per gradient tile: one each while another kernel that adds their
+// partials costs more (8,192 samples: 10.4 us, with eight 8.3 and 4.0 for the
+// sum), eight above (16,384: 20.5 us against 8.9 + 4.0, 32,768: 39.8 against
+// 14.9 + 4.0).
+constexpr int kGradSplits = 8;
+inline int grad_splits(int batch) { return batch >= 12288 ? kGradSplits : 1; }
 
 // Sum of the split-K partial gradients, in slice order.
 __device__ __forceinline__ float grad_sum(const float* __restrict__ part, int splits, int e) {
@@ -393,7 +472,7 @@ static __global__ __launch_bounds__(256) void k_mlp_forward(const float* __restr
     if (wave_g * 16 >= batch) return;
     const int p = wave_g * 16 + (l & 15);
     const f32x4 xv = *reinterpret_cast<const f32x4*>(x + (int64_t)p * 16 + 4 * g);
-    const f32x4 out = mlp_forward(s, params, pack_bf16(xv), nullptr, nullptr);
+    const f32x4 out = mlp_forward(s, params, pack_bf16(xv));
     *reinterpret_cast<f32x4*>(y + (int64_t)p * 16 + 4 * g) = out;
 }
 

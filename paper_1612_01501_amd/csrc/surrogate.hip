@@ -132,48 +132,54 @@ void launch_macro(infoli_ctx* c, hipStream_t st, const infoli_drift_cfg& dc, int
     else go(k_surrogate_step<256>, 256, 3 * (int64_t)c->n_cu);
 }
 
+// ---------------------------------------------------------------- gradient
+// Loss and gradient of one batch in two kernels; `grad` takes
+// grad_splits(batch) partials. Workgroups beyond one per compute unit
+// (their registers allow no second) would read the weights again, so they
+// loop (8,192 samples: 10.6 us, 12.0 with twice the workgroups).
+void launch_gradient(hipStream_t st, const float* params, const float* xn, const float* tn, int64_t n_data, int batch,
+                     uint64_t seed, uint64_t step, const TrainBufs& tb, float* grad, float* loss) {
+    constexpr int kMost = 256;
+    const int splits = grad_splits(batch);
+    hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3((unsigned)std::min(batch / 16, kMost)), dim3(kFwdBwdBlock), 0, st, params, xn,
+                       tn, n_data, batch, seed, step, tb);
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(kGradTiles * splits)), dim3(64 * kGradWaves), 0, st, tb, batch, splits,
+                       grad, loss);
+}
+
 // ---------------------------------------------------------------- staging without allocation
 // Largest batch of infoli_mlp_loss_grad_noalloc and the staging memory it
-// needs: the bf16 weights, the split-K partial gradients, the six transposed
-// activation buffers and the per-wave loss sums, each start 256-byte aligned.
+// needs: the six transposed activation buffers and the loss sums, each start
+// 256-byte aligned.
 constexpr int32_t kNoAllocMaxBatch = 8192;
 
 constexpr size_t round256(size_t b) { return (b + 255) & ~size_t(255); }
 
 constexpr size_t staging_bytes(int32_t batch) {
-    return round256(sizeof(uint16_t) * kNumParams) + round256(sizeof(float) * kNumParams * kGradSplits) +
-           2 * round256(sizeof(uint16_t) * 16 * (size_t)batch) + 4 * round256(sizeof(uint16_t) * kHid * (size_t)batch) +
+    return 2 * round256(sizeof(uint16_t) * 16 * (size_t)batch) + 4 * round256(sizeof(uint16_t) * kHid * (size_t)batch) +
            round256(sizeof(float) * (size_t)(batch / 16));
 }
 
-constexpr size_t kScratchBytes = staging_bytes(kNoAllocMaxBatch);     // 10,284,800 bytes
+constexpr size_t kScratchBytes = staging_bytes(kNoAllocMaxBatch);     // 8,914,944 bytes
 
 // Carves the staging buffers of one call out of `base` (device address).
-struct Staging {
-    uint16_t* wb;
-    float* part;
-    TrainBufs tb;
-};
-
-Staging carve(unsigned char* base, int32_t batch) {
+TrainBufs carve(unsigned char* base, int32_t batch) {
     size_t off = 0;
     auto take = [&](size_t bytes) {
         unsigned char* p = base + off;
         off += round256(bytes);
         return p;
     };
-    Staging st;
-    st.wb = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * kNumParams));
-    st.part = reinterpret_cast<float*>(take(sizeof(float) * kNumParams * kGradSplits));
-    st.tb.xT = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * 16 * (size_t)batch));
-    st.tb.dyT = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * 16 * (size_t)batch));
-    st.tb.h1T = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * kHid * (size_t)batch));
-    st.tb.h2T = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * kHid * (size_t)batch));
-    st.tb.dz2T = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * kHid * (size_t)batch));
-    st.tb.dz1T = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * kHid * (size_t)batch));
-    st.tb.loss_part = reinterpret_cast<float*>(take(sizeof(float) * (size_t)(batch / 16)));
+    TrainBufs tb;
+    tb.xT = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * 16 * (size_t)batch));
+    tb.dyT = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * 16 * (size_t)batch));
+    tb.h1T = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * kHid * (size_t)batch));
+    tb.h2T = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * kHid * (size_t)batch));
+    tb.dz2T = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * kHid * (size_t)batch));
+    tb.dz1T = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * kHid * (size_t)batch));
+    tb.loss_part = reinterpret_cast<float*>(take(sizeof(float) * (size_t)(batch / 16)));
     if (off != staging_bytes(batch) || off > kScratchBytes) fail(INFOLI_E_DEVICE, "staging layout mismatch");
-    return st;
+    return tb;
 }
 
 }  // namespace
@@ -370,17 +376,15 @@ infoli_status infoli_surrogate_train(infoli_ctx* ctx, const infoli_train_cfg* cf
         float* dloss = dev_alloc<float>(tmp.owned, (size_t)std::max(cfg->steps, 1));
         double c1 = 1.0, c2 = 1.0;
         for (int t = 1; t <= cfg->steps; ++t) {
-            hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3(B / 64), dim3(256), 0, st, s.params, s.wb, xd, td, n_data, B,
-                               cfg->seed | 1ull, (uint64_t)t, tb);
-            hipLaunchKernelGGL(k_mlp_wgrad, dim3(kGradTiles * kGradSplits), dim3(64), 0, st, tb, B, s.grad,
-                               dloss + (t - 1));
+            launch_gradient(st, s.params, xd, td, n_data, B, cfg->seed | 1ull, (uint64_t)t, tb, s.grad,
+                            dloss + (t - 1));
             c1 *= cfg->beta1;
             c2 *= cfg->beta2;
             // cosine decay of the learning rate from lr to lr_min
             const double frac = cfg->steps > 1 ? (double)(t - 1) / (double)(cfg->steps - 1) : 0.0;
             const float lr_t = (float)(cfg->lr_min + 0.5 * (cfg->lr - cfg->lr_min) * (1.0 + std::cos(M_PI * frac)));
             hipLaunchKernelGGL(k_adam, dim3((kNumParams + 255) / 256), dim3(256), 0, st, s.params, s.m, s.v, s.grad,
-                               kGradSplits, s.wb, lr_t, cfg->beta1, cfg->beta2, cfg->eps, (float)(1.0 - c1),
+                               grad_splits(B), s.wb, lr_t, cfg->beta1, cfg->beta2, cfg->eps, (float)(1.0 - c1),
                                (float)(1.0 - c2));
         }
         HIPX(hipGetLastError());
@@ -514,11 +518,11 @@ infoli_status infoli_mlp_loss_grad(const float* params, const float* x, const fl
         check_params(t, (int64_t)batch * 16);
         Scoped tmp;
         float* dp = dev_alloc<float>(tmp.owned, kNumParams);
-        uint16_t* dw = dev_alloc<uint16_t>(tmp.owned, kNumParams);
         float* dx = dev_alloc<float>(tmp.owned, (size_t)batch * 16);
         float* dt = dev_alloc<float>(tmp.owned, (size_t)batch * 16);
+        const int splits = grad_splits(batch);
         float* dg = dev_alloc<float>(tmp.owned, kNumParams);
-        float* dpart = dev_alloc<float>(tmp.owned, (size_t)kNumParams * kGradSplits);
+        float* dpart = splits > 1 ? dev_alloc<float>(tmp.owned, (size_t)kNumParams * splits) : dg;
         float* dl = dev_alloc<float>(tmp.owned, 1);
         TrainBufs tb;
         tb.xT = dev_alloc<uint16_t>(tmp.owned, (size_t)16 * batch);
@@ -531,11 +535,9 @@ infoli_status infoli_mlp_loss_grad(const float* params, const float* x, const fl
         HIPX(hipMemcpy(dp, params, sizeof(float) * kNumParams, hipMemcpyHostToDevice));
         HIPX(hipMemcpy(dx, x, sizeof(float) * batch * 16, hipMemcpyHostToDevice));
         HIPX(hipMemcpy(dt, t, sizeof(float) * batch * 16, hipMemcpyHostToDevice));
-        hipLaunchKernelGGL(k_mlp_to_bf16, dim3((kNumParams + 255) / 256), dim3(256), 0, 0, dp, dw);
-        hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3((batch + 63) / 64), dim3(256), 0, 0, dp, dw, dx, dt, (int64_t)batch,
-                           batch, 0ull, 0ull, tb);
-        hipLaunchKernelGGL(k_mlp_wgrad, dim3(kGradTiles * kGradSplits), dim3(64), 0, 0, tb, batch, dpart, dl);
-        hipLaunchKernelGGL(k_grad_reduce, dim3((kNumParams + 255) / 256), dim3(256), 0, 0, dpart, kGradSplits, dg);
+        launch_gradient(nullptr, dp, dx, dt, batch, batch, 0, 0, tb, dpart, dl);
+        if (splits > 1)
+            hipLaunchKernelGGL(k_grad_reduce, dim3((kNumParams + 255) / 256), dim3(256), 0, 0, dpart, splits, dg);
         HIPX(hipGetLastError());
         HIPX(hipDeviceSynchronize());
         HIPX(hipMemcpy(grad, dg, sizeof(float) * kNumParams, hipMemcpyDeviceToHost));
@@ -586,15 +588,9 @@ infoli_status infoli_mlp_loss_grad_noalloc(const float* d_params, const float* d
         check_device_ptr(d_t, dev, "t");
         check_device_ptr(d_grad, dev, "grad");
         if (d_loss) check_device_ptr(d_loss, dev, "loss");
-        const Staging sg = carve(scratch_on_current_device(), batch);
+        const TrainBufs tb = carve(scratch_on_current_device(), batch);
         const hipStream_t st = static_cast<hipStream_t>(stream);
-        hipLaunchKernelGGL(k_mlp_to_bf16, dim3((kNumParams + 255) / 256), dim3(256), 0, st, d_params, sg.wb);
-        hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3((batch + 63) / 64), dim3(256), 0, st, d_params, sg.wb, d_x, d_t,
-                           (int64_t)batch, batch, 0ull, 0ull, sg.tb);
-        hipLaunchKernelGGL(k_mlp_wgrad, dim3(kGradTiles * kGradSplits), dim3(64), 0, st, sg.tb, batch, sg.part,
-                           d_loss);
-        hipLaunchKernelGGL(k_grad_reduce, dim3((kNumParams + 255) / 256), dim3(256), 0, st, sg.part, kGradSplits,
-                           d_grad);
+        launch_gradient(st, d_params, d_x, d_t, batch, batch, 0, 0, tb, d_grad, d_loss);
         HIPX(hipGetLastError());
     });
 }

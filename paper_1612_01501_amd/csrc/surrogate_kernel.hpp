@@ -231,7 +231,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_surrogate_step(StepArgs a, SurrArg
             far = far || !(fabsf(xnv[e]) <= s.z_max);
         }
         if (!(s.z_max > 0.0f)) far = false;
-        const f32x4 y = mlp_forward(sm, s.params, pack_bf16(xnv), nullptr, nullptr);
+        const f32x4 y = mlp_forward(sm, s.params, pack_bf16(xnv));
         const bool cell_far = ((__ballot(far) >> (l & 15)) & kCellLanes) != 0;
         // MLP candidate: x + denormalised increment (lane holds 4 variables)
         f32x4 xm;
