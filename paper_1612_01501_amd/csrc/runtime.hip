@@ -9,6 +9,8 @@
 
 namespace infoli_rt {
 
+static_assert(kPersistPulses >= INFOLI_MAX_PULSES, "the persistent kernel holds a network's pulses in LDS");
+
 thread_local std::string g_thread_error;
 
 // Default cell parameters, in the order of INFOLI_NUM_PARAMS, of the
@@ -301,7 +303,7 @@ size_t flat_lds_floats(const infoli_ctx* c, int k, int rows) {
 // A network's chunked rows can run as flat tiles of `rows` rows.
 bool flat_ok(const infoli_ctx* c, int k, int rows) {
     const InstDesc& d = c->inst[k];
-    return d.conn == CONN_CSR && d.ca_off >= 0 && d.n <= kFlatCells && c->d_rtag &&
+    return !c->no_flat && d.conn == CONN_CSR && d.ca_off >= 0 && d.n <= kFlatCells && c->d_rtag &&
            flat_lds_floats(c, k, rows) * sizeof(float) + kStaticLds <= (size_t)c->lds_max;
 }
 
@@ -741,8 +743,9 @@ std::string tune_key(const infoli_ctx* c, const InstDesc& d, double deg) {
     const int nb = (int)std::ceil(std::log2((double)d.n) * 4.0);
     const int db = (int)std::ceil(std::log2(deg + 1.0) * 4.0);
     char buf[128];
-    snprintf(buf, sizeof buf, "gfx950 groups2 c16=%d w=%d bits=%d blk=%d n%d d%d%s", d.col16, d.has_w,
-             d.bits_off >= 0 ? 1 : 0, d.cb_off >= 0 ? c->blk_cols : 0, nb, db, d.sgj ? " sgj" : "");
+    snprintf(buf, sizeof buf, "gfx950 groups2 c16=%d w=%d bits=%d blk=%d n%d d%d%s%s", d.col16, d.has_w,
+             d.bits_off >= 0 ? 1 : 0, d.cb_off >= 0 ? c->blk_cols : 0, nb, db, d.sgj ? " sgj" : "",
+             c->no_flat ? " rows" : "");
     return buf;
 }
 
@@ -1755,6 +1758,86 @@ hipGraphExec_t get_graph(infoli_ctx* c, int parity) {
     return ex;
 }
 
+// GRAPH mode: both captured chunks (by starting buffer), so no step call pays
+// for capture.
+void make_graphs(infoli_ctx* c) {
+    if (c->opt.step_mode != INFOLI_MODE_GRAPH) return;
+    get_graph(c, 0);
+    get_graph(c, 1);
+}
+
+}  // namespace
+
+// Plans a surrogate's network without flat tiles (its rows summed by lane
+// groups), once, when the surrogate gets its weights. Its macro steps decide
+// per cell (guards, the drift test) on inputs rounded to BF16, so another order
+// of a row's sum, itself as good, can hand a cell to the other method: of 24
+// runs of 20 macro steps two had cells 0.5 and 2.2 mV elsewhere. Costs 5 us of
+// a macro step at 16,384 cells (24.5 -> 29.8 us), 2 at 6,000 (20.6 -> 22.6).
+void infoli_rt::leave_flat(infoli_ctx* c) {
+    if (c->no_flat) return;
+    bool flat = false;
+    for (const InstDesc& d : c->inst) flat = flat || (d.conn == CONN_CSR && d.flat);
+    if (!flat) {
+        c->no_flat = true;
+        return;
+    }
+    HIPX(hipStreamSynchronize(c->stream));
+    for (hipGraphExec_t& g : c->graph) {
+        if (g) (void)hipGraphExecDestroy(g);
+        g = nullptr;
+    }
+    const auto inst = c->inst;
+    const auto rows = c->rows_of;
+    const int blocks[2] = {c->grp[0].block, c->grp[1].block};
+    const int tuned = c->tuned, cached = c->tune_cached, mode = c->tune_mode;
+    const bool fork = c->fork_groups;
+    struct Events {        // the tuner's own: the last step's stay as they are
+        infoli_ctx* c;
+        hipEvent_t e0, e1;
+        explicit Events(infoli_ctx* c) : c(c), e0(c->ev0), e1(c->ev1) {
+            hipEvent_t a = nullptr, b = nullptr;
+            HIPX(hipEventCreate(&a));
+            if (const hipError_t e = hipEventCreate(&b); e != hipSuccess) {
+                (void)hipEventDestroy(a);
+                fail(INFOLI_E_DEVICE, "hipEventCreate: %s", hipGetErrorString(e));
+            }
+            c->ev0 = a;
+            c->ev1 = b;
+        }
+        ~Events() {
+            (void)hipEventDestroy(c->ev0);
+            (void)hipEventDestroy(c->ev1);
+            c->ev0 = e0;
+            c->ev1 = e1;
+        }
+    } events(c);
+    c->no_flat = true;
+    try {
+        if (c->opt.autotune && c->opt.csr_path == 0) {
+            c->tuned = c->tune_cached = 0;
+            c->tune_mode = -1;
+            autotune(c);
+        }
+    } catch (...) {      // the plan as it was
+        c->no_flat = false;
+        c->inst = inst;
+        c->rows_of = rows;
+        for (int g = 0; g < 2; ++g) c->grp[g].block = blocks[g];
+        c->tuned = tuned;
+        c->tune_cached = cached;
+        c->tune_mode = mode;
+        c->fork_groups = fork;
+        finalize_tiles(c);
+        throw;
+    }
+    finalize_tiles(c);
+    HIPX(hipStreamSynchronize(c->stream));
+    make_graphs(c);
+}
+
+namespace {
+
 void launch_persistent(infoli_ctx* c, int64_t n_steps, bool dry) {
     StepArgs a = make_args(c, false);
     a.dry = dry ? 1 : 0;
@@ -1885,12 +1968,7 @@ infoli_status infoli_batch_init(const infoli_network_spec* specs, int32_t n_inst
     }
     infoli_status st = guarded(nullptr, [&] {
         build_context(c, specs, n_instances, opt);
-        // GRAPH mode: both captured chunks (by starting buffer) are built and
-        // instantiated here, so no step call pays for capture
-        if (c->opt.step_mode == INFOLI_MODE_GRAPH) {
-            get_graph(c, 0);
-            get_graph(c, 1);
-        }
+        make_graphs(c);
     });
     if (st != INFOLI_OK) {
         c->release();

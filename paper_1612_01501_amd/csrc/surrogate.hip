@@ -120,8 +120,8 @@ void launch_macro(infoli_ctx* c, hipStream_t st, const infoli_drift_cfg& dc, int
     const SurrArgs s = surr_args(c, dc, step0 / kMacro);
     // Eight waves a workgroup share one copy of the weights and one plain phase,
     // from where four-wave workgroups would already stand on every compute unit
-    // (16,384 cells 22.9 -> 22.3 us per macro step with the gap kernel, 32,768
-    // cells 27.8 -> 25.7, 65,536 cells 38.0 -> 36.4); below, they would leave
+    // (per macro step with the gap kernel, 32,768 cells 27.8 -> 25.7 us, 65,536
+    // cells 38.0 -> 36.4; 16,384 cells 0.6 us faster); below, they would leave
     // compute units without work (2,000 cells: 20.3 us, 18.9 with four waves).
     const auto go = [&](auto kernel, int block, int64_t most) {
         const int64_t per = surr_cells(block);
@@ -301,6 +301,7 @@ infoli_status infoli_surrogate_train(infoli_ctx* ctx, const infoli_train_cfg* cf
         const int64_t n_data = per_traj * cfg->n_trajectories;
         if (n_data > (int64_t)1 << 28) fail(INFOLI_E_INVALID_ARG, "training set too large");
         ensure_surrogate_buffers(ctx);
+        leave_flat(ctx);
         SurrogateState& s = ctx->surr;
         hipStream_t st = ctx->stream;
         Scoped tmp(st);
@@ -429,6 +430,7 @@ infoli_status infoli_surrogate_set(infoli_ctx* ctx, const float* params, const f
         check_params(params, kNumParams);
         check_norm(norm);
         ensure_surrogate_buffers(ctx);
+        leave_flat(ctx);
         HIPX(hipStreamSynchronize(ctx->stream));
         upload_weights(ctx, params);
         std::memcpy(ctx->surr.norm, norm, sizeof(float) * 64);

@@ -76,9 +76,9 @@ constexpr int surr_plain(int block) { return block / 128 * 64; }   // cells of o
 // cells' steps: every wave with such a cell waited for an atomic on one address
 // (16,384 cells of which a fifth were held: 17.3 us, 8.8 without any), and the
 // listed cells' kernel took another 8.0 us for four steps of any number of
-// cells. A macro step with its gap kernel and a rotating sixteenth checked:
-// 16,384 cells 40.4 -> 24.2 us, 65,536 cells 74.9 -> 38.3, 2,000 cells 22.5 ->
-// 18.9. What is left is a chain: weights to LDS, the layers' matrix products
+// cells. A macro step with its gap kernel, 1/64 of the cells checked:
+// 16,384 cells 40.4 -> 30.6 us, 65,536 cells 74.9 -> 36.4, 1,500 cells 22.1 ->
+// 20.2. What is left is a chain: weights to LDS, the layers' matrix products
 // each on the one before, then four dependent cell steps.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK, 4) void k_surrogate_step(StepArgs a, SurrArgs s, const float* __restrict__ xin,

@@ -46,3 +46,28 @@ def test_every_cell_checked_equals_the_held_gap_step(infoli, n):
     # there, and stood still (to the scaled output) in the other two
     moved = np.abs(got[3][1].astype(np.float64) - x0[1])
     assert np.all(np.isfinite(got[3])) and moved.max() > 0
+
+
+@pytest.mark.parametrize("n,mode", [(100, "auto"), (3000, "launch"), (3000, "graph"), (9001, "graph"), (20000, "launch")])
+def test_weights_replan_the_rows_and_nothing_else(infoli, n, mode):
+    """Setting the weights may plan a CSR network's rows anew: the state and
+    the step count stay, steps go on from there, and the
+    rows' currents are the same sums (400 fp32 terms of up to 20 mV in another
+    order: 400 x 2^-24 x 20 mV of each weight, ten steps of 0.05 ms)."""
+    row_ptr, col = I.erdos_renyi_csr(n, min(0.3, 400.0 / n), 5)
+    g = 0.04 / 400
+    net = I.Network(n=n, conn="csr", row_ptr=row_ptr, col=col, g=g, bias=I.input_bias(n, 3), jitter=I.voltage_jitter(n, 4, 5.0))
+    out = {}
+    for weights in (False, True):
+        sim = infoli.Simulator(net, init_states=[infoli.initial_state(net)], step_mode=mode, graph_chunk=2)
+        sim.step(5)
+        before = sim.read_state(0)
+        if weights:
+            sim.surrogate_set(I.mlp_init_params(7), still_norm())
+            np.testing.assert_array_equal(sim.read_state(0), before)
+            assert sim.last_step_ms() > 0 and sim.info()["step"] == 5
+        sim.step(10)
+        out[weights] = sim.read_state(0)
+        sim.close()
+    assert np.all(np.isfinite(out[True]))
+    assert np.abs(out[True] - out[False]).max() <= 1e-3
