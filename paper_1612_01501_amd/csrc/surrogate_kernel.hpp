@@ -78,7 +78,9 @@ constexpr int surr_plain(int block) { return block / 128 * 64; }   // cells of o
 // listed cells' kernel took another 8.0 us for four steps of any number of
 // cells. A macro step with its gap kernel, 1/64 of the cells checked:
 // 16,384 cells 40.4 -> 30.6 us, 65,536 cells 74.9 -> 36.4, 1,500 cells 22.1 ->
-// 20.2. What is left is a chain: weights to LDS, the layers' matrix products
+// 20.2; where hardly a cell is listed the launch saved and the chain of cell
+// steps in every workgroup cancel (65,536 cells of degree 1,000, none held: 54.3
+// -> 55.1). What is left is a chain: weights to LDS, the layers' matrix products
 // each on the one before, then four dependent cell steps.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK, 4) void k_surrogate_step(StepArgs a, SurrArgs s, const float* __restrict__ xin,
