@@ -887,6 +887,11 @@ constexpr int kFlatCells = 32768;       // networks up to this size (128 KB of V
 
 __host__ __device__ constexpr int flat_vd_floats(int n) { return (n + 3) & ~3; }
 
+// Chunk that slot k of a tile of m chunks loads: its own, past the last one the
+// last again. None (-1) in a tile whose rows have no connections: its first
+// chunk may be one past the last of the arrays.
+__host__ __device__ constexpr int flat_load(int k, int m) { return m <= 0 ? -1 : k < m ? k : m - 1; }
+
 template <int BLOCK, bool HASW, bool SGJ, bool VD0>
 __device__ __forceinline__ void gap_flat(const StepArgs& a, const InstDesc& d, const Tile& t,
                                          const float* __restrict__ vd, float* s_vd, float* s_ig) {
@@ -904,7 +909,7 @@ __device__ __forceinline__ void gap_flat(const StepArgs& a, const InstDesc& d, c
     auto load = [&](int base) {
 #pragma unroll
         for (int u = 0; u < K; ++u) {
-            const int i = max(0, min(base + u * BLOCK + (int)threadIdx.x, m - 1));
+            const int i = flat_load(base + u * BLOCK + (int)threadIdx.x, m);
             q[u] = ch[i];
             tg[u] = tag[i];
             if (HASW) {
@@ -913,7 +918,7 @@ __device__ __forceinline__ void gap_flat(const StepArgs& a, const InstDesc& d, c
             }
         }
     };
-    load(0);
+    if (m > 0) load(0);
     // the owners of a row: OWN consecutive threads (a power of two, at most a wave)
     const int own = max(1, min(64, BLOCK >> (nrows <= 1 ? 0 : 32 - __builtin_clz(nrows - 1))));
     const int orow = threadIdx.x / own, oq = threadIdx.x & (own - 1);
