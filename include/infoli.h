@@ -458,7 +458,10 @@ infoli_status infoli_surrogate_set(infoli_ctx *ctx, const float *params, const f
  * A cell takes the MLP unless it is held, checked or guarded (see the report's
  * fields); a checked cell runs the plain method and is flagged when the MLP's
  * voltages differ from it by more than theta; a flagged cell is held on the
- * plain method for hold_steps macro steps.
+ * plain method for hold_steps macro steps. On CSR networks of at most 32,768
+ * cells the gap currents of the macro steps are summed in an order fixed by the
+ * network's size, degree and form, not by the tuner (which may choose another
+ * order for the plain steps from run to run).
  * cfg NULL => defaults (theta 0.5 mV, v_max -40 mV, ca_max 20, 1/64 checked per
  * macro step, 50 macro steps of hold, z_max 8). report optional (blocking when
  * given). */

@@ -77,6 +77,8 @@ struct SurrogateState {
     float norm[64] = {0};               // in_mean[16] in_rstd[16] out_mean[16] out_std[16]
     int32_t* hold = nullptr;            // [cells]
     unsigned long long* counters = nullptr;   // [4] plain, checked, flagged, guarded
+    TileGroup gap;                      // the macro steps' gap launch, and its descriptor
+    InstDesc* gap_inst = nullptr;       //   (null: the plain steps' launches)
 };
 
 }  // namespace infoli_rt
@@ -116,7 +118,6 @@ struct infoli_ctx {
     int tuned = 0;                  // networks whose tiles came from timing runs
     int tune_cached = 0;            // networks whose tiles came from the tuning cache
     int tune_mode = -1;             // whole-step launch mode the tuner chose (-1: none)
-    bool no_flat = false;           // planned without flat chunked tiles (leave_flat)
 
     // device memory
     std::vector<void*> allocs;
@@ -227,7 +228,7 @@ void launch_tiles(infoli_ctx* c, hipStream_t st, const StepArgs& a, int block, u
 void launch_groups(infoli_ctx* c, hipStream_t st, const StepArgs& a, int from, int64_t step_arg, int32_t off,
                    bool fork);
 int64_t tile_count(const infoli_ctx* c);
-void leave_flat(infoli_ctx* c);
+void plan_surrogate_gap(infoli_ctx* c, TileGroup& tg, InstDesc** d_inst);
 void check_instance(const infoli_ctx* c, int32_t k);
 
 }  // namespace infoli_rt

@@ -303,7 +303,7 @@ size_t flat_lds_floats(const infoli_ctx* c, int k, int rows) {
 // A network's chunked rows can run as flat tiles of `rows` rows.
 bool flat_ok(const infoli_ctx* c, int k, int rows) {
     const InstDesc& d = c->inst[k];
-    return !c->no_flat && d.conn == CONN_CSR && d.ca_off >= 0 && d.n <= kFlatCells && c->d_rtag &&
+    return d.conn == CONN_CSR && d.ca_off >= 0 && d.n <= kFlatCells && c->d_rtag &&
            flat_lds_floats(c, k, rows) * sizeof(float) + kStaticLds <= (size_t)c->lds_max;
 }
 
@@ -743,9 +743,8 @@ std::string tune_key(const infoli_ctx* c, const InstDesc& d, double deg) {
     const int nb = (int)std::ceil(std::log2((double)d.n) * 4.0);
     const int db = (int)std::ceil(std::log2(deg + 1.0) * 4.0);
     char buf[128];
-    snprintf(buf, sizeof buf, "gfx950 groups2 c16=%d w=%d bits=%d blk=%d n%d d%d%s%s", d.col16, d.has_w,
-             d.bits_off >= 0 ? 1 : 0, d.cb_off >= 0 ? c->blk_cols : 0, nb, db, d.sgj ? " sgj" : "",
-             c->no_flat ? " rows" : "");
+    snprintf(buf, sizeof buf, "gfx950 groups2 c16=%d w=%d bits=%d blk=%d n%d d%d%s", d.col16, d.has_w,
+             d.bits_off >= 0 ? 1 : 0, d.cb_off >= 0 ? c->blk_cols : 0, nb, db, d.sgj ? " sgj" : "");
     return buf;
 }
 
@@ -1766,74 +1765,69 @@ void make_graphs(infoli_ctx* c) {
     get_graph(c, 1);
 }
 
+// Shape of a surrogate's gap launch, by rule and not by timing: its macro steps
+// decide per cell (guards, the drift test) on inputs rounded to BF16, so another
+// order of a row's sum, itself as good, can hand a cell to the other method (of
+// 24 runs of 20 macro steps two had cells 0.5 and 2.2 mV elsewhere). Row sums by
+// lane groups from the chunked rows, one 256-thread workgroup per compute unit
+// and no more lanes than a row has chunks (dry steps: 1,000 cells of degree 300
+// L64 6.3 us, L32 6.5, L16 6.7; 4,000 of 150 L16 6.6, L32 6.9; 8,192 of 300 L8
+// 8.1, L16 9.3; 16,384 of 150 L4 8.7, L8 10.0; past 16,384 cells L8: 20,000 of
+// degree 50 8.5, L4 8.9); dense patterns the bitmap (4,000
+// cells of degree 500 8.2 us against 11.1, which does not grow with the degree);
+// past 16,384 cells the chunk stream (32,768 cells of degree 50 9.8 us against
+// 10.7, 20,000 of 300 13.7 against 16.3, of 50 9.7 against 8.5), and the column
+// blocks for high degrees that do not fill the stream's tiles (16,384 cells of
+// degree 500 14.4 us against 15.6 and the stream's 15.3, 9,000 12.2 against 13.8;
+// of 300 13.2 against 11.4).
+TuneChoice surrogate_shape(const infoli_ctx* c, const InstDesc& d, double deg) {
+    if (d.bits_off >= 0 && deg >= 0.3 * d.n) return TuneChoice{16, kBitRows, 0, 1, 1024};
+    InstDesc s = d;
+    s.blocked = s.stream = 1;
+    if (d.n > 16384 && deg * d.n >= 1.5e6 && d.cb_off >= 0 && !d.has_w && d.nblk <= kStreamMaxBlocks &&
+        d.cell_off % 4 == 0 && stream_ok(c) &&
+        lds_floats_for(c, 0, s, 1024) * sizeof(float) + kStaticLds <= (size_t)c->lds_max)
+        return TuneChoice{64, kSelfSlots, 0, 4, deg < 100.0 ? 512 : 1024};
+    if (d.cb_off >= 0 && deg >= 400.0)
+        return d.n <= 16384 ? TuneChoice{16, 64, 0, 2, 1024} : TuneChoice{8, 128, 0, 2, 1024};
+    int L = d.n > 16384 ? 8 : 4;
+    while (L < 64 && L < deg / kChunkCols && 2 * (int64_t)L * d.n <= 256 * (int64_t)c->n_cu) L *= 2;
+    return TuneChoice{L, 256 / L, 0, 3, 256};
+}
+
 }  // namespace
 
-// Plans a surrogate's network without flat tiles (its rows summed by lane
-// groups), once, when the surrogate gets its weights. Its macro steps decide
-// per cell (guards, the drift test) on inputs rounded to BF16, so another order
-// of a row's sum, itself as good, can hand a cell to the other method: of 24
-// runs of 20 macro steps two had cells 0.5 and 2.2 mV elsewhere. Costs 5 us of
-// a macro step at 16,384 cells (24.5 -> 29.8 us), 2 at 6,000 (20.6 -> 22.6).
-void infoli_rt::leave_flat(infoli_ctx* c) {
-    if (c->no_flat) return;
-    bool flat = false;
-    for (const InstDesc& d : c->inst) flat = flat || (d.conn == CONN_CSR && d.flat);
-    if (!flat) {
-        c->no_flat = true;
-        return;
-    }
-    HIPX(hipStreamSynchronize(c->stream));
-    for (hipGraphExec_t& g : c->graph) {
-        if (g) (void)hipGraphExecDestroy(g);
-        g = nullptr;
-    }
-    const auto inst = c->inst;
-    const auto rows = c->rows_of;
-    const int blocks[2] = {c->grp[0].block, c->grp[1].block};
-    const int tuned = c->tuned, cached = c->tune_cached, mode = c->tune_mode;
-    const bool fork = c->fork_groups;
-    struct Events {        // the tuner's own: the last step's stay as they are
-        infoli_ctx* c;
-        hipEvent_t e0, e1;
-        explicit Events(infoli_ctx* c) : c(c), e0(c->ev0), e1(c->ev1) {
-            hipEvent_t a = nullptr, b = nullptr;
-            HIPX(hipEventCreate(&a));
-            if (const hipError_t e = hipEventCreate(&b); e != hipSuccess) {
-                (void)hipEventDestroy(a);
-                fail(INFOLI_E_DEVICE, "hipEventCreate: %s", hipGetErrorString(e));
-            }
-            c->ev0 = a;
-            c->ev1 = b;
-        }
-        ~Events() {
-            (void)hipEventDestroy(c->ev0);
-            (void)hipEventDestroy(c->ev1);
-            c->ev0 = e0;
-            c->ev1 = e1;
-        }
-    } events(c);
-    c->no_flat = true;
-    try {
-        if (c->opt.autotune && c->opt.csr_path == 0) {
-            c->tuned = c->tune_cached = 0;
-            c->tune_mode = -1;
-            autotune(c);
-        }
-    } catch (...) {      // the plan as it was
-        c->no_flat = false;
-        c->inst = inst;
-        c->rows_of = rows;
-        for (int g = 0; g < 2; ++g) c->grp[g].block = blocks[g];
-        c->tuned = tuned;
-        c->tune_cached = cached;
-        c->tune_mode = mode;
-        c->fork_groups = fork;
-        finalize_tiles(c);
-        throw;
-    }
-    finalize_tiles(c);
-    HIPX(hipStreamSynchronize(c->stream));
-    make_graphs(c);
+// The gap launch of a surrogate's macro steps, beside the plan of the plain
+// steps: for networks that those could run as flat tiles, whose order the tuner
+// chooses. A caller's own csr_path or tile shape is kept, without flat tiles;
+// otherwise (larger networks, built-in shapes) the macro steps launch the plain
+// steps' tiles.
+void infoli_rt::plan_surrogate_gap(infoli_ctx* c, TileGroup& tg, InstDesc** d_inst) {
+    InstDesc d = c->inst[0];
+    if (c->n_inst != 1 || d.conn != CONN_CSR || d.ca_off < 0 || d.n > kFlatCells) return;
+    const bool tuned = c->opt.autotune && c->opt.csr_path == 0 && !c->opt.lanes_per_row && !c->opt.tile_rows;
+    if (!tuned && !d.flat) return;
+    const TuneChoice t = tuned ? surrogate_shape(c, d, c->deg_of[0])
+                               : TuneChoice{d.lanes_per_row, c->rows_of[0], 0, 3, c->grp[c->group_of[0]].block};
+    d.lanes_per_row = t.L;
+    d.vd_lds = 0;
+    d.bitmap = t.bm == 1;
+    d.blocked = t.bm == 2 || t.bm == 4;
+    d.stream = t.bm == 4;
+    d.stream_round = t.rnd;
+    d.chunked = t.bm == 3;
+    d.flat = 0;
+    std::vector<std::pair<double, Tile>> planned;
+    append_tiles(c, planned, 0, t.R, c->deg_of[0]);
+    tg.tiles.clear();
+    for (const auto& pt : planned) tg.tiles.push_back(pt.second);
+    tg.block = t.block;
+    tg.lds = ((lds_floats_for(c, 0, d, t.block) + 3) / 4) * sizeof(float4);
+    tg.var = d.stream ? kVarStream : d.has_w || d.pcell ? kVarAll : kVarNoW;
+    tg.d_tiles = c->alloc<Tile>(tg.tiles.size());
+    HIPX(hipMemcpy(tg.d_tiles, tg.tiles.data(), sizeof(Tile) * tg.tiles.size(), hipMemcpyHostToDevice));
+    *d_inst = c->alloc<InstDesc>(1);
+    HIPX(hipMemcpy(*d_inst, &d, sizeof(d), hipMemcpyHostToDevice));
 }
 
 namespace {

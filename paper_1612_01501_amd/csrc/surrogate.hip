@@ -53,7 +53,7 @@ NormStats norm_of(const float* n64) {
 void ensure_surrogate_buffers(infoli_ctx* c) {
     SurrogateState& s = c->surr;
     if (s.params) return;
-    s.params = c->alloc<float>(kNumParams);
+    float* params = c->alloc<float>(kNumParams);
     s.m = c->alloc<float>(kNumParams);
     s.v = c->alloc<float>(kNumParams);
     s.grad = c->alloc<float>((size_t)kNumParams * kGradSplits);   // split-K partials
@@ -62,6 +62,8 @@ void ensure_surrogate_buffers(infoli_ctx* c) {
     s.counters = c->alloc<unsigned long long>(4);
     HIPX(hipMemset(s.hold, 0, sizeof(int32_t) * c->stride));
     HIPX(hipMemset(s.counters, 0, sizeof(unsigned long long) * 4));
+    plan_surrogate_gap(c, s.gap, &s.gap_inst);
+    s.params = params;      // last: a call that failed half-way is made anew
 }
 
 void check_params(const float* p, int64_t n) {
@@ -109,7 +111,14 @@ SurrArgs surr_args(infoli_ctx* c, const infoli_drift_cfg& dc, int64_t macro_inde
 void launch_macro(infoli_ctx* c, hipStream_t st, const infoli_drift_cfg& dc, int from, int64_t step0) {
     StepArgs g = make_args(c, false);
     g.gap_only = 1;
-    launch_groups(c, st, g, from, step0, 0, false);
+    if (c->surr.gap_inst) {
+        const TileGroup& tg = c->surr.gap;
+        g.inst = c->surr.gap_inst;
+        g.tiles = tg.d_tiles;
+        launch_tiles(c, st, g, tg.block, (unsigned)tg.tiles.size(), tg.lds, from, step0, 0, tg.var);
+    } else {
+        launch_groups(c, st, g, from, step0, 0, false);
+    }
     const StepArgs a = make_args(c, false);
     const int64_t cells = c->total_cells;
     if (dc.mode == INFOLI_SURROGATE_PLAIN_HOLD) {
@@ -301,7 +310,6 @@ infoli_status infoli_surrogate_train(infoli_ctx* ctx, const infoli_train_cfg* cf
         const int64_t n_data = per_traj * cfg->n_trajectories;
         if (n_data > (int64_t)1 << 28) fail(INFOLI_E_INVALID_ARG, "training set too large");
         ensure_surrogate_buffers(ctx);
-        leave_flat(ctx);
         SurrogateState& s = ctx->surr;
         hipStream_t st = ctx->stream;
         Scoped tmp(st);
@@ -430,7 +438,6 @@ infoli_status infoli_surrogate_set(infoli_ctx* ctx, const float* params, const f
         check_params(params, kNumParams);
         check_norm(norm);
         ensure_surrogate_buffers(ctx);
-        leave_flat(ctx);
         HIPX(hipStreamSynchronize(ctx->stream));
         upload_weights(ctx, params);
         std::memcpy(ctx->surr.norm, norm, sizeof(float) * 64);
