@@ -360,7 +360,7 @@ size_t lds_floats_for(const infoli_ctx* c, int k, const InstDesc& d, int block) 
     if (d.conn == CONN_UNIFORM) return (size_t)std::min(d.n, kChunk) + 8 * (size_t)(block / 64);
     if (d.conn == CONN_CSR && d.bitmap) return bitmap_lds_floats(d.n);
     if (d.conn == CONN_CSR && d.flat) return flat_lds_floats(c, k, c->rows_of[k]);
-    if (d.conn == CONN_CSR && d.vd_lds) return (size_t)d.n;
+    if (d.conn == CONN_CSR && d.vd_lds && !(d.chunked && d.ca_off >= 0)) return (size_t)d.n;
     return 4;
 }
 
@@ -885,7 +885,7 @@ float time_shape(infoli_ctx* c, const std::vector<int>& ks, const TuneChoice& t,
         else if (t.bm == 4)
             lds = std::max(lds, ((lds_floats_for(c, k, d, t.block) + 3) / 4) * sizeof(float4));
         else if (d.flat) lds = std::max(lds, ((flat_lds_floats(c, k, t.R) + 3) / 4) * sizeof(float4));
-        else if (t.lds) lds = std::max(lds, ((size_t)(d.n + 3) / 4) * sizeof(float4));
+        else if (t.lds && t.bm != 3) lds = std::max(lds, ((size_t)(d.n + 3) / 4) * sizeof(float4));
     }
     std::vector<Tile> tl;
     for (const auto& pt : planned) tl.push_back(pt.second);
@@ -1070,10 +1070,8 @@ void autotune_shapes(infoli_ctx* c) {
                 for (int m = 1; m <= 4; m *= 2) {
                     const int R = std::max(1, 256 / L) * m;
                     if (R > kMaxTileRows) continue;
-                    for (int lds = 0; lds <= (n <= kChunk ? 1 : 0); ++lds) {
-                        consider(TuneChoice{L, R, lds, 0, 256});
-                        if (all_rows && !all_flat(R)) consider(TuneChoice{L, R, lds, 3, 256});
-                    }
+                    for (int lds = 0; lds <= (n <= kChunk ? 1 : 0); ++lds) consider(TuneChoice{L, R, lds, 0, 256});
+                    if (all_rows && !all_flat(R)) consider(TuneChoice{L, R, 0, 3, 256});
                 }
             }
             // the gathers in 1024-thread workgroups (at the best 256-thread
@@ -1085,7 +1083,7 @@ void autotune_shapes(infoli_ctx* c) {
                     const int R = std::max(1, 1024 / L) * m;
                     if (R > kMaxTileRows) continue;
                     consider(TuneChoice{L, R, best256.lds, 0, 1024});
-                    if (all_rows && !all_flat(R)) consider(TuneChoice{L, R, best256.lds, 3, 1024});
+                    if (all_rows && !all_flat(R)) consider(TuneChoice{L, R, 0, 3, 1024});
                 }
             }
             // the chunked rows as flat runs: a quarter to sixteen chunks per thread

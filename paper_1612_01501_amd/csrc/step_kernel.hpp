@@ -971,9 +971,11 @@ __device__ __forceinline__ void gap_flat(const StepArgs& a, const InstDesc& d, c
     if (orow < nrows && oq == 0) s_ig[orow] = (HASW ? 1.0f : d.g) * part * kInvPreScale;
 }
 
-// Chunked rows of networks beyond kFlatCells (at most 65,536 cells): L lanes
-// per row, the neighbours' voltages gathered from global memory. Row r's chunks
-// [ca[r], ca[r + 1]), padded with r itself.
+// Chunked rows that are no flat tiles (networks beyond kFlatCells, tiles whose
+// sums do not fit LDS, a surrogate's gap launch): L lanes per row, the
+// neighbours' voltages gathered from global memory (from a copy in LDS they were
+// no faster at any of 2,000 to 8,192 cells and degrees 50 to 500: 2,000 of 500
+// 7.2 us, 7.8 from LDS). Row r's chunks [ca[r], ca[r + 1]), padded with r itself.
 template <int BLOCK, bool HASW, bool SGJ>
 __device__ __forceinline__ void gap_chunks(const StepArgs& a, const InstDesc& d, const Tile& t,
                                            const float* __restrict__ vd, float* s_part,
@@ -1417,15 +1419,17 @@ __device__ __forceinline__ void gap_csr_form(const StepArgs& a, const InstDesc& 
             by_weights<W>(d, [&](auto hw) { gap_flat<BLOCK, decltype(hw)::value, SGJ, var_vd_first(VAR)>(a, d, t, vd, s_vd, s_ig); });
             return;
         }
+        if (d.chunked && d.ca_off >= 0) {
+            by_weights<W>(d, [&](auto hw) { gap_chunks<BLOCK, decltype(hw)::value, SGJ>(a, d, t, vd, s_part, s_ig); });
+            return;
+        }
         if (d.vd_lds) {
             for (int k = threadIdx.x; k < d.n; k += BLOCK) s_vd[k] = vd[k] * kPreScale;
             __syncthreads();
         }
         by_weights<W>(d, [&](auto hw) {
             constexpr bool HW = decltype(hw)::value;
-            if (d.chunked && d.ca_off >= 0) {
-                gap_chunks<BLOCK, HW, SGJ>(a, d, t, vd, s_part, s_ig);
-            } else if (d.vd_lds) {
+            if (d.vd_lds) {
                 if (d.col16) gap_csr_impl<BLOCK, true, true, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
                 else gap_csr_impl<BLOCK, true, false, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
             } else {

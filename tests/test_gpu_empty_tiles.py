@@ -35,3 +35,26 @@ def test_isolated_last_rows(infoli, o64, n, linked, rows, weights):
         sim.step(2)
         sim.sync()
         sim.close()
+
+
+def test_chunked_rows_past_the_flat_tiles(infoli, o64, tmp_path, monkeypatch):
+    """Tiles of 256 rows whose chunk sums do not fit LDS beside the voltages:
+    the lane groups gather from memory, with no copy of the voltages that
+    nothing reads (the tuner times none such)."""
+    n, deg = 8192, 1000
+    rp, col = I.erdos_renyi_csr(n, deg / (n - 1), 3)
+    net = I.Network(n=n, conn="csr", g=0.04 * 96 / deg, row_ptr=rp, col=col, jitter=I.voltage_jitter(n, 5, 15.0))
+    x0 = infoli.initial_state(net)
+    sim = infoli.Simulator(net, init_states=[x0], csr_path=4, tile_rows=256, step_mode="graph")
+    assert sim.gap_path(0) == ("csr_chunked", False)
+    check_gap(sim, 0, net, x0[0], o64)
+    sim.close()
+    log = tmp_path / "log.txt"
+    monkeypatch.setenv("INFOLI_TUNE_LOG", str(log))
+    sim = infoli.Simulator(net, init_states=[x0], step_mode="graph", autotune=2)
+    check_gap(sim, 0, net, x0[0], o64)
+    sim.close()
+    shapes = [ln.split(" shape ")[1].split(":")[0].split() for ln in log.read_text().splitlines() if " shape " in ln]
+    rows = [s for s in shapes if s[3] == "path3"]
+    assert any(s[1] == "R256" and s[0] != "L64" for s in rows)      # lane groups, timed
+    assert all(s[2] == "lds0" or s[0] == "L64" for s in rows)       # staged by the flat tiles alone
