@@ -277,7 +277,7 @@ Tile make_tile(const infoli_ctx* c, int k, int r0, int r1) {
         t.row_chk = d.ca_off + r0;
         t.chk_base = c->h_ca[(size_t)t.row_chk];
         t.chunks = c->h_ca[(size_t)(d.ca_off + r1)] - t.chk_base;
-        t.chk0 = d.chk_off + t.chk_base;
+        t.chk0 = flat_first(d.chk_off, t.chk_base, t.chunks);
     }
     return t;
 }

@@ -106,7 +106,7 @@ struct Tile {
     int32_t row1;
     int32_t n;             // the network's cells
     int64_t cell_off;      // its cell 0
-    int64_t chk0;          // chunked CSR in LDS: the tile's first chunk
+    int64_t chk0;          // chunked CSR in LDS: the tile's first chunk (flat_first)
     int64_t row_chk;       //   where the chunk starts of its rows are in StepArgs::ca
     int32_t chunks;        //   and its chunks
     int32_t chk_base;      //   the first one's index in the network
@@ -887,10 +887,19 @@ constexpr int kFlatCells = 32768;       // networks up to this size (128 KB of V
 
 __host__ __device__ constexpr int flat_vd_floats(int n) { return (n + 3) & ~3; }
 
-// Chunk that slot k of a tile of m chunks loads: its own, past the last one the
-// last again. None (-1) in a tile whose rows have no connections: its first
-// chunk may be one past the last of the arrays.
-__host__ __device__ constexpr int flat_load(int k, int m) { return m <= 0 ? -1 : k < m ? k : m - 1; }
+// Chunk, from the tile's first one on, that slot k of a tile of m chunks loads: its
+// own, past the last one the last again. A tile whose rows have no connections
+// loads one chunk all the same (a branch around the loads would keep them from
+// overlapping the staging of Vd: three 4,096-cell networks 9.3 -> 9.5 us a step),
+// so its first chunk is the network's first: its own may be one past the last of
+// the arrays.
+__host__ __device__ constexpr int flat_load(int k, int m) {
+    const int last = k < m - 1 ? k : m - 1;
+    return last > 0 ? last : 0;
+}
+__host__ __device__ constexpr int64_t flat_first(int64_t network, int base, int m) {
+    return m > 0 ? network + base : network;
+}
 
 template <int BLOCK, bool HASW, bool SGJ, bool VD0>
 __device__ __forceinline__ void gap_flat(const StepArgs& a, const InstDesc& d, const Tile& t,
@@ -918,7 +927,7 @@ __device__ __forceinline__ void gap_flat(const StepArgs& a, const InstDesc& d, c
             }
         }
     };
-    if (m > 0) load(0);
+    load(0);
     // the owners of a row: OWN consecutive threads (a power of two, at most a wave)
     const int own = max(1, min(64, BLOCK >> (nrows <= 1 ? 0 : 32 - __builtin_clz(nrows - 1))));
     const int orow = threadIdx.x / own, oq = threadIdx.x & (own - 1);

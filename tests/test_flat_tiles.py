@@ -1,6 +1,6 @@
 """Host check of the chunks a flat chunked tile loads (step_kernel.hpp's own
-flat_load): every index lies in the network's chunks, also where a tile's rows,
-the last ones of the last network among them, have no connections."""
+flat_first and flat_load): every index lies in the arrays, also where a tile's
+rows, the last ones of the last network among them, have no connections."""
 import os
 import subprocess
 
@@ -19,13 +19,15 @@ int main() {
                 for (int deg : {1, 8, 9, 200}) {
                     std::vector<int> ca(n + 1, 0);
                     for (int i = 0; i < n; ++i) ca[i + 1] = ca[i] + (i < n - isolated ? (deg + kChunkCols - 1) / kChunkCols : 0);
-                    for (int r0 = 0; r0 < n; r0 += rows) {
+                    const long network = 3, total = network + ca[n];    // three chunks of another network ahead
+                    for (int r0 = 0; ca[n] > 0 && r0 < n; r0 += rows) {
                         const int r1 = r0 + rows < n ? r0 + rows : n;
-                        const int chk0 = ca[r0], m = ca[r1] - chk0;
+                        const int m = ca[r1] - ca[r0];
+                        const long first = flat_first(network, ca[r0], m);
                         for (int base = 0; base == 0 || base < m; base += kFlatChunks * 256)
                             for (int k = base; k < base + kFlatChunks * 256; ++k) {
                                 const int i = flat_load(k, m);
-                                if (m == 0 ? i != -1 : (i < 0 || chk0 + i >= ca[n] || (k < m && i != k))) {
+                                if (i < 0 || first < 0 || first + i >= total || (k < m && first + i != network + ca[r0] + k)) {
                                     std::printf("n %d rows %d tile %d chunks %d slot %d: %d\n", n, rows, r0, m, k, i);
                                     return 1;
                                 }
