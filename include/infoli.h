@@ -185,7 +185,9 @@ typedef struct infoli_options {
                                     millivolts and interpolated at every cell: by each
                                     tile, or for a context's only network from 4,096
                                     cells on by a kernel ahead of the step, 2,568 bytes
-                                    for each of at most 128 shares of the cells); 1 => every
+                                    for each of at most 128 shares of the cells; rows
+                                    whose voltages are too far apart, or outside -155 to
+                                    154 mV ahead of the step, take their pairs); 1 => every
                                     ordered pair; 2 => each unordered pair once (the pair
                                     term of Section 2.3.1, Algorithm 1, is odd in dV,
                                     so the pair (j, i) gives minus the term of (i, j)).

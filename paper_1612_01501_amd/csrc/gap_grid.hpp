@@ -23,7 +23,11 @@
 // Measured per step against every unordered pair once (or, in the batch, every
 // ordered pair): 16,384 cells 39.8 -> 12.3 us (k_grid_sums 4.5 of it), 8,192
 // 18.7 -> 11.6, 40,000 178 -> 14.7, a batch of 256 networks of 64-2,048 cells
-// a third of them all-to-all 75.8 -> 54.4. What remains is latency: two
+// a third of them all-to-all 75.8 -> 54.4. With voltages over 150 mV 5,000 cells
+// 14.0 -> 15.7, 16,384 41 -> 17.4; over 250 mV 18.9 and 21.1; 2,000 cells (their
+// pairs then) 13.7 -> 14.5; with some beyond the grid ahead (every pair, ordered,
+// one workgroup for 64 rows up to 16,384 cells, for 256 above) 5,000 cells 34,
+// 16,384 90, 40,000 780. What remains is latency: two
 // launches, and in each a chain of loads, fp64 exponentials and exchanges
 // between lanes.
 #pragma once
@@ -40,7 +44,8 @@ constexpr int kGridCells = 512;
 constexpr int kGridQ = 12;              // grid points of one interpolation
 constexpr int kGridLeft = 5;            // of them below floor(v)
 constexpr int kGridGroup = 16;          // grid points per group
-constexpr int kGridMaxGroups = 12;      // groups of one tile (voltages up to 180 mV apart)
+constexpr int kGridMaxGroups = 12;      // groups of a tile's own sums, or a workgroup's of the persistent
+                                        // kernel (voltages up to 180 mV apart)
 constexpr int kGridAheadLo = -160;      // k_grid_sums: first grid point (mV)
 constexpr int kGridAheadGroups = 20;    //   and groups: up to 159 mV
 constexpr double kGridReach = 64.0;     // k_grid_sums skips a group farther than this from a cell:
@@ -56,8 +61,17 @@ __host__ __device__ constexpr int grid_chunks(int n) { return (n + grid_per(n) -
 __host__ __device__ constexpr int64_t grid_floats(int n) {
     return (2 * (int64_t)grid_chunks(n) * (kGridAheadGroups * kGridGroup + 1) + 63) / 64 * 64;
 }
-// doubles of LDS of a tile: the waves' sums, then the grid
-__host__ __device__ constexpr int grid_lds_doubles(int waves) { return (waves + 1) * kGridMaxGroups * kGridGroup; }
+// doubles of LDS of a tile: the waves' sums, then the grid (room for all of
+// k_grid_sums' groups, one constant for both kinds of tiles: with two a batch of
+// 256 networks took 1 % longer)
+__host__ __device__ constexpr int grid_lds_doubles(int waves) { return (waves + 1) * kGridAheadGroups * kGridGroup; }
+// Groups a tile of so many rows sums itself at most; where its voltages need more
+// it takes its pairs. One row per lane (600 cells: 7.0 us a step with one group,
+// 9.4 with three, 8.4 with all pairs; 2,000: 9.4, 14.2, 14.6): two. More rows,
+// where the chip is full of such tiles (64 networks of 2,048 cells: eleven groups
+// 55 us, all pairs 73; 1,000 cells 25 and 27): three for each 64.
+__host__ __device__ constexpr int grid_tile_groups(int rows) { return rows <= 64 ? 2 : 3 * ((rows + 63) / 64); }
+static_assert(grid_tile_groups(256) <= kGridMaxGroups, "a tile of 256 rows");
 
 // e^x to about 1e-13 for |x| below a few thousand (0 or infinity beyond the
 // range of fp64): x = n ln 2 + r, |r| <= ln 2 / 2, the Taylor series of e^r to

@@ -1505,12 +1505,18 @@ void build_context(infoli_ctx* c, const infoli_network_spec* specs, int32_t nins
         if (c->inst[k].conn == CONN_CSR && c->inst[k].n > 65536) col16 = false;
     c->rows_of.assign(ninst, kMaxTileRows);
     c->deg_of.assign(ninst, 0.0);
+    // All-to-all networks on the voltage grid: a row per thread, so that the sums
+    // are taken (or added) for 256 rows at once, where the context has more than
+    // a compute unit's 64 rows for each; one row per lane below, where the other
+    // units stand idle: the same chain of work beside more of them, and a tile
+    // whose voltages ask for its pairs has a quarter of them.
+    const bool narrow_grid = cells <= (int64_t)kUniformRows * c->n_cu;
     for (int k = 0; k < ninst; ++k) {
         InstDesc& d = c->inst[k];
         int rows;
         switch (d.conn) {
             case CONN_UNIFORM:   // one row per lane; a row per thread when the sum is taken once
-                rows = sum_once(c, d) || grid_kind(c, d) ? kMaxTileRows : kUniformRows;
+                rows = sum_once(c, d) || (grid_kind(c, d) && !narrow_grid) ? kMaxTileRows : kUniformRows;
                 c->deg_of[k] = grid_kind(c, d) ? d.n / 32.0 : d.n;
                 break;
             case CONN_DENSE: rows = c->opt.tile_rows ? c->opt.tile_rows : kDenseRows; c->deg_of[k] = d.n; break;

@@ -375,18 +375,97 @@ __device__ __forceinline__ void gap_uniform_sum(const StepArgs& a, const InstDes
         s_ig[k] = d.g * (float)((double)d.n * (double)vd[t.row0 + k] - tot);
 }
 
+// Every pair of the tile's rows, 64 rows at a time: a lane per row, a wave's share
+// of the cells 64 at a time, a lane each to load (the next ones ahead) and then one
+// after the other for all rows, their terms' sums added up in fp64 (2,000 cells
+// 14.6 us a step; through LDS, 1,024 cells at a time, 16.1). Where k_grid_sums took
+// the voltages' sum and it is not finite, a voltage is not, and no row's terms are
+// (an infinite difference times e^-inf is a NaN).
+template <int BLOCK>
+__device__ __forceinline__ void gap_uniform_pairs(const StepArgs& a, const InstDesc& d, const Tile& t,
+                                                  const float* __restrict__ vd, float* s_ig, double* s_red,
+                                                  double* s_w) {
+    constexpr int W = BLOCK / 64;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = d.n;
+    const int nrows = t.row1 - t.row0;
+    double vsum = 0.0;
+    const auto wave_total = [&]() {
+        vsum = grid_wave(vsum, [](double x, double y) { return x + y; });
+        if (lane == 0) s_red[wave] = vsum;
+    };
+    const auto total = [&]() {
+        double tot = 0.0;
+        for (int w = 0; w < W; ++w) tot += s_red[w];
+        return tot;
+    };
+    if (d.grid == 2) {
+        const int C = grid_chunks(n);
+        const double* vs = reinterpret_cast<const double*>(a.psym + d.psym_off) + (int64_t)kGridAheadGroups * C * kGridGroup;
+        for (int c = threadIdx.x; c < C; c += BLOCK) vsum += vs[c];
+        wave_total();
+        __syncthreads();
+        if (!(fabs(total()) <= 1.0e300)) {
+            if ((int)threadIdx.x < nrows) s_ig[threadIdx.x] = __builtin_nanf("");
+            return;
+        }
+    }
+    const int per = ((n + W - 1) / W + 63) / 64 * 64;
+    const int j0 = min(n, wave * per), j1 = min(n, j0 + per);
+    for (int r0 = 0; r0 < nrows; r0 += 64) {
+        const bool sum = d.grid != 2 && r0 == 0;
+        const float v = vd[t.row0 + min(r0 + lane, nrows - 1)];
+        double acc = 0.0;
+        float next = vd[min(j0 + lane, n - 1)];
+        for (int j = j0; j < j1; j += 64) {
+            const float u = next;
+            next = vd[min(j + 64 + lane, n - 1)];
+            const auto cell = [&](int k) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(u), k)); };
+            const int m = min(64, j1 - j);
+            float a0 = 0.0f, a1 = 0.0f;
+            int k = 0;
+            for (; k + 8 <= m; k += 8) {
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) {
+                    const float d0 = v - cell(k + e), d1 = v - cell(k + e + 1);
+                    a0 = fmaf(d0, __builtin_amdgcn_exp2f(-(d0 * d0) * kL2eOver100), a0);
+                    a1 = fmaf(d1, __builtin_amdgcn_exp2f(-(d1 * d1) * kL2eOver100), a1);
+                }
+            }
+            for (; k < m; ++k) {
+                const float d0 = v - cell(k);
+                a0 = fmaf(d0, __builtin_amdgcn_exp2f(-(d0 * d0) * kL2eOver100), a0);
+            }
+            acc += (double)(a0 + a1);
+            if (sum && lane < m) vsum += (double)u;
+        }
+        s_w[wave * 64 + lane] = acc;
+        if (sum) wave_total();
+        __syncthreads();
+        if ((int)threadIdx.x < 64 && r0 + lane < nrows) {
+            double f = 0.0;
+            for (int w = 0; w < W; ++w) f += s_w[w * 64 + lane];
+            const double lin = (double)n * (double)v - total();
+            s_ig[r0 + lane] = (float)((double)d.g * (0.8 * f + 0.2 * lin));
+        }
+        __syncthreads();
+    }
+}
+
 // All-to-all networks with the realistic term on the voltage grid
 // (gap_grid.hpp): up to BLOCK rows, one per thread. The tile takes the grid
 // points its own rows' voltages need; it sums the cells' terms there itself,
 // or (AHEAD) adds the shares' sums k_grid_sums wrote, in a fixed order either
-// way. A tile whose rows are too far apart for its grid, or hold a voltage that
-// is not finite, takes every pair instead (a thread per row).
+// way. A tile whose rows hold a voltage that is not finite or, ahead, outside
+// the grid, or are so far apart that its own sums cost more than the pairs,
+// takes every pair (grid_tile_groups).
 template <int BLOCK>
 __device__ __forceinline__ void gap_uniform_grid(const StepArgs& a, const InstDesc& d, const Tile& t,
                                                  const float* __restrict__ vd, float* s_ig, float* s_part,
                                                  double* s_red, double* s_g) {
     constexpr int W = BLOCK / 64;
-    constexpr int GP = kGridMaxGroups * kGridGroup;
+    constexpr int GP = kGridAheadGroups * kGridGroup;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = d.n;
@@ -415,20 +494,10 @@ __device__ __forceinline__ void gap_uniform_grid(const StepArgs& a, const InstDe
         g0 -= (g0 - kGridAheadLo) & (kGridGroup - 1);           // whole groups of k_grid_sums
     }
     const int groups = __builtin_amdgcn_readfirstlane((g1 - g0 + kGridGroup - 1) / kGridGroup);
-    ok = ok && groups <= kGridMaxGroups;
+    ok = ok && (d.grid == 2 || groups <= grid_tile_groups(nrows));
     double vsum = 0.0;
     if (!ok) {
-        if ((int)threadIdx.x < nrows) {
-            const float vs = v * kPreScale;
-            float acc = 0.0f;
-            for (int j = 0; j < n; ++j) {
-                const float dv = vs - vd[j] * kPreScale;
-                acc = fmaf(dv, __builtin_amdgcn_exp2f(-(dv * dv)), acc);
-                vsum += (double)vd[j];
-            }
-            const float lin = (float)((double)n * (double)v - vsum);
-            s_ig[threadIdx.x] = d.g * (0.8f * (acc * kInvPreScale) + 0.2f * lin);
-        }
+        gap_uniform_pairs<BLOCK>(a, d, t, vd, s_ig, s_red, s_g);
         return;
     }
     if (d.grid == 2) {
