@@ -187,10 +187,13 @@ typedef struct infoli_options {
                                     cells on by a kernel ahead of the step, 2,568 bytes
                                     for each of at most 128 shares of the cells; rows
                                     whose voltages are too far apart, or outside -155 to
-                                    154 mV ahead of the step, take their pairs); 1 => every
+                                    154 mV ahead of the step, take their pairs; by the
+                                    workgroup of the persistent kernel when its launch
+                                    holds a network of more than 192 cells); 1 => every
                                     ordered pair; 2 => each unordered pair once (the pair
                                     term of Section 2.3.1, Algorithm 1, is odd in dV,
-                                    so the pair (j, i) gives minus the term of (i, j)).
+                                    so the pair (j, i) gives minus the term of (i, j));
+                                    the persistent kernel takes every ordered pair.
                                     Once costs
                                     64 x (B/2 + waves + 1) x B floats of partial sums per
                                     network of B = ceil(n/64) blocks (8.4 MB at 16,384

@@ -13,7 +13,8 @@
 // own, the pair terms in the others, a row's terms split over several threads
 // and added in a fixed order; only the dendrite's voltage waits for them.
 // Larger networks give a thread per cell, with all threads sharing the gap
-// currents first (all-to-all: sums on the voltage grid, gap_grid.hpp).
+// currents first (all-to-all: sums on the voltage grid, gap_grid.hpp, or every
+// pair where the caller asks for pairs).
 // Measured per step against 256 threads that each walked whole rows: 96 cells
 // all-to-all 2.75 -> 1.32 us, 192 4.58 -> 2.91, 200 (grid) 4.67 -> 3.84, 1,000
 // 8.74 -> 7.08; 100 cells with 25 connections each 4.63 -> 2.22; 1,000 uncoupled
@@ -35,12 +36,15 @@ constexpr int kPersistParts = 12;                               // threads per r
 constexpr int kPersistPulses = 64;                              // pulses per network
 
 // What the networks of a launch couple by (a lone network's launch compiles its
-// form only; a batch of several forms takes kFormAny).
+// form only; a batch of several forms takes kFormAny). Every pair past a split
+// network is a form of its own: its code beside the grid's cost a step on the
+// grid 0.2 us (200 cells 3.55 -> 3.78).
 enum : int {
     kFormNone = 0,      // no gap junctions, or the simplified all-to-all closed form
     kFormPairs = 1,     // realistic all-to-all
     kFormRows = 2,      // CSR rows or a dense weight matrix
-    kFormAny = 3
+    kFormAny = 3,
+    kFormOrdered = 5    // realistic all-to-all, the caller's choice of pairs
 };
 
 // Gap current of row r from the voltages v in LDS, its terms shared by `parts`
@@ -84,8 +88,7 @@ __device__ __forceinline__ float persist_row(const StepArgs& a, const InstDesc& 
         }
     } else if (FORM & kFormPairs) {
         // a consecutive share, a multiple of four cells, read four at a time
-        // (the lanes of a wave mostly share theirs); past the last cell v holds
-        // copies of the row's own voltage's term zero by the bound below
+        // (the lanes of a wave mostly share theirs), the last ones singly
         const int len = ((n + parts - 1) / parts + 3) & ~3;
         const int j1 = min(n, (sub + 1) * len);
         int j = sub * len;
@@ -123,11 +126,12 @@ __global__ __launch_bounds__(kPersistBlock) void k_persist(StepArgs a, const flo
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int conn = FORM == kFormPairs ? CONN_UNIFORM : d.conn;
-    const bool sgj = FORM == kFormPairs ? false : (bool)d.sgj;
+    constexpr bool uniform = FORM == kFormPairs || FORM == kFormOrdered;
+    const int conn = uniform ? CONN_UNIFORM : d.conn;
+    const bool sgj = uniform ? false : (bool)d.sgj;
     const float g = d.g;
     const bool summed = (FORM == kFormNone || FORM == kFormAny) && conn == CONN_UNIFORM && sgj;              // the closed form g (n Vd_i - sum_j Vd_j)
-    const bool grid = !SPLIT && (FORM & kFormPairs) && conn == CONN_UNIFORM && !sgj;
+    const bool grid = !SPLIT && (FORM == kFormPairs || (FORM == kFormAny && conn == CONN_UNIFORM && !sgj && !d.pairs));
     const float scale = conn == CONN_DENSE || (conn == CONN_CSR && d.has_w) ? 1.0f : g;
     const int n_pulses = d.n_pulses;
     const CellParams p = d.p;
@@ -142,7 +146,8 @@ __global__ __launch_bounds__(kPersistBlock) void k_persist(StepArgs a, const flo
     const int gap_n = SPLIT ? kPersistBlock - 3 * nw * 64 : kPersistBlock;
     // threads per row of the pair terms; consecutive threads for the rows read
     // from memory, consecutive rows where the lanes share the cells they read
-    const bool by_row = (FORM & kFormRows) && (conn == CONN_CSR || conn == CONN_DENSE);
+    const bool by_row = ((FORM & kFormRows) && (conn == CONN_CSR || conn == CONN_DENSE)) ||
+                        (!SPLIT && (FORM == kFormOrdered || (FORM == kFormAny && conn == CONN_UNIFORM && !sgj && !grid)));
     int parts = 1;
     if (SPLIT && !by_row) parts = min(kPersistParts, max(1, gap_n / n));
     else if (by_row)

@@ -514,6 +514,7 @@ void build_sym(infoli_ctx* c) {
         d.psym_off = 0;
         d.sym_ki = 0;
         d.grid = 0;
+        d.pairs = c->opt.pair_path != 0;
         if (d.sgj) {
             if (!sum_once(c, d)) continue;
             d.sym = 1;
@@ -1850,6 +1851,7 @@ void launch_persistent(infoli_ctx* c, int64_t n_steps, bool dry) {
         if (d.conn == CONN_CSR || d.conn == CONN_DENSE) form |= kFormRows;
         else if (d.conn == CONN_UNIFORM && !d.sgj) form |= kFormPairs;
     if (c->n_inst > 1 && form != kFormNone) form = kFormAny;
+    if (form == kFormPairs && c->opt.pair_path && c->persist_cells > kPersistSplit) form = kFormOrdered;
     const auto by_form = [&](auto cpt, auto split) {
         constexpr int C = decltype(cpt)::value;
         constexpr bool S = decltype(split)::value;
@@ -1857,6 +1859,9 @@ void launch_persistent(infoli_ctx* c, int64_t n_steps, bool dry) {
             case kFormNone: return go(k_persist<C, S, kFormNone>);
             case kFormPairs: return go(k_persist<C, S, kFormPairs>);
             case kFormRows: return go(k_persist<C, S, kFormRows>);
+            case kFormOrdered:
+                if constexpr (!S) return go(k_persist<C, S, kFormOrdered>);
+                [[fallthrough]];
             default: return go(k_persist<C, S, kFormAny>);
         }
     };

@@ -93,6 +93,7 @@ struct InstDesc {
     int64_t p0_n0, p0_n1;  // the first pulse (StepArgs::pulses[pulse_off]), an empty window without
     float p0_amp;          // pulses: read with the descriptor, not by a load of its own that the
     int32_t p0_c0, p0_c1;  // cells' waves would wait for before their gap work
+    int32_t pairs;         // UNIFORM, realistic: the caller asked for pairs (pair_path)
     int32_t grid;          // UNIFORM, realistic: sums on the voltage grid, 1 each tile its own, 2
                            // k_grid_sums ahead of the step (partial sums at psym_off)
     CellParams p;
