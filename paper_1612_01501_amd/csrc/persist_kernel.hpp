@@ -18,7 +18,12 @@
 // Measured per step against 256 threads that each walked whole rows: 96 cells
 // all-to-all 2.75 -> 1.32 us, 192 4.58 -> 2.91, 200 (grid) 4.67 -> 3.84, 1,000
 // 8.74 -> 7.08; 100 cells with 25 connections each 4.63 -> 2.22; 1,000 uncoupled
-// cells 3.51 -> 2.12.
+// cells 3.51 -> 2.12. Where a launch has more networks than the chip compute
+// units, and they are small, 256 threads take one (a thread per cell or two), so
+// that a unit holds several: their registers stay at four waves per SIMD and a
+// launch of one form, or without networks for the grid, compiles no more
+// (1,024 networks of 64 to 192 cells of three forms: 11.6 us with 1,024 threads,
+// 8.9 with 256, 8.4 as whole rows per thread).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -31,20 +36,21 @@ namespace infoli {
 constexpr int kPersistBlock = 1024;
 constexpr int kPersistMaxCpt = 2;                               // cells per thread
 constexpr int kPersistCells = kPersistBlock * kPersistMaxCpt;   // 2048
+constexpr int kPersistSmall = 256;                              // threads where compute units hold several networks
 constexpr int kPersistSplit = 192;                              // cells of a split network: three waves a part
 constexpr int kPersistParts = 12;                               // threads per row of its pair terms, at most
 constexpr int kPersistPulses = 64;                              // pulses per network
 
-// What the networks of a launch couple by (a lone network's launch compiles its
-// form only; a batch of several forms takes kFormAny). Every pair past a split
-// network is a form of its own: its code beside the grid's cost a step on the
-// grid 0.2 us (200 cells 3.55 -> 3.78).
+// What the networks of a launch couple by: a launch compiles its form only, one of
+// several forms takes kFormAny. Pairs without the grid are forms of their own
+// (the caller's choice, or no network past a split one's cells): their code beside
+// the grid's cost a step on the grid 0.2 us (200 cells 3.55 -> 3.78).
 enum : int {
     kFormNone = 0,      // no gap junctions, or the simplified all-to-all closed form
     kFormPairs = 1,     // realistic all-to-all
     kFormRows = 2,      // CSR rows or a dense weight matrix
     kFormAny = 3,
-    kFormOrdered = 5    // realistic all-to-all, the caller's choice of pairs
+    kFormOrdered = 4    // added to kFormPairs or kFormAny: pairs only, no grid
 };
 
 // Gap current of row r from the voltages v in LDS, its terms shared by `parts`
@@ -108,30 +114,31 @@ __device__ __forceinline__ float persist_row(const StepArgs& a, const InstDesc& 
     return acc0 + acc1;
 }
 
-template <int CPT, bool SPLIT, int FORM>
-__global__ __launch_bounds__(kPersistBlock) void k_persist(StepArgs a, const float* __restrict__ xin,
+template <int BLOCK, int CPT, bool SPLIT, int FORM>
+__global__ __launch_bounds__(BLOCK, 4) void k_persist(StepArgs a, const float* __restrict__ xin,
                                                            float* __restrict__ xout, int64_t step0,
                                                            int64_t n_steps) {
-    constexpr int CELLS = SPLIT ? kPersistSplit : kPersistBlock * CPT;
-    constexpr int W = kPersistBlock / 64;
+    constexpr int CELLS = SPLIT ? kPersistSplit : BLOCK * CPT;
+    constexpr int W = BLOCK / 64;
     constexpr int GP = kGridMaxGroups * kGridGroup;
     __shared__ __align__(16) float s_v[2][3][CELLS];              // Vd, Vs, Va of the current and the next step
     __shared__ float s_ig[SPLIT ? kPersistParts * CELLS : CELLS];   // (split: the parts' sums)
     __shared__ DevPulse s_pulse[kPersistPulses];
     __shared__ double s_red[W];
     __shared__ float s_mm[3][W];
-    __shared__ double s_g[SPLIT ? 1 : (W + 1) * GP];
+    __shared__ double s_g[!SPLIT && (FORM & kFormPairs) && !(FORM & kFormOrdered) ? (W + 1) * GP : 1];
     const InstDesc& d = a.inst[blockIdx.x];
     const int n = d.n;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    constexpr bool uniform = FORM == kFormPairs || FORM == kFormOrdered;
+    constexpr bool uniform = (FORM & kFormAny) == kFormPairs, any = (FORM & kFormAny) == kFormAny;
+    constexpr bool grids = !SPLIT && (FORM & kFormPairs) && !(FORM & kFormOrdered);
     const int conn = uniform ? CONN_UNIFORM : d.conn;
     const bool sgj = uniform ? false : (bool)d.sgj;
     const float g = d.g;
-    const bool summed = (FORM == kFormNone || FORM == kFormAny) && conn == CONN_UNIFORM && sgj;              // the closed form g (n Vd_i - sum_j Vd_j)
-    const bool grid = !SPLIT && (FORM == kFormPairs || (FORM == kFormAny && conn == CONN_UNIFORM && !sgj && !d.pairs));
+    const bool summed = (FORM == kFormNone || any) && conn == CONN_UNIFORM && sgj;   // the closed form g (n Vd_i - sum_j Vd_j)
+    const bool grid = grids && (uniform || (conn == CONN_UNIFORM && !sgj && !d.pairs && n > kPersistSplit));
     const float scale = conn == CONN_DENSE || (conn == CONN_CSR && d.has_w) ? 1.0f : g;
     const int n_pulses = d.n_pulses;
     const CellParams p = d.p;
@@ -143,11 +150,11 @@ __global__ __launch_bounds__(kPersistBlock) void k_persist(StepArgs a, const flo
     const int role = SPLIT ? wave / nw : 0;
     const bool dend = SPLIT ? role == 0 : true, soma = SPLIT ? role == 1 : true, axon = SPLIT ? role == 2 : true;
     const int gap_t = SPLIT ? tid - 3 * nw * 64 : tid;            // thread of the gap work (< 0: none)
-    const int gap_n = SPLIT ? kPersistBlock - 3 * nw * 64 : kPersistBlock;
+    const int gap_n = SPLIT ? BLOCK - 3 * nw * 64 : BLOCK;
     // threads per row of the pair terms; consecutive threads for the rows read
     // from memory, consecutive rows where the lanes share the cells they read
     const bool by_row = ((FORM & kFormRows) && (conn == CONN_CSR || conn == CONN_DENSE)) ||
-                        (!SPLIT && (FORM == kFormOrdered || (FORM == kFormAny && conn == CONN_UNIFORM && !sgj && !grid)));
+                        (!SPLIT && (FORM & kFormPairs) && !(uniform && grids) && conn == CONN_UNIFORM && !sgj && !grid);
     int parts = 1;
     if (SPLIT && !by_row) parts = min(kPersistParts, max(1, gap_n / n));
     else if (by_row)
@@ -158,7 +165,7 @@ __global__ __launch_bounds__(kPersistBlock) void k_persist(StepArgs a, const flo
     int cell_i[CPT], count[CPT];
 #pragma unroll
     for (int m = 0; m < CPT; ++m) {
-        const int li = SPLIT ? (role < 3 ? tid - role * nw * 64 : n) : tid + m * kPersistBlock;
+        const int li = SPLIT ? (role < 3 ? tid - role * nw * 64 : n) : tid + m * BLOCK;
         cell_i[m] = li;
         bias[m] = 0.0f;
         count[m] = 0;
@@ -175,7 +182,7 @@ __global__ __launch_bounds__(kPersistBlock) void k_persist(StepArgs a, const flo
             if (axon) s_v[0][2][li] = x[m][SV_VA];
         }
     }
-    for (int k = tid; k < n_pulses; k += kPersistBlock) s_pulse[k] = a.pulses[d.pulse_off + k];
+    for (int k = tid; k < n_pulses; k += BLOCK) s_pulse[k] = a.pulses[d.pulse_off + k];
     __syncthreads();
     int64_t slot = a.out_slots ? step0 % a.out_slots : 0;
     const int64_t stream_steps = d.stream_off >= 0 ? d.stream_steps : 0;
@@ -211,7 +218,7 @@ __global__ __launch_bounds__(kPersistBlock) void k_persist(StepArgs a, const flo
         if (summed && (!SPLIT || wave == W - 1)) {
             // the sum in fp64 in a fixed order (split: by the last wave)
             double t = 0.0;
-            for (int j = SPLIT ? lane : tid; j < n; j += SPLIT ? 64 : kPersistBlock) t += (double)vd[j];
+            for (int j = SPLIT ? lane : tid; j < n; j += SPLIT ? 64 : BLOCK) t += (double)vd[j];
             t = grid_wave(t, [](double x, double y) { return x + y; });
             if (lane == 0) s_red[SPLIT ? 0 : wave] = t;
         }
@@ -252,7 +259,7 @@ __global__ __launch_bounds__(kPersistBlock) void k_persist(StepArgs a, const flo
             t = grid_wave(t, [](double x, double y) { return x + y; });
             if (lane == 0) s_red[wave] = t;
             const bool ok = !far && groups <= kGridMaxGroups;
-            const int used = (min(n, kPersistBlock) + 63) / 64;      // waves that hold cells
+            const int used = (min(n, BLOCK) + 63) / 64;      // waves that hold cells
             if (ok) {
                 const double ck = grid_exp((double)((lane & 15) * (lane & 15)) * -0.01);
                 // (group, cells of one wave) over all waves, whether they hold cells or not
@@ -263,7 +270,7 @@ __global__ __launch_bounds__(kPersistBlock) void k_persist(StepArgs a, const flo
                     for (int k = 0; k < kGridGroup; ++k) acc[k] = 0.0;
 #pragma unroll
                     for (int m = 0; m < CPT; ++m) {
-                        const int j = cw * 64 + lane + m * kPersistBlock;
+                        const int j = cw * 64 + lane + m * BLOCK;
                         if (j < n) grid_add(acc, g0 + gr * kGridGroup, vd[j]);
                     }
                     const double f = grid_lane_sum(acc, lane) * ck;
@@ -274,7 +281,7 @@ __global__ __launch_bounds__(kPersistBlock) void k_persist(StepArgs a, const flo
             for (int w = 0; w < W; ++w) tot += s_red[w];
             double* s_f = s_g + W * GP;
             if (ok) {
-                for (int k = tid; k < groups * kGridGroup; k += kPersistBlock) {
+                for (int k = tid; k < groups * kGridGroup; k += BLOCK) {
                     double f = s_g[k];
                     for (int w = 1; w < used; ++w) f += s_g[w * GP + k];
                     s_f[k] = f;

@@ -1840,34 +1840,57 @@ namespace {
 void launch_persistent(infoli_ctx* c, int64_t n_steps, bool dry) {
     StepArgs a = make_args(c, false);
     a.dry = dry ? 1 : 0;
-    const dim3 grid((unsigned)c->n_inst), block(kPersistBlock);
     const float* xin = c->state[c->cur];
     float* xout = c->state[c->cur ^ 1];
-    const auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, c->stream, a, xin, xout, c->step, n_steps);
+    const auto go = [&](auto kernel, int block) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)c->n_inst), dim3((unsigned)block), 0, c->stream, a, xin, xout, c->step,
+                           n_steps);
     };
     int form = kFormNone;
+    bool summed = false;
     for (const InstDesc& d : c->inst)
         if (d.conn == CONN_CSR || d.conn == CONN_DENSE) form |= kFormRows;
         else if (d.conn == CONN_UNIFORM && !d.sgj) form |= kFormPairs;
-    if (c->n_inst > 1 && form != kFormNone) form = kFormAny;
-    if (form == kFormPairs && c->opt.pair_path && c->persist_cells > kPersistSplit) form = kFormOrdered;
+        else if (d.conn == CONN_UNIFORM) summed = true;
+    const bool rows = (form & kFormRows) != 0;
+    if (c->n_inst > 1 && form != kFormNone && (form != kFormRows || summed)) form = kFormAny;
+    const bool ordered = c->opt.pair_path || c->persist_cells <= kPersistSplit;
+    if ((form & kFormPairs) && ordered) form |= kFormOrdered;
     const auto by_form = [&](auto cpt, auto split) {
-        constexpr int C = decltype(cpt)::value;
+        constexpr int B = kPersistBlock, C = decltype(cpt)::value;
         constexpr bool S = decltype(split)::value;
         switch (form) {
-            case kFormNone: return go(k_persist<C, S, kFormNone>);
-            case kFormPairs: return go(k_persist<C, S, kFormPairs>);
-            case kFormRows: return go(k_persist<C, S, kFormRows>);
-            case kFormOrdered:
-                if constexpr (!S) return go(k_persist<C, S, kFormOrdered>);
-                [[fallthrough]];
-            default: return go(k_persist<C, S, kFormAny>);
+            case kFormNone: return go(k_persist<B, C, S, kFormNone>, B);
+            case kFormRows: return go(k_persist<B, C, S, kFormRows>, B);
+            case kFormPairs | kFormOrdered: return go(k_persist<B, C, S, kFormPairs | kFormOrdered>, B);
+            case kFormAny | kFormOrdered: return go(k_persist<B, C, S, kFormAny | kFormOrdered>, B);
+            default: break;
+        }
+        if constexpr (!S) {
+            if (form == kFormPairs) go(k_persist<B, C, S, kFormPairs>, B);
+            else go(k_persist<B, C, S, kFormAny>, B);
+        }
+    };
+    const auto small = [&](auto cpt) {
+        constexpr int B = kPersistSmall, C = decltype(cpt)::value;
+        switch (form) {
+            case kFormNone: return go(k_persist<B, C, false, kFormNone>, B);
+            case kFormRows: return go(k_persist<B, C, false, kFormRows>, B);
+            case kFormAny | kFormOrdered: return go(k_persist<B, C, false, kFormAny | kFormOrdered>, B);
+            default: return go(k_persist<B, C, false, kFormAny>, B);
         }
     };
     const std::integral_constant<int, 1> one{};
     const std::integral_constant<int, 2> two{};
-    if (c->persist_cells <= kPersistSplit) by_form(one, std::true_type{});
+    // More networks than compute units: workgroups of 256 threads, of which a unit
+    // holds several at once (1,024 uncoupled networks of 64 cells 2.3 us a step with
+    // 1,024 threads, 0.8 with 256; all-to-all 5.6 and 3.2; 192 cells of 25
+    // connections 13.2 and 7.8). Two cells a thread pay for rows from twice as many
+    // on (64 to 512 cells of 25 connections, 512 networks 11.7 and 14.2, 1,024 22.2
+    // and 19.2; all-to-all 10.8 and 8.4, 21.0 and 12.7).
+    if (c->n_inst > c->n_cu && c->persist_cells <= kPersistSmall) small(one);
+    else if (c->n_inst > (rows ? 2 : 1) * c->n_cu && c->persist_cells <= 2 * kPersistSmall) small(two);
+    else if (c->persist_cells <= kPersistSplit) by_form(one, std::true_type{});
     else if (c->persist_cells <= kPersistBlock) by_form(one, std::false_type{});
     else by_form(two, std::false_type{});
     if (dry) return;

@@ -28,3 +28,46 @@ def test_pair_path_holds_in_the_persistent_kernel(infoli, o32, o64, n):
     r64 = o64.run(net, 60, x0=x0.astype(np.float64))["x"]
     for x in (end[0], end[1]):
         check_state_bounds(x[None], ref[None], r64[None], f"persistent {n}")
+
+
+def network(kind, n, seed):
+    rs = I.rng(seed)
+    kw = dict(jitter=rs.uniform(-10, 10, (3, n)), bias=I.input_bias(n, seed), g=0.04 * 96 / max(n, 96),
+              pulses=[I.Pulse(5, 30, 6.0), I.Pulse(20, 50, -2.0, 0, max(1, n // 2))])
+    if kind == "csr":
+        rp, col = I.erdos_renyi_csr(n, min(1.0, 20.0 / max(n - 1, 1)), seed)
+        return I.Network(n=n, conn="csr", row_ptr=rp, col=col, **kw)
+    if kind == "dense":
+        return I.Network(n=n, conn="dense", w_dense=rs.uniform(0, 2 * kw["g"], (n, n)).astype(np.float32), **kw)
+    return I.Network(n=n, conn="uniform" if kind == "sgj" else kind, gap="sgj" if kind == "sgj" else "rgj", **kw)
+
+
+@pytest.mark.parametrize("kinds", ["uniform", "csr", "dense", "none", "sgj", "uniform csr none", "csr sgj", "none sgj",
+                                   "uniform dense"])
+@pytest.mark.parametrize("most,count", [(64, 300), (192, 300), (256, 300), (257, 300), (512, 600), (513, 300)])
+@pytest.mark.parametrize("path", [0, 1])
+def test_batches_past_a_network_for_each_unit(infoli, o32, o64, kinds, most, count, path):
+    """More networks than compute units (256 threads each, one or two cells a
+    thread; 1,024 above), of one form and of several, most of them tiny: 60 steps
+    in launches of odd lengths against the oracle."""
+    kinds = kinds.split()
+    if path and "uniform" not in kinds:
+        pytest.skip("pair_path concerns all-to-all networks")
+    big = [most, most - 1, 65, 193 if most > 193 else 33]
+    sizes = [big[k] if k < len(big) else 1 + k % 7 for k in range(count)]
+    nets = [network(kinds[k % len(kinds)], n, k + most) for k, n in enumerate(sizes)]
+    x0s = [infoli.initial_state(net) for net in nets]
+    sim = infoli.Simulator(nets, init_states=x0s, step_mode="persistent", output_ring_steps=16, pair_path=path)
+    for steps in (7, 1, 52):
+        sim.step(steps)
+    out = np.zeros((16, sum(sizes)), np.float32)
+    sim.output_copy_async(44, 16, out.ctypes.data, out.size)
+    sim.output_wait()
+    at = np.concatenate([[0], np.cumsum(sizes)])
+    for k in (0, 1, 2, 3, 4, count - 1):
+        got = sim.read_state(k)
+        np.testing.assert_array_equal(out[-1, at[k]:at[k + 1]], got[11])
+        ref = o32.run(nets[k], 60, x0=x0s[k])["x"]
+        r64 = o64.run(nets[k], 60, x0=x0s[k].astype(np.float64))["x"]
+        check_state_bounds(got[None], ref[None], r64[None], f"batch {kinds} {sizes[k]}")
+    sim.close()
