@@ -76,7 +76,7 @@ struct SurrogateState {
     uint16_t* wb = nullptr;             // bf16 copies
     float norm[64] = {0};               // in_mean[16] in_rstd[16] out_mean[16] out_std[16]
     int32_t* hold = nullptr;            // [cells]
-    unsigned long long* counters = nullptr;   // [4] plain, checked, flagged, guarded
+    unsigned long long* counters = nullptr;   // [workgroups][4] plain, checked, flagged, guarded
     TileGroup gap;                      // the macro steps' gap launch, and its descriptor
     InstDesc* gap_inst = nullptr;       //   (null: the plain steps' launches)
 };

@@ -4,6 +4,7 @@
 #include "context.hpp"
 #include "surrogate_kernel.hpp"
 
+#include <array>
 #include <mutex>
 
 using namespace infoli_rt;
@@ -50,6 +51,18 @@ NormStats norm_of(const float* n64) {
     return ns;
 }
 
+// Workgroups of a macro step at most (the four-wave ones).
+int surr_groups(const infoli_ctx* c) { return 3 * c->n_cu; }
+
+// The report's counts so far, summed over the workgroups; the stream is drained.
+std::array<unsigned long long, 4> read_counters(const infoli_ctx* c) {
+    std::vector<unsigned long long> h(4 * (size_t)surr_groups(c));
+    HIPX(hipMemcpy(h.data(), c->surr.counters, sizeof(unsigned long long) * h.size(), hipMemcpyDeviceToHost));
+    std::array<unsigned long long, 4> sum{};
+    for (size_t k = 0; k < h.size(); ++k) sum[k & 3] += h[k];
+    return sum;
+}
+
 void ensure_surrogate_buffers(infoli_ctx* c) {
     SurrogateState& s = c->surr;
     if (s.params) return;
@@ -59,9 +72,9 @@ void ensure_surrogate_buffers(infoli_ctx* c) {
     s.grad = c->alloc<float>((size_t)kNumParams * kGradSplits);   // split-K partials
     s.wb = c->alloc<uint16_t>(kNumParams);
     s.hold = c->alloc<int32_t>(c->stride);
-    s.counters = c->alloc<unsigned long long>(4);
+    s.counters = c->alloc<unsigned long long>(4 * (size_t)surr_groups(c));
     HIPX(hipMemset(s.hold, 0, sizeof(int32_t) * c->stride));
-    HIPX(hipMemset(s.counters, 0, sizeof(unsigned long long) * 4));
+    HIPX(hipMemset(s.counters, 0, sizeof(unsigned long long) * 4 * surr_groups(c)));
     plan_surrogate_gap(c, s.gap, &s.gap_inst);
     s.params = params;      // last: a call that failed half-way is made anew
 }
@@ -138,7 +151,7 @@ void launch_macro(infoli_ctx* c, hipStream_t st, const infoli_drift_cfg& dc, int
                            s, c->state[from], c->state[from ^ 1], step0, cells);
     };
     if (cells >= (int64_t)surr_cells(256) * c->n_cu) go(k_surrogate_step<512>, 512, 2 * (int64_t)c->n_cu);
-    else go(k_surrogate_step<256>, 256, 3 * (int64_t)c->n_cu);
+    else go(k_surrogate_step<256>, 256, surr_groups(c));
 }
 
 // ---------------------------------------------------------------- gradient
@@ -471,9 +484,9 @@ infoli_status infoli_step_surrogate(infoli_ctx* ctx, int64_t n_macro, const info
         ensure_surrogate_buffers(ctx);
         if (dc.mode == INFOLI_SURROGATE_MLP && !ctx->surr.ready)
             fail(INFOLI_E_STATE, "no surrogate trained or set");
-        unsigned long long before[4];
+        std::array<unsigned long long, 4> before{};
         HIPX(hipStreamSynchronize(ctx->stream));
-        HIPX(hipMemcpy(before, ctx->surr.counters, sizeof(before), hipMemcpyDeviceToHost));
+        if (rep) before = read_counters(ctx);
         HIPX(hipEventRecord(ctx->ev0, ctx->stream));
         for (int64_t m = 0; m < n_macro; ++m) {
             launch_macro(ctx, ctx->stream, dc, ctx->cur, ctx->step);
@@ -485,8 +498,7 @@ infoli_status infoli_step_surrogate(infoli_ctx* ctx, int64_t n_macro, const info
         ctx->timed = true;
         if (rep) {
             HIPX(hipEventSynchronize(ctx->ev1));
-            unsigned long long after[4];
-            HIPX(hipMemcpy(after, ctx->surr.counters, sizeof(after), hipMemcpyDeviceToHost));
+            const auto after = read_counters(ctx);
             std::memset(rep, 0, sizeof(*rep));
             rep->plain_cell_macro_steps = (int64_t)(after[0] - before[0]);
             rep->checked = (int64_t)(after[1] - before[1]);

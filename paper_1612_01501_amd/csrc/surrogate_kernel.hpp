@@ -34,7 +34,9 @@ struct SurrArgs {
     NormStats norm;
     const float* igap;          // [cells] held gap currents
     int32_t* hold;              // [cells] macro steps left on the plain method
-    unsigned long long* counters;   // [0] cells on plain, [1] checked, [2] flagged, [3] guarded
+    unsigned long long* counters;   // per workgroup: [0] cells on plain, [1] checked, [2] flagged,
+                                    // [3] guarded (one line for all took 4.3 us of 512 workgroups'
+                                    // atomics at 65,536 cells)
     float theta_mv;             // drift threshold on Vd, Vs, Va
     float v_max;                // regime served by the MLP: every voltage <= v_max
     float ca_max;               //   and [Ca] <= ca_max
@@ -77,11 +79,12 @@ constexpr int surr_plain(int block) { return block / 128 * 64; }   // cells of o
 // (16,384 cells of which a fifth were held: 17.3 us, 8.8 without any), and the
 // listed cells' kernel took another 8.0 us for four steps of any number of
 // cells. A macro step with its gap kernel, 1/64 of the cells checked:
-// 16,384 cells 40.4 -> 30.6 us, 65,536 cells 74.9 -> 36.4, 1,500 cells 22.1 ->
+// 16,384 cells 40.4 -> 28.0 us, 65,536 cells 74.9 -> 36.4, 1,500 cells 22.1 ->
 // 20.2; where hardly a cell is listed the launch saved and the chain of cell
-// steps in every workgroup cancel (65,536 cells of degree 1,000, none held: 54.3
-// -> 55.1). What is left is a chain: weights to LDS, the layers' matrix products
-// each on the one before, then four dependent cell steps.
+// steps in every workgroup cancel (65,536 cells of degree 1,000, none held:
+// 51.8 us either way, 54.5 while all workgroups counted in one line; 2,000 cells
+// with none checked 13.3 -> 13.6). What is left is a chain: weights to LDS, the
+// layers' matrix products each on the one before, then four dependent cell steps.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK, 4) void k_surrogate_step(StepArgs a, SurrArgs s, const float* __restrict__ xin,
                                                              float* __restrict__ xout, int64_t step0,
@@ -287,12 +290,11 @@ __global__ __launch_bounds__(BLOCK, 4) void k_surrogate_step(StepArgs a, SurrArg
         __syncthreads();
         const int listed = s_count;
         __syncthreads();                           // (read by all before the next pass adds to it)
-        if (listed > PLAIN - CELLS) plain_phase();
+        const bool last = pass + (int64_t)gridDim.x * CELLS >= n_cells_total;
+        if (listed > (last ? 0 : PLAIN - CELLS)) plain_phase();
     }
-    __syncthreads();
-    if (s_count > 0) plain_phase();
     if (threadIdx.x < 4 && s_sum[threadIdx.x])
-        atomicAdd(&s.counters[threadIdx.x], (unsigned long long)s_sum[threadIdx.x]);
+        s.counters[4 * blockIdx.x + threadIdx.x] += (unsigned long long)s_sum[threadIdx.x];
 }
 
 // Four plain forward-Euler steps per cell with the macro step's gap current
