@@ -313,7 +313,7 @@ bool flat_ok(const infoli_ctx* c, int k, int rows) {
 // otherwise.
 int group_for(const InstDesc& d) {
     if (d.conn == CONN_CSR && (d.blocked || d.wide)) return 1;
-    if (d.conn == CONN_UNIFORM && d.grid) return d.wide;
+    if (d.conn == CONN_UNIFORM && d.grid) return d.wide || (d.grid == 1 && d.n >= 4096);
     if (d.conn == CONN_UNIFORM && !(d.sgj && d.sym) && (d.n >= 4096 || d.wide)) return 1;
     return 0;
 }
@@ -1506,18 +1506,18 @@ void build_context(infoli_ctx* c, const infoli_network_spec* specs, int32_t nins
         if (c->inst[k].conn == CONN_CSR && c->inst[k].n > 65536) col16 = false;
     c->rows_of.assign(ninst, kMaxTileRows);
     c->deg_of.assign(ninst, 0.0);
-    // All-to-all networks on the voltage grid: a row per thread, so that the sums
-    // are taken (or added) for 256 rows at once, where the context has more than
-    // a compute unit's 64 rows for each; one row per lane below, where the other
-    // units stand idle: the same chain of work beside more of them, and a tile
-    // whose voltages ask for its pairs has a quarter of them.
-    const bool narrow_grid = cells <= (int64_t)kUniformRows * c->n_cu;
+    // All-to-all networks on the voltage grid: about a tile for each compute unit, of
+    // 64 rows (one per lane) to 256 (a row per thread): fewer tiles take the sums
+    // fewer times, more leave no unit idle, and one whose voltages ask for its pairs
+    // has fewer of them.
+    int grid_rows = kUniformRows;
+    while (grid_rows < kMaxTileRows && cells > (int64_t)grid_rows * c->n_cu) grid_rows *= 2;
     for (int k = 0; k < ninst; ++k) {
         InstDesc& d = c->inst[k];
         int rows;
         switch (d.conn) {
             case CONN_UNIFORM:   // one row per lane; a row per thread when the sum is taken once
-                rows = sum_once(c, d) || (grid_kind(c, d) && !narrow_grid) ? kMaxTileRows : kUniformRows;
+                rows = sum_once(c, d) ? kMaxTileRows : grid_kind(c, d) ? grid_rows : kUniformRows;
                 c->deg_of[k] = grid_kind(c, d) ? d.n / 32.0 : d.n;
                 break;
             case CONN_DENSE: rows = c->opt.tile_rows ? c->opt.tile_rows : kDenseRows; c->deg_of[k] = d.n; break;

@@ -426,9 +426,9 @@ __device__ __forceinline__ void gap_uniform_pairs(const StepArgs& a, const InstD
             const int m = min(64, j1 - j);
             float a0 = 0.0f, a1 = 0.0f;
             int k = 0;
-            for (; k + 8 <= m; k += 8) {
+            for (; k + 16 <= m; k += 16) {
 #pragma unroll
-                for (int e = 0; e < 8; e += 2) {
+                for (int e = 0; e < 16; e += 2) {
                     const float d0 = v - cell(k + e), d1 = v - cell(k + e + 1);
                     a0 = fmaf(d0, __builtin_amdgcn_exp2f(-(d0 * d0) * kL2eOver100), a0);
                     a1 = fmaf(d1, __builtin_amdgcn_exp2f(-(d1 * d1) * kL2eOver100), a1);
