@@ -220,14 +220,16 @@ def gap_paths(info, sim, nets):
 
 def tuned_config(info, sim, nets):
     """What the library runs for these networks, as chosen at init."""
+    paths = gap_paths(info, sim, nets)
     return {"tiles": info["n_tiles"], "tiles_wide": info["n_tiles_wide"], "wide_threads": info["wide_threads"],
             "csr_bitmap_networks": info["n_bitmap"], "csr_blocked_networks": info["n_blocked"],
             "lanes_per_row": info["lanes_per_row"], "tile_rows": info["tile_rows"],
-            "gap_paths": sorted(set(gap_paths(info, sim, nets))),
-            "step_kernel": step_kernel_name(info, nets, gap_paths(info, sim, nets)),
+            "gap_paths": sorted(set(paths)),
+            "step_kernel": step_kernel_name(info, nets, paths),
             "tuned_networks": info["tuned"], "tune_cached_networks": info["tune_cached"],
             "csr_stream_networks": info["n_stream"], "tune_mode": info["tune_mode"],
-            "stream_round": info["stream_round"], "unordered_pair_networks": info["n_sym"]}
+            "stream_round": info["stream_round"], "sums_ahead_networks": info["n_sym"],
+            "unordered_pair_networks": sum(p == "uniform_sym" for p in paths)}
 
 
 WORKLOADS = {
