@@ -309,8 +309,8 @@ bool flat_ok(const infoli_ctx* c, int k, int rows) {
 
 // Launch group of a network: the wide group (1024- or 512-thread
 // workgroups) for column blocks, CSR or all-to-all networks the tuner marked
-// wide, and all-to-all networks of >= 4,096 cells; 256-thread workgroups
-// otherwise.
+// wide, and all-to-all networks of >= 4,096 cells whose tiles evaluate pairs or
+// sum the grid themselves; 256-thread workgroups otherwise.
 int group_for(const InstDesc& d) {
     if (d.conn == CONN_CSR && (d.blocked || d.wide)) return 1;
     if (d.conn == CONN_UNIFORM && d.grid) return d.wide || (d.grid == 1 && d.n >= 4096);

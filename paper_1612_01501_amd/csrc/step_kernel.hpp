@@ -11,8 +11,11 @@
 //                staged in LDS in chunks and read as wave-wide broadcasts.
 //                w = g is factored out and the linear part 0.2*sum_j dV is
 //                taken in closed form, 0.2*(n*Vd_i - sum_j Vd_j), in fp64.
-//   DENSE        lanes = sending cells j of one row (coalesced weight rows),
-//                one row per wave at a time, butterfly reduction.
+//                From kGridCells cells on by default: sums on a grid of
+//                voltages, interpolated at each row (gap_grid.hpp).
+//   DENSE        lanes = four consecutive sending cells each of four rows
+//                (coalesced weight rows), the waves a share of the columns,
+//                butterfly reduction.
 //   BITMAP       (CSR networks with one weight g, when faster) the coupling
 //                pattern as one bit per pair: 16 receiving cells per wave,
 //                four lane groups per cell take interleaved 32-sender blocks
@@ -379,7 +382,7 @@ __device__ __forceinline__ void gap_uniform_sum(const StepArgs& a, const InstDes
 // Every pair of the tile's rows, 64 rows at a time: a lane per row, a wave's share
 // of the cells 64 at a time, a lane each to load (the next ones ahead) and then one
 // after the other for all rows, their terms' sums added up in fp64 (2,000 cells
-// 14.6 us a step; through LDS, 1,024 cells at a time, 16.1). Where k_grid_sums took
+// 14.3 us a step; through LDS, read four at a time by all lanes, 16.5). Where k_grid_sums took
 // the voltages' sum and it is not finite, a voltage is not, and no row's terms are
 // (an infinite difference times e^-inf is a NaN).
 template <int BLOCK>
@@ -457,7 +460,7 @@ __device__ __forceinline__ void gap_uniform_pairs(const StepArgs& a, const InstD
 // All-to-all networks with the realistic term on the voltage grid
 // (gap_grid.hpp): up to BLOCK rows, one per thread. The tile takes the grid
 // points its own rows' voltages need; it sums the cells' terms there itself,
-// or (AHEAD) adds the shares' sums k_grid_sums wrote, in a fixed order either
+// or (d.grid 2) adds the shares' sums k_grid_sums wrote, in a fixed order either
 // way. A tile whose rows hold a voltage that is not finite or, ahead, outside
 // the grid, or are so far apart that its own sums cost more than the pairs,
 // takes every pair (grid_tile_groups).
@@ -1731,8 +1734,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const float* __rest
         for (int k = threadIdx.x; k < nrows; k += BLOCK) a.igap_out[t.cell_off + t.row0 + k] = s_ig[k];
         return;
     }
-    // per-cell parameters exist in the general variant only (the runtime
-    // launches networks that have them with it)
+    // per-cell parameters exist in the var_cells variants only (the runtime
+    // launches networks that have them with those)
     CellParams pc = d.p;
     if constexpr (var_cells(VAR)) {
         if (own) pc = cell_params_of(a, d, cell);
@@ -1793,8 +1796,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const float* __rest
 }
 
 // The step. Vd staging in dynamic LDS, sized per launch: the largest
-// all-to-all chunk (min(n, kChunk) + 8 per wave) or the largest LDS-staged
-// CSR network. The chunk stream variant has no static LDS, so its staged
+// all-to-all chunk (min(n, kChunk) + 8 per wave), the grid's sums, the largest
+// flat tile or the largest LDS-staged CSR network. The chunk stream variant has no static LDS, so its staged
 // voltages start at LDS address 0 (a gather's address is its column times
 // four, with no base to add) and its row sums follow the stream's region; the
 // same holds for the var_vd_first variants.
