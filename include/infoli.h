@@ -159,7 +159,7 @@ typedef struct infoli_options {
     int32_t check_finite;        /* 1 => a NaN/Inf state makes infoli_sync fail            */
     int32_t autotune;            /* CSR tile shapes: 0 => built-in rule; 1 => timed on the
                                     device at init, cached on disk (INFOLI_TUNE_CACHE, else
-                                    ~/.cache/infoli-tune-v15.txt); 2 => timed, cache ignored */
+                                    ~/.cache/infoli-tune-v16.txt); 2 => timed, cache ignored */
     int32_t csr_path;            /* CSR networks: 0 => tuned choice; 1 => edge gathers;
                                     2 => coupling bitmap (one weight g, <= 16,384 cells;
                                     in the wide group when wide_threads is set);
@@ -320,7 +320,9 @@ typedef struct infoli_info {
                                    1024-thread shape, 16 wide group of 512 threads, 32
                                    every class with a bitmap shape and a density of a
                                    fifth or more on it, 64 every class in the highest
-                                   chunked tiles)                                         */
+                                   chunked tiles, 128 all-to-all networks of >= 4,096
+                                   cells that sum the voltage grid themselves in the
+                                   wide group)                                            */
     int32_t stream_round;       /* chunks per round of the chunk stream networks (the
                                    largest; 8,192 or 4,096 as the tuner timed), 0 none    */
     int32_t n_sym;              /* all-to-all networks whose sums a kernel ahead of the

@@ -310,10 +310,11 @@ bool flat_ok(const infoli_ctx* c, int k, int rows) {
 // Launch group of a network: the wide group (1024- or 512-thread
 // workgroups) for column blocks, CSR or all-to-all networks the tuner marked
 // wide, and all-to-all networks of >= 4,096 cells whose tiles evaluate pairs or
-// sum the grid themselves; 256-thread workgroups otherwise.
+// (where no other network would need a launch beside theirs) sum the grid
+// themselves; 256-thread workgroups otherwise.
 int group_for(const InstDesc& d) {
     if (d.conn == CONN_CSR && (d.blocked || d.wide)) return 1;
-    if (d.conn == CONN_UNIFORM && d.grid) return d.wide || (d.grid == 1 && d.n >= 4096);
+    if (d.conn == CONN_UNIFORM && d.grid) return d.wide || d.grid_wide;
     if (d.conn == CONN_UNIFORM && !(d.sgj && d.sym) && (d.n >= 4096 || d.wide)) return 1;
     return 0;
 }
@@ -375,9 +376,10 @@ void finalize_tiles(infoli_ctx* c) {
     // launch with other tiles, or has weights or per-cell parameters, takes
     // the chunked column blocks instead
     {
-        bool mixed[2] = {false, false};
-        for (int k = 0; k < c->n_inst; ++k) {
-            const InstDesc& d = c->inst[k];
+        bool alone = true, mixed[2] = {false, false};
+        for (const InstDesc& d : c->inst) alone = alone && d.grid == 1 && d.n >= 4096;
+        for (InstDesc& d : c->inst) {
+            d.grid_wide = alone;
             const bool st = d.conn == CONN_CSR && d.blocked && d.stream && d.cb_off >= 0 && !d.has_w && !d.pcell &&
                             d.nblk <= kStreamMaxBlocks && d.cell_off % 4 == 0 && stream_ok(c);
             if (!st) mixed[group_for(d)] = true;
@@ -723,7 +725,7 @@ void build_chunks(infoli_ctx* c, const infoli_network_spec* specs) {
 // timed on the network's own device data with dry launches (they write only
 // the next-state buffer) replayed from graphs, as steps run, and the fastest
 // is kept, in memory and in an
-// on-disk cache (INFOLI_TUNE_CACHE, else ~/.cache/infoli-tune-v15.txt).
+// on-disk cache (INFOLI_TUNE_CACHE, else ~/.cache/infoli-tune-v16.txt).
 struct TuneChoice {
     int L, R, lds, bm;     // lanes per row, rows per tile, Vd in LDS,
                            // path (0 gathers, 1 bitmap, 2 blocked, 3 chunked gathers,
@@ -736,7 +738,7 @@ std::string tune_cache_path() {
     const char* p = std::getenv("INFOLI_TUNE_CACHE");
     if (p && *p) return p;
     const char* h = std::getenv("HOME");
-    if (h && *h) return std::string(h) + "/.cache/infoli-tune-v15.txt";
+    if (h && *h) return std::string(h) + "/.cache/infoli-tune-v16.txt";
     return "";
 }
 
@@ -749,8 +751,8 @@ std::string tune_key(const infoli_ctx* c, const InstDesc& d, double deg) {
     return buf;
 }
 
-// Whole-step launch modes: seven bits (see the tuner below), so 0..127.
-constexpr int kStepModes = 128;
+// Whole-step launch modes: eight bits (see the tuner below), so 0..255.
+constexpr int kStepModes = 256;
 
 // Lines "<class key>|L R lds bm block" (the class's best shape),
 // "<class key>#256|..." (its best shape in 256-thread workgroups) and
@@ -1186,8 +1188,9 @@ void autotune_shapes(infoli_ctx* c) {
     // non-chunked 256-thread shape; bit 5, every class with a bitmap shape
     // and a density of a fifth or more takes it (in 1024 threads under bit 3
     // when timed, else in 256): timed alone a class can rank the bitmap and its
-    // gathers differently from the whole step; bit 6 (alone or with bit 1),
-    // every class in its highest flat tiles
+    // gathers differently from the whole step; bit 6 (alone or with bits 1 and 7),
+    // every class in its highest flat tiles; bit 7, the all-to-all networks of
+    // 4,096 cells or more that sum the grid themselves in the wide group
     auto pick = [&](const ClassChoice& ch, int m) {
         if ((m & 32) && ch.bits)
             return ((m & 8) && ch.bm1024.block) || !ch.bm256.block ? ch.bm1024 : ch.bm256;
@@ -1200,11 +1203,12 @@ void autotune_shapes(infoli_ctx* c) {
     auto wide_block = [&](int m) { return c->opt.wide_threads ? c->opt.wide_threads : (m & 16) ? 512 : 1024; };
     auto apply_all = [&](int m) {
         for (const auto& kv : classes) apply_choice(c, kv.second, pick(chosen[kv.first], m));
-        // bit 3 also moves every all-to-all network into the wide group
-        for (int k = 0; k < c->n_inst; ++k)
-            if (c->inst[k].conn == CONN_UNIFORM) c->inst[k].wide = (m & 8) ? 1 : 0;
+        // bit 3 also moves every all-to-all network into the wide group, bit 7 those
+        // of 4,096 cells or more that sum the grid themselves
+        for (InstDesc& d : c->inst)
+            if (d.conn == CONN_UNIFORM) d.wide = (m & 8) || ((m & 128) && d.grid == 1 && d.n >= 4096) ? 1 : 0;
     };
-    // bits 0, 2, 3 and 5 as above; bit 1: the two launch groups one after the
+    // bits 0, 2, 3 and 5 to 7 as above; bit 1: the two launch groups one after the
     // other; bit 4: the wide launch group in 512-thread workgroups (two per
     // compute unit, so one can stage a column block while the other gathers)
     int mode = 0;
@@ -1216,6 +1220,9 @@ void autotune_shapes(infoli_ctx* c) {
         for (int i = 0; i < ncls; ++i) refine[i] = mh->second[1 + i];
     } else {
         bool wide = false, chunk = false, narrow = false, bits = false, tall = false;   // variants that change something
+        bool grids = false;
+        for (const InstDesc& d : c->inst) grids = grids || (d.grid == 1 && d.n >= 4096);
+        grids = grids && ncls > 0;      // (all-to-all networks alone have one launch as it is)
         for (const auto& kv : chosen) {
             bits = bits || kv.second.bits;
             tall = tall || kv.second.tall.block;
@@ -1230,7 +1237,8 @@ void autotune_shapes(infoli_ctx* c) {
             for (int m = 0; m < kStepModes; ++m) {
                 if (((m & 1) && !wide) || ((m & 4) && !chunk) || ((m & 8) && (!narrow || (m & 1)))) continue;
                 if ((m & 32) && !bits) continue;
-                if ((m & 64) && (!tall || (m & ~66))) continue;
+                if ((m & 64) && (!tall || (m & ~(64 | 2 | 128)))) continue;
+                if ((m & 128) && (!grids || (m & 8))) continue;
                 if ((m & 16) && c->opt.wide_threads) continue;
                 apply_all(m);
                 c->grp[1].block = wide_block(m);
@@ -1509,9 +1517,13 @@ void build_context(infoli_ctx* c, const infoli_network_spec* specs, int32_t nins
     // All-to-all networks on the voltage grid: about a tile for each compute unit, of
     // 64 rows (one per lane) to 256 (a row per thread): fewer tiles take the sums
     // fewer times, more leave no unit idle, and one whose voltages ask for its pairs
-    // has fewer of them.
+    // has fewer of them. 256 rows beside connection lists or weight matrices, whose
+    // tiles leave no unit idle (7,680 cells beside a graph of as many, a half of the
+    // pairs: 44.6 us a step, 49.1 with 64 rows).
     int grid_rows = kUniformRows;
-    while (grid_rows < kMaxTileRows && cells > (int64_t)grid_rows * c->n_cu) grid_rows *= 2;
+    bool lists = false;
+    for (const InstDesc& d : c->inst) lists = lists || d.conn == CONN_CSR || d.conn == CONN_DENSE;
+    while (grid_rows < kMaxTileRows && (lists || cells > (int64_t)grid_rows * c->n_cu)) grid_rows *= 2;
     for (int k = 0; k < ninst; ++k) {
         InstDesc& d = c->inst[k];
         int rows;

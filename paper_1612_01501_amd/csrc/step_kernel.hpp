@@ -76,7 +76,7 @@ struct InstDesc {
     int32_t bitmap;        // CSR with uniform g: gap from the coupling bitmap
     int32_t blocked;       // CSR: Vd staged in LDS one column block at a time
     int32_t nblk;          // blocked: number of column blocks
-    int32_t wide;          // bitmap: run in the 1024-thread launch group
+    int32_t wide;          // run in the wide launch group
     int32_t chunked;       // CSR from the chunked rows layout
     int32_t flat;          //   as one flat run of chunks per tile, Vd in LDS
     int32_t sgj;           // simplified (linear) gap junctions: term w * dV
@@ -97,6 +97,7 @@ struct InstDesc {
     float p0_amp;          // pulses: read with the descriptor, not by a load of its own that the
     int32_t p0_c0, p0_c1;  // cells' waves would wait for before their gap work
     int32_t pairs;         // UNIFORM, realistic: the caller asked for pairs (pair_path)
+    int32_t grid_wide;     // UNIFORM on the grid: run in the wide launch group, with others like it alone
     int32_t grid;          // UNIFORM, realistic: sums on the voltage grid, 1 each tile its own, 2
                            // k_grid_sums ahead of the step (partial sums at psym_off)
     CellParams p;
@@ -1501,17 +1502,16 @@ __device__ __forceinline__ void gap_csr_form(const StepArgs& a, const InstDesc& 
             by_weights<W>(d, [&](auto hw) { gap_flat<BLOCK, decltype(hw)::value, SGJ, var_vd_first(VAR)>(a, d, t, vd, s_vd, s_ig); });
             return;
         }
-        if (d.chunked && d.ca_off >= 0) {
-            by_weights<W>(d, [&](auto hw) { gap_chunks<BLOCK, decltype(hw)::value, SGJ>(a, d, t, vd, s_part, s_ig); });
-            return;
-        }
-        if (d.vd_lds) {
+        const bool chunks = d.chunked && d.ca_off >= 0;
+        if (d.vd_lds && !chunks) {
             for (int k = threadIdx.x; k < d.n; k += BLOCK) s_vd[k] = vd[k] * kPreScale;
             __syncthreads();
         }
         by_weights<W>(d, [&](auto hw) {
             constexpr bool HW = decltype(hw)::value;
-            if (d.vd_lds) {
+            if (chunks) {
+                gap_chunks<BLOCK, HW, SGJ>(a, d, t, vd, s_part, s_ig);
+            } else if (d.vd_lds) {
                 if (d.col16) gap_csr_impl<BLOCK, true, true, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
                 else gap_csr_impl<BLOCK, true, false, HW, SGJ>(a, d, t, vd, s_vd, s_part, s_ig);
             } else {

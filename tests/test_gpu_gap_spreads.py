@@ -67,3 +67,27 @@ def test_a_bad_voltage_reaches_every_row(infoli, n, spread, others):
     sim.step(2)
     assert not np.any(np.isfinite(sim.read_gap_current(0)))
     sim.close()
+
+
+@pytest.mark.parametrize("path,gap_path", [(5, ("csr_stream", True)), (1, ("csr_gather", False)), (0, None)])
+def test_launches_of_large_grid_networks(infoli, o64, path, gap_path):
+    """Large all-to-all networks that sum the grid themselves run in the wide
+    workgroups where all networks are such, and not (but by the tuner's choice)
+    where the others would need a launch beside theirs."""
+    from test_gpu_gap_forms import check_gap, er_net
+    csr = er_net(20000, 40, 3)
+    uni = [I.Network(n=n, conn="uniform", g=0.04 * 96 / n, jitter=I.voltage_jitter(n, 5, 10.0)) for n in (5001, 4096)]
+    for nets in ([csr] + uni, uni):
+        x0s = [infoli.initial_state(m) for m in nets]
+        sim = infoli.Simulator(nets, init_states=x0s, csr_path=path, step_mode="graph")
+        info = sim.info()
+        if nets is uni:
+            assert info["n_tiles_wide"] == info["n_tiles"]
+        elif gap_path:
+            assert sim.gap_path(0) == gap_path
+            assert info["n_tiles_wide"] == (79 if path == 5 else 0)
+        for k, (net, x0) in enumerate(zip(nets, x0s)):
+            check_gap(sim, k, net, x0[0], o64)
+        sim.step(2)
+        sim.sync()
+        sim.close()
