@@ -42,17 +42,14 @@ def network(kind, n, seed):
     return I.Network(n=n, conn="uniform" if kind == "sgj" else kind, gap="sgj" if kind == "sgj" else "rgj", **kw)
 
 
-@pytest.mark.parametrize("kinds", ["uniform", "csr", "dense", "none", "sgj", "uniform csr none", "csr sgj", "none sgj",
-                                   "uniform dense"])
+@pytest.mark.parametrize("kinds,path", [(k, 0) for k in ("csr", "dense", "none", "sgj", "csr sgj", "none sgj")] +
+                         [(k, p) for k in ("uniform", "uniform csr none", "uniform dense") for p in (0, 1)])
 @pytest.mark.parametrize("most,count", [(64, 300), (192, 300), (256, 300), (257, 300), (512, 600), (513, 300)])
-@pytest.mark.parametrize("path", [0, 1])
 def test_batches_past_a_network_for_each_unit(infoli, o32, o64, kinds, most, count, path):
     """More networks than compute units (256 threads each, one or two cells a
     thread; 1,024 above), of one form and of several, most of them tiny: 60 steps
     in launches of odd lengths against the oracle."""
     kinds = kinds.split()
-    if path and "uniform" not in kinds:
-        pytest.skip("pair_path concerns all-to-all networks")
     big = [most, most - 1, 65, 193 if most > 193 else 33]
     sizes = [big[k] if k < len(big) else 1 + k % 7 for k in range(count)]
     nets = [network(kinds[k % len(kinds)], n, k + most) for k, n in enumerate(sizes)]
